@@ -33,18 +33,21 @@ struct alignas(16) SrcRec {
     double c0[3];
     double e1[3];
     double e2[3];
-    double e3[3];     // e1 x e2
+    // circular, linear: omega / c, its square, 2 amp omega^2 / c^2 (geo_prepare_k)
+    double koc, koc2, akoc;
     double amp, omega;  // uniform velocity: c^2 - |v|^2 and its reciprocal (rcp_steer)
     double cT, sT;    // cos, sin of Theta = omega t + phase
-    double accel;
-    double Lmax;      // accel: distance travelled along e1 by time t
-    double v[3];
-    double rt[3];     // uniform velocity: position at time t
+    double accel;     // circular, linear: ORBIT_TAB / (2 pi) omega / c
+    double Lmax;      // accel: distance travelled along e1 by time t; circular, linear: 1 / omega
+    double v[3];      // circular, linear: amp e1
+    double rt[3];     // uniform velocity: position at time t; circular: amp e2; linear: rt[0] = (amp omega / c)^2
     // FP32 coefficients of beta and beta_dot (mixed path) in the orbit frame:
     // circular  beta = -s bw1 + c bw2,  beta_dot = -(c aw1 + s aw2);
     // linear    beta = -s bw1,          beta_dot = -c aw1;
-    // bw = amp omega / c * e, aw = amp omega^2 / c * e; uniform velocity: bw1 = beta
+    // bw = amp omega / c * e, aw = amp omega^2 / c * e; uniform velocity: bw1 = beta;
+    // accel: bw1 = e1, aw1 = accel / c * e1
     float bw1[3], bw2[3], aw1[3], aw2[3];
+    float omb;        // circular, uniform velocity: 1 - |beta|^2
 };
 
 // Retarded kinematics seen from the observation point: R = x - r(t'),
@@ -54,6 +57,7 @@ struct Kin {
     double v[3];        // FP64 path
     double a[3];
     float bf[3], df[3]; // mixed path: beta = v / c and beta_dot = a / c in FP32
+    float omb;          // mixed path: 1 - |beta|^2
     double tp;          // retarded time t'
     double cph, sph;    // cos, sin of the phase at t' (oscillating families)
     uint32_t flags;
@@ -63,15 +67,6 @@ struct Kin {
 };
 
 constexpr int ITER_FALLBACK = 1 << 16;
-
-// The mixed path's beta and beta_dot from FP64 velocity and acceleration.
-__device__ __forceinline__ void kin_beta_from_va(Kin &k)
-{
-    for (int i = 0; i < 3; ++i) {
-        k.bf[i] = (float)(k.v[i] * INV_C);
-        k.df[i] = (float)(k.a[i] * INV_C);
-    }
-}
 
 // a * b + k with the constant k read from a scalar register pair.  Polynomial
 // coefficients used this way stay out of vector registers: held there, every
@@ -124,37 +119,6 @@ __device__ __forceinline__ void sincos_reduced(double x, double &s, double &c)
     sincos_small(r, sr, cr);
     const int q = (int)k & 3;
     const double a = (q & 1) ? cr : sr;          // |sin x|, |cos x| up to sign
-    const double b = (q & 1) ? sr : cr;
-    s = (q & 2) ? -a : a;
-    c = ((q + 1) & 2) ? -b : b;
-}
-
-// sin and cos to about 1e-11 absolute (mixed path only, whose outputs are FP32):
-// the same reduction, then Taylor terms through x^11 and x^12 for |r| <= pi/4
-// (truncation below 7e-12 and 4e-13).
-__device__ __forceinline__ void sincos_reduced_short(double x, double &s, double &c)
-{
-    const double P1 = 0x1.921fb54442d18p+0;     // pi/2 = P1 + P2 + P3
-    const double P2 = 0x1.1a62633145c07p-54;
-    const double P3 = -0x1.f1976b7ed8fbcp-110;
-    const double k = rint(x * 0x1.45f306dc9c883p-1);   // x * 2/pi
-    double r = fma(-k, P1, x);
-    r = fma(-k, P2, r);
-    r = fma(-k, P3, r);
-    const double r2 = r * r;
-    double ps = fma_k(r2, -1.0 / 39916800.0, 1.0 / 362880.0);   // -1/11!, 1/9!
-    ps = fma_k(ps, r2, -1.0 / 5040.0);
-    ps = fma_k(ps, r2, 1.0 / 120.0);
-    ps = fma_k(ps, r2, -1.0 / 6.0);
-    const double sr = fma(r * r2, ps, r);
-    double pc = fma_k(r2, 1.0 / 479001600.0, -1.0 / 3628800.0);  // 1/12!, -1/10!
-    pc = fma_k(pc, r2, 1.0 / 40320.0);
-    pc = fma_k(pc, r2, -1.0 / 720.0);
-    pc = fma_k(pc, r2, 1.0 / 24.0);
-    pc = fma(pc, r2, -0.5);
-    const double cr = fma(pc, r2, 1.0);
-    const int q = (int)k & 3;
-    const double a = (q & 1) ? cr : sr;
     const double b = (q & 1) ? sr : cr;
     s = (q & 2) ? -a : a;
     c = ((q + 1) & 2) ? -b : b;
@@ -317,93 +281,154 @@ __device__ __forceinline__ bool converged_smooth(double tn, double tau, double t
     return fabs(st) <= tol_rel * tn || (free_step && fabs(ddD) * (st * st) <= 0.5 * tol_rel * tn * (C_LIGHT - dD));
 }
 
+// cos and sin of 2 pi k / ORBIT_TAB, the phases that starting values lie on.
+constexpr int ORBIT_TAB = 128;
+constexpr double TWO_PI = 6.28318530717958647692;
+
+constexpr double series_sin(double x)       // |x| <= pi / 4, to rounding
+{
+    double term = x, sum = x;
+    for (int n = 1; n < 12; ++n) {
+        term *= -x * x / (2.0 * n * (2.0 * n + 1.0));
+        sum += term;
+    }
+    return sum;
+}
+constexpr double series_cos(double x)
+{
+    double term = 1.0, sum = 1.0;
+    for (int n = 1; n < 12; ++n) {
+        term *= -x * x / (2.0 * n * (2.0 * n - 1.0));
+        sum += term;
+    }
+    return sum;
+}
+struct OrbitTable {
+    double cs[ORBIT_TAB][2];
+    constexpr OrbitTable() : cs{}
+    {
+        for (int k = 0; k < ORBIT_TAB; ++k) {
+            // nearest quadrant's axis plus a remainder of at most pi / 4
+            const int q = (k + ORBIT_TAB / 8) / (ORBIT_TAB / 4);
+            const double r = TWO_PI / ORBIT_TAB * (k - q * (ORBIT_TAB / 4));
+            const double c = series_cos(r), s = series_sin(r);
+            cs[k][0] = (q & 1) ? ((q & 2) ? s : -s) : ((q & 2) ? -c : c);
+            cs[k][1] = (q & 1) ? ((q & 2) ? -c : c) : ((q & 2) ? -s : s);
+        }
+    }
+};
+__device__ const OrbitTable orbit_table{};
+
 // Part of a source's retarded-time problem that does not depend on the
-// observation time, for one observation point: the point in the source's frame,
-// the geometric bracket on tau and the starting value with cos/sin(omega tau0).
-// Field kernels build it once per (point, charge) and reuse it for every time.
+// observation time, for one observation point.  Field kernels build it once per
+// (point, charge) and reuse it for every time.
+//
+// Circular and linear orbits: the retarded time is sought as a phase, T = omega
+// tau = T0 + a, about a start T0: the light time from the orbit's RMS distance,
+// beyond the near field moved to the grid of 2 pi / ORBIT_TAB.  With theta = Theta -
+// T the condition (c tau)^2 = D^2, in units of c / omega, reads
+//   g(a) = a (2 T0 + a) + G(theta) - K = 0,
+// circular:  G = w1b cos theta + w2b sin theta,  K = (|w|^2 + A^2) (omega / c)^2 - T0^2,
+// linear:    G = w1b cos theta - beta^2 cos^2 theta,  K = |w|^2 (omega / c)^2 - T0^2,
+// with w1b = 2 beta (omega / c) w.e1, w2b likewise, beta = A omega / c.  g needs no
+// square root, has the root of Eq. (ret_t) as its only root with tau > 0, and needs
+// no division here.  A start on the grid costs one table entry instead of a sine
+// and cosine (27 VALU instructions per (point, charge)) and moves |a| by at most
+// pi / ORBIT_TAB.
 struct Geo {
     double w[3];      // x - c0
-    double w1, w2, w3;// circular: coordinates along e1, e2, e3; linear, accel: w1 along e1, w2 = distance^2 from the axis
-    double lo, hi;    // bracket on c tau / c (circular, linear)
-    double tau0;      // starting value (circular, linear)
-    double cw, sw;    // cos, sin of omega tau0
-    // the correction form (circular, linear; see solve_u_mixed), lengths in units of
-    // D0 = c tau0: w1h = w1 / D0, w2h = w2 / D0 (circular), Ah = A / D0, kh = omega tau0,
-    // K0h = (W + A^2 - D0^2) / D0^2 (circular) or (W - D0^2) / D0^2 (linear), W = |x - c0|^2
-    double w1h, w2h, Ah, kh, K0h;
+    double w1, w2;    // accel: w along e1, distance^2 from the axis
+    double T2;        // 2 T0
+    double cw, sw;    // cos, sin of T0
+    double w1b, w2b, K;
 };
 
-// The time-independent part of the retarded-time problem for a charge of family
-// KIND (the record of any observation time), seen from x.  The stationary and
-// uniform families need only w.  BRACKET: also the bracket lo, hi, which only the
-// safeguarded solver reads (the correction solves' fallbacks build their own).
-// The start tau0 is the RMS distance to the orbit over c: the mean of the squared
-// distance lies between its least and greatest values, so the clamp to the
-// bracket never moves it.  PHASE64 = false (mixed path) takes the phase of tau0
-// to about 1e-11 instead of to FP64 rounding.
-template <int KIND, bool BRACKET = true, bool PHASE64 = true>
+template <int KIND>
 __device__ __forceinline__ void geo_prepare_k(const SrcRec &S, const double x[3], Geo &g)
 {
     for (int i = 0; i < 3; ++i) g.w[i] = x[i] - S.c0[i];
-    if constexpr (KIND != K_CIRCULAR && KIND != K_LINEAR_OSC && KIND != K_ACCEL) return;
+    const double *w = g.w;
+    if constexpr (KIND == K_CIRCULAR || KIND == K_LINEAR_OSC) {
+        const double W = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
+        const double w1 = w[0] * S.e1[0] + w[1] * S.e1[1] + w[2] * S.e1[2];
+        const double A2 = S.amp * S.amp, WA = KIND == K_CIRCULAR ? W + A2 : W;
+        // RMS distance to the orbit (omega = 0 gives T0 = 0 and a solve that is never
+        // accepted; the safeguarded solver takes it)
+        const double rms = sqrt_rough(KIND == K_CIRCULAR ? WA : fma(0.5, A2, W));
+        const double kk = rint(rms * S.accel);
+        if (fabs(kk) < 15.0) {
+            // near field (|T0| < 0.72): the grid is coarse against T0 there
+            const double T0 = rms * S.koc;
+            g.T2 = T0 + T0;
+            sincos_small(T0, g.sw, g.cw);
+        } else {
+            const uint32_t o = (uint32_t)(__builtin_amdgcn_fract(kk * (1.0 / ORBIT_TAB)) * (double)(ORBIT_TAB * 16));
+            const double *cs = (const double *)((const char *)orbit_table.cs + o);
+            g.cw = cs[0];
+            g.sw = cs[1];
+            g.T2 = kk * (2.0 * TWO_PI / ORBIT_TAB);
+        }
+        g.w1b = w1 * S.akoc;
+        if constexpr (KIND == K_CIRCULAR)
+            g.w2b = (w[0] * S.e2[0] + w[1] * S.e2[1] + w[2] * S.e2[2]) * S.akoc;
+        g.K = fma(-0.25 * g.T2, g.T2, WA * S.koc2);
+    } else if constexpr (KIND == K_ACCEL) {
+        g.w1 = w[0] * S.e1[0] + w[1] * S.e1[1] + w[2] * S.e1[2];
+        const double p0 = w[0] - g.w1 * S.e1[0], p1 = w[1] - g.w1 * S.e1[1], p2 = w[2] - g.w1 * S.e1[2];
+        g.w2 = p0 * p0 + p1 * p1 + p2 * p2;
+    }
+}
+
+// The point in the orbit's frame with the geometric bracket on tau and a start,
+// for the safeguarded solvers (circular, linear).  The start is the RMS distance
+// to the orbit over c: the mean of the squared distance lies between its least
+// and greatest values, so the clamp to the bracket never moves it.
+struct GeoSafe {
+    double w[3];      // x - c0
+    double w1, w2, w3;// circular: coordinates along e1, e2, e1 x e2; linear: w1 along e1, w2 = distance^2 from the axis
+    double lo, hi;    // bracket on tau
+    double tau0;      // starting value
+    double cw, sw;    // cos, sin of omega tau0
+};
+
+template <int KIND>
+__device__ __forceinline__ void geo_safe(const SrcRec &S, const double x[3], GeoSafe &g)
+{
+    for (int i = 0; i < 3; ++i) g.w[i] = x[i] - S.c0[i];
     const double *w = g.w;
     const double A = S.amp;
     g.w1 = w[0] * S.e1[0] + w[1] * S.e1[1] + w[2] * S.e1[2];
+    const double w1 = g.w1;
     if constexpr (KIND == K_CIRCULAR) {
-        const double w1 = g.w1;
         const double w2 = w[0] * S.e2[0] + w[1] * S.e2[1] + w[2] * S.e2[2];
-        const double w3 = w[0] * S.e3[0] + w[1] * S.e3[1] + w[2] * S.e3[2];
+        const double w3 = w[0] * (S.e1[1] * S.e2[2] - S.e1[2] * S.e2[1]) +
+                          w[1] * (S.e1[2] * S.e2[0] - S.e1[0] * S.e2[2]) +
+                          w[2] * (S.e1[0] * S.e2[1] - S.e1[1] * S.e2[0]);
         g.w2 = w2;
         g.w3 = w3;
-        const double WA = w1 * w1 + w2 * w2 + w3 * w3 + A * A;
-        if constexpr (BRACKET) {
-            const double rho = sqrt_rough(w1 * w1 + w2 * w2);
-            // the distance to the orbit lies between these, so c tau does too
-            // (widened by 1e-6 to cover the rough square roots)
-            g.lo = sqrt_rough(w3 * w3 + (rho - A) * (rho - A)) * (INV_C * (1.0 - 1e-6));
-            g.hi = sqrt_rough(w3 * w3 + (rho + A) * (rho + A)) * (INV_C * (1.0 + 1e-6));
-            g.tau0 = fmin(fmax(sqrt_rough(WA) * INV_C, g.lo), g.hi);
-        } else {
-            g.tau0 = sqrt_rough(WA) * INV_C;
-        }
-        if constexpr (PHASE64) sincos_reduced(S.omega * g.tau0, g.sw, g.cw);
-        else sincos_reduced_short(S.omega * g.tau0, g.sw, g.cw);
-        const double D0 = C_LIGHT * g.tau0, iD0 = rcp_steer(D0);
-        g.w1h = w1 * iD0;
-        g.w2h = w2 * iD0;
-        g.Ah = A * iD0;
-        g.kh = S.omega * g.tau0;
-        g.K0h = fma(-D0, D0, WA) * (iD0 * iD0);
+        const double rho = sqrt_rough(w1 * w1 + w2 * w2);
+        // the distance to the orbit lies between these, so c tau does too
+        // (widened by 1e-6 to cover the rough square roots)
+        g.lo = sqrt_rough(w3 * w3 + (rho - A) * (rho - A)) * (INV_C * (1.0 - 1e-6));
+        g.hi = sqrt_rough(w3 * w3 + (rho + A) * (rho + A)) * (INV_C * (1.0 + 1e-6));
+        g.tau0 = fmin(fmax(sqrt_rough(w1 * w1 + w2 * w2 + w3 * w3 + A * A) * INV_C, g.lo), g.hi);
     } else {
-        const double w1 = g.w1;
         const double p0 = w[0] - w1 * S.e1[0], p1 = w[1] - w1 * S.e1[1], p2 = w[2] - w1 * S.e1[2];
         const double perp2 = p0 * p0 + p1 * p1 + p2 * p2;     // distance^2 from the axis line
         g.w2 = perp2;
-        if constexpr (KIND == K_LINEAR_OSC) {
-            const double W2 = perp2 + w1 * w1;
-            if constexpr (BRACKET) {
-                const double u = fmin(fmax(w1, -A), A);
-                g.lo = sqrt_rough(perp2 + (w1 - u) * (w1 - u)) * (INV_C * (1.0 - 1e-6));
-                g.hi = sqrt_rough(W2 + A * A + 2.0 * A * fabs(w1)) * (INV_C * (1.0 + 1e-6));
-                g.tau0 = fmin(fmax(sqrt_rough(W2 + 0.5 * A * A) * INV_C, g.lo), g.hi);
-            } else {
-                g.tau0 = sqrt_rough(W2 + 0.5 * A * A) * INV_C;
-            }
-            if constexpr (PHASE64) sincos_reduced(S.omega * g.tau0, g.sw, g.cw);
-            else sincos_reduced_short(S.omega * g.tau0, g.sw, g.cw);
-            const double D0 = C_LIGHT * g.tau0, iD0 = rcp_steer(D0);
-            g.w1h = w1 * iD0;
-            g.w2h = 0.0;
-            g.Ah = A * iD0;
-            g.kh = S.omega * g.tau0;
-            g.K0h = fma(-D0, D0, W2) * (iD0 * iD0);
-        }
+        g.w3 = 0.0;
+        const double W2 = perp2 + w1 * w1;
+        const double u = fmin(fmax(w1, -A), A);
+        g.lo = sqrt_rough(perp2 + (w1 - u) * (w1 - u)) * (INV_C * (1.0 - 1e-6));
+        g.hi = sqrt_rough(W2 + A * A + 2.0 * A * fabs(w1)) * (INV_C * (1.0 + 1e-6));
+        g.tau0 = fmin(fmax(sqrt_rough(W2 + 0.5 * A * A) * INV_C, g.lo), g.hi);
     }
+    sincos_reduced(S.omega * g.tau0, g.sw, g.cw);
 }
 
 // --- circular orbit: r = c0 + amp (cos th e1 + sin th e2), th = Theta - w tau ---
 template <bool FULL>
-__device__ __forceinline__ void solve_circular(const SrcRec &S, const Geo &g, int max_iter, double tol_rel, Kin &k)
+__device__ __forceinline__ void solve_circular(const SrcRec &S, const GeoSafe &g, int max_iter, double tol_rel, Kin &k)
 {
     const double A = S.amp, om = S.omega;
     const double w1 = g.w1, w2 = g.w2, w3 = g.w3;
@@ -450,12 +475,13 @@ __device__ __forceinline__ void solve_circular(const SrcRec &S, const Geo &g, in
             k.bf[i] = cf * S.bw2[i] - sf * S.bw1[i];
             k.df[i] = -(cf * S.aw1[i] + sf * S.aw2[i]);
         }
+        k.omb = S.omb;
     }
 }
 
 // --- linear oscillation: r = c0 + amp cos th e1 ---
 template <bool FULL>
-__device__ __forceinline__ void solve_linear(const SrcRec &S, const Geo &g, int max_iter, double tol_rel, Kin &k)
+__device__ __forceinline__ void solve_linear(const SrcRec &S, const GeoSafe &g, int max_iter, double tol_rel, Kin &k)
 {
     const double A = S.amp, om = S.omega;
     const double w1 = g.w1, perp2 = g.w2;
@@ -497,6 +523,7 @@ __device__ __forceinline__ void solve_linear(const SrcRec &S, const Geo &g, int 
             k.bf[i] = -sf * S.bw1[i];
             k.df[i] = -cf * S.aw1[i];
         }
+        k.omb = fmaf(-(float)S.rt[0] * sf, sf, 1.f);
     }
 }
 
@@ -563,12 +590,18 @@ __device__ __forceinline__ void solve_uniform(const SrcRec &S, const double x[3]
     const double ww = wt[0] * wt[0] + wt[1] * wt[1] + wt[2] * wt[2];
     const double den = S.amp;
     const double disc = wv * wv + den * ww;
-    double sq, isq;
-    if (FULL) sq = sqrt(disc);
-    else root_rsqrt<false>(fmax(disc, 1e-300), sq, isq);
-    // the two algebraically equal forms, chosen to avoid cancellation
-    const double tau = FULL ? ((wv >= 0.0) ? (wv + sq) / den : ww / (sq - wv))
-                            : ((wv >= 0.0) ? (wv + sq) * S.omega : ww * rcp_steer(sq - wv));
+    double sq, isq, tau;
+    if (FULL) {
+        sq = sqrt(disc);
+        // the two algebraically equal forms, chosen to avoid cancellation
+        tau = (wv >= 0.0) ? (wv + sq) / den : ww / (sq - wv);
+    } else {
+        root_rsqrt<false>(fmax(disc, 1e-300), sq, isq);
+        // at |v| <= 0.999 c (the same for every lane) the first form alone loses at most
+        // a factor 2 / (1 - |beta|) < 2000 of the root's 2^-40, far below FP32
+        if (den >= 2e-3 * C_LIGHT * C_LIGHT) tau = (wv + sq) * S.omega;
+        else tau = (wv >= 0.0) ? (wv + sq) * S.omega : ww * rcp_steer(sq - wv);
+    }
     k.tp = S.t - tau;
     k.cph = 1.0;
     k.sph = 0.0;
@@ -581,393 +614,313 @@ __device__ __forceinline__ void solve_uniform(const SrcRec &S, const double x[3]
     k.iters = 0;
 }
 
-// Mixed path, circular and linear orbits: the retarded time as a correction to
-// the start, tau = tau0 (1 + u), in units of D0 = c tau0.  With the phase
-// theta = theta0 - kh u (theta0 = Theta - omega tau0, kh = omega tau0), the
-// condition (c tau)^2 = D^2 reads, for the circular orbit,
-//   f(u) = u (2 + u) + 2 Ah P(theta) - K0h = 0,  P = w1h cos theta + w2h sin theta,
-// and for the linear oscillation
-//   f(u) = u (2 + u) - K0h + 2 Ah w1h cos theta - Ah^2 cos^2 theta = 0.
-// f = (c tau - D)(c tau + D) / D0^2 has the root of Eq. (ret_t) as its only root
-// with u > -1, needs no square root, and its terms are all of the size of
-// Ah, so it is solved in FP32: Halley steps until a step is below 2^-7, the
-// phase rotated from theta0 by -kh u with short Taylor polynomials (|kh u| is at
-// most the charge's speed over c).  Halley's error after such a step is of the
-// order of its cube, 5e-7, and FP32 rounding of f, amplified by kh, leaves the
-// root's phase good to about 1e-7 rad; one Newton step in FP64 from the FP64
-// phase theta0 then squares the remaining error (phase error below 1e-9 rad).
-// (A stop at 2^-10 took a second FP32 step on 81 % of the benchmark's pairs for
-// no change in the outputs' error; at 2^-5 the vector potential's error grew.)
-// Returns false (the caller takes the safeguarded solver instead) when the FP32
-// steps do not settle or leave the physical range.
-__device__ __forceinline__ void rot_small_f32(float c0, float s0, float a, float &c, float &s)
+// The next iterate's distance from a root of a function with Taylor coefficients
+// F[0..N-1] (F[k] = f^(k) / k!): the root of the Pade approximant of 1 / f's
+// series (Householder's method of order N), -F0 D_{N-2} / D_{N-1} with D_0 = 1,
+// D_k = sum_i (-1)^(i-1) F0^(i-1) F_i D_{k-i}.  The error left is of the order of
+// the N-th power of the error before.  Returns numerator and denominator.
+template <int N, typename F>
+__device__ __forceinline__ void pade_step(const F c[5], F &num, F &den)
 {
-    // sin a and cos a through a^7 and a^8: the truncation, below 2.1e-7 for
-    // |a| <= 0.75 and 5.4e-9 for |a| <= 0.5, moves the FP32 root by at most
-    // about Ah times that, which the FP64 Newton step that follows squares away
-    const float a2 = a * a;
-    const float sa = a * fmaf(a2, fmaf(a2, fmaf(a2, -1.f / 5040.f, 1.f / 120.f), -1.f / 6.f), 1.f);
-    const float ca = fmaf(a2, fmaf(a2, fmaf(a2, fmaf(a2, 1.f / 40320.f, -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
-    c = c0 * ca - s0 * sa;
-    s = s0 * ca + c0 * sa;
+    static_assert(N >= 3 && N <= 5, "");
+    const F x2 = c[0] * c[2];
+    const F d2 = c[1] * c[1] - x2;
+    if constexpr (N == 3) {
+        num = -c[0] * c[1];
+        den = d2;
+    } else {
+        const F f2 = c[0] * c[0];
+        const F x3 = f2 * c[3];
+        const F d3 = c[1] * (d2 - x2) + x3;
+        if constexpr (N == 4) {
+            num = -c[0] * d2;
+            den = d3;
+        } else {
+            const F x4 = f2 * c[0] * c[4];
+            num = -c[0] * d3;
+            den = c[1] * (d3 + x3) - x2 * d2 - x4;
+        }
+    }
 }
 
-// The FP32 Halley steps of the correction form from u = 0, phase (c0, s0) at
-// tau0: returns whether a step fell below `stop`; u and the step count n32.
-template <int KIND>
-__device__ __forceinline__ bool u_stage_f32(const Geo &g, double c0, double s0, float stop, float &u, int &n32)
+// Taylor coefficients of g (Geo) at a, phase (c, s) = (cos, sin) theta, in precision
+// F.  b2 = beta^2 (linear).
+template <int KIND, int N, typename F>
+__device__ __forceinline__ void orbit_taylor(F w1b, F w2b, F b2, F T2, F K, F a, F c, F s, F g[5])
 {
-    const float c0f = (float)c0, s0f = (float)s0;
-    const float w1f = (float)g.w1h, w2f = (float)g.w2h, Af = (float)g.Ah, kf = (float)g.kh, K0f = (float)g.K0h;
-    float c = c0f, s = s0f;
-    bool ok = false;
-    u = 0.f;
-    n32 = 0;
-    for (int it = 0; it < 4; ++it) {
-        ++n32;
-        float fv, fp, fpp;
-        if (KIND == K_CIRCULAR) {
-            const float P = fmaf(w1f, c, w2f * s), Q = fmaf(w2f, c, -w1f * s);
-            fv = fmaf(u, 2.f + u, fmaf(2.f * Af, P, -K0f));
-            fp = fmaf(-2.f * Af * kf, Q, 2.f + 2.f * u);
-            fpp = fmaf(-2.f * Af * kf * kf, P, 2.f);
+    if constexpr (KIND == K_CIRCULAR) {
+        const F P = w1b * c + w2b * s, Q = w2b * c - w1b * s;      // dP/da = -Q, dQ/da = P
+        g[0] = a * (T2 + a) + (P - K);
+        g[1] = (F)2 * a + (T2 - Q);
+        g[2] = (F)-0.5 * P + (F)1;
+        if constexpr (N >= 4) g[3] = Q * (F)(1.0 / 6.0);
+        if constexpr (N >= 5) g[4] = P * (F)(1.0 / 24.0);
+    } else {
+        const F bc = b2 * c, bs = b2 * s, y = w1b - bc;            // y - bc = -dG / d cos theta
+        const F cy = c * (y - bc) + (F)2 * bs * s;                 // -G''
+        g[0] = a * (T2 + a) + (c * y - K);
+        g[1] = (F)2 * a + (s * (y - bc) + T2);
+        g[2] = (F)-0.5 * cy + (F)1;
+        if constexpr (N >= 4) g[3] = s * ((F)7 * bc - y) * (F)(1.0 / 6.0);
+        if constexpr (N >= 5) g[4] = (cy - (F)6 * (bc * c - bs * s)) * (F)(1.0 / 24.0);
+    }
+}
+
+// (cos, sin) of theta0 - a from (c0, s0) = (cos, sin) theta0, |a| <= 0.75: Taylor
+// terms through a^11 and a^12 (truncation below 2e-17), or for the mixed path
+// (SHORT) through a^9 and a^10 (below 1.1e-9, and 1.3e-11 for |a| <= 0.5, against
+// FP32 outputs).
+template <bool SHORT>
+__device__ __forceinline__ void rot_phase(double c0, double s0, double a, double &c, double &s)
+{
+    const double a2 = a * a;
+    double sa, ca;
+    if constexpr (SHORT) {
+        sa = fma_k(a2, 1.0 / 362880.0, -1.0 / 5040.0);
+        ca = fma_k(a2, -1.0 / 3628800.0, 1.0 / 40320.0);
+    } else {
+        sa = fma_k(a2, fma_k(a2, -1.0 / 39916800.0, 1.0 / 362880.0), -1.0 / 5040.0);
+        ca = fma_k(a2, fma_k(a2, 1.0 / 479001600.0, -1.0 / 3628800.0), 1.0 / 40320.0);
+    }
+    sa = a * fma_k(a2, fma_k(a2, fma_k(a2, sa, 1.0 / 120.0), -1.0 / 6.0), 1.0);
+    ca = fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, ca, -1.0 / 720.0), 1.0 / 24.0), -0.5), 1.0);
+    c = c0 * ca + s0 * sa;
+    s = s0 * ca - c0 * sa;
+}
+
+// Circular and linear orbits: the root of g (Geo).  One step of order 4 (mixed
+// path) or 5 (FULL, the FP64 path) in FP32 from a = 0, whose phase is known in
+// FP64; then one step of order 3 or 4 in FP64 from the FP64 phase there, and the
+// phase follows by a short rotation.  What remains after an FP64 step e is about
+// 0.04 |e|^3 rad (mixed) and 0.02 |e|^4 rad (FULL), measured over the families and
+// geometries of the grid workloads: accepted at |e| <= 2^-9 it is below 3e-10 rad
+// (mixed, FP32 outputs), at |e| <= 2^-12 below 7e-17 rad (FULL).  About 1 % of the
+// waves hold a lane that is not accepted or whose |a| leaves the range of the
+// phase rotation: false is returned (the caller takes the safeguarded solver).
+//
+// VALU issue bounds the grid kernels, where an FP64 instruction costs as much as an
+// FP32 one (v_rcp_f64 four, v_rcp_f32 two).  So steps of high order, whose extra
+// terms cost two or three instructions each, replace further low-order steps,
+// each of which evaluates the phase anew (about 36): against FP32 Halley steps
+// until one was below 2^-7 and one FP64 Newton step, the 512^2 x 64 x 16 mixed grid
+// went from 1.47 to 1.22 ms per call and
+// the FP64 75^3 x 5 x 16 volume from 0.292 to 0.227 ms.
+template <int KIND, bool FULL>
+__device__ __forceinline__ bool solve_orbit(const SrcRec &S, const Geo &g, Kin &k)
+{
+    // phase at T0 for this observation time (FP64)
+    const double c0 = S.cT * g.cw + S.sT * g.sw;
+    const double s0 = S.sT * g.cw - S.cT * g.sw;
+    const double b2 = KIND == K_LINEAR_OSC ? S.rt[0] : 0.0;
+    constexpr int N32 = FULL ? 5 : 4, N64 = FULL ? 4 : 3;
+    float t32[5], n32, d32;
+    orbit_taylor<KIND, N32, float>((float)g.w1b, (float)g.w2b, (float)b2, (float)g.T2, (float)g.K, 0.f, (float)c0,
+                                   (float)s0, t32);
+    pade_step<N32, float>(t32, n32, d32);
+    double a = (double)(n32 * __builtin_amdgcn_rcpf(d32));
+    double c, s, t[5], num, den;
+    rot_phase<!FULL>(c0, s0, a, c, s);
+    orbit_taylor<KIND, N64, double>(g.w1b, g.w2b, b2, g.T2, g.K, a, c, s, t);
+    pade_step<N64, double>(t, num, den);
+    // v_rcp_f64 unrefined (relative error below 2^-26) for the mixed path
+    const double e = num * (FULL ? rcp_steer(den) : __builtin_amdgcn_rcp(den));
+    if (!(fabs(a) <= 0.75) || !(fabs(e) <= (FULL ? 0x1p-12 : 0x1p-9))) return false;
+    a += e;
+    {
+        // to fourth order (truncation e^5 / 120 below 1e-19), mixed to second (e^3 / 6
+        // below 1.3e-9)
+        const double e2 = e * e;
+        double ce, se;
+        if constexpr (FULL) {
+            ce = fma(e2, fma(e2, 1.0 / 24.0, -0.5), 1.0);
+            se = e * fma(e2, -1.0 / 6.0, 1.0);
         } else {
-            const float gx = fmaf(-Af, c, w1f);                  // w1h - Ah cos theta
-            fv = fmaf(u, 2.f + u, fmaf(2.f * Af * w1f, c, fmaf(-Af * Af * c, c, -K0f)));
-            fp = fmaf(2.f * Af * kf * s, gx, 2.f + 2.f * u);
-            fpp = fmaf(-2.f * Af * kf * kf, fmaf(c, gx, -Af * s * s), 2.f);
+            ce = fma(-0.5, e2, 1.0);
+            se = e;
         }
-        const float fp2 = fp * fp;
-        float den = fmaf(2.f, fp2, -fv * fpp);
-        den = den > fp2 ? den : 2.f * fp2;
-        const float d = -2.f * fv * fp * __builtin_amdgcn_rcpf(den);
-        u += d;
-        if (fabsf(d) <= stop) {
-            ok = true;
-            break;
+        const double cn = c * ce + s * se, sn = s * ce - c * se;
+        c = cn;
+        s = sn;
+    }
+    k.flags = 0u;
+    k.iters = 2;
+    k.tp = S.t - fma(0.5, g.T2, a) * S.Lmax;
+    k.cph = c;
+    k.sph = s;
+    if constexpr (FULL) {
+        const double A = S.amp, om = S.omega;
+        const double vw = om * A, aw = -om * om;
+        for (int i = 0; i < 3; ++i) {
+            const double ro = KIND == K_CIRCULAR ? c * S.v[i] + s * S.rt[i] : c * S.v[i];
+            k.R[i] = g.w[i] - ro;
+            k.v[i] = KIND == K_CIRCULAR ? vw * (c * S.e2[i] - s * S.e1[i]) : -vw * s * S.e1[i];
+            k.a[i] = aw * ro;
         }
-        rot_small_f32(c0f, s0f, -kf * u, c, s);
+    } else {
+        const float cf = (float)c, sf = (float)s;
+        for (int i = 0; i < 3; ++i) {
+            if (KIND == K_CIRCULAR) {
+                k.R[i] = fma(-s, S.rt[i], fma(-c, S.v[i], g.w[i]));
+                k.bf[i] = cf * S.bw2[i] - sf * S.bw1[i];
+                k.df[i] = -(cf * S.aw1[i] + sf * S.aw2[i]);
+            } else {
+                k.R[i] = fma(-c, S.v[i], g.w[i]);
+                k.bf[i] = -sf * S.bw1[i];
+                k.df[i] = -cf * S.aw1[i];
+            }
+        }
+        k.omb = KIND == K_CIRCULAR ? S.omb : fmaf(-(float)S.rt[0] * sf, sf, 1.f);
+    }
+    return true;
+}
+
+// Uniform acceleration from rest at t = 0: where the point is at least c t away
+// from the rest position, the retarded time lies before the start and tau = |w| / c.
+// Elsewhere the charge sits at L - m along e1 at t - tau, with L = a t^2 / 2 and
+// m = a tau (2t - tau) / 2, and with tau = tau0 (1 + u), tau0 = D0 / c the light time
+// from its position at t, X = w1 - L, in units of D0:
+//   f(u) = u (2 + u) - m (2 X + m) - K0h,  m = (a / 2c)(1 + u)(2t - tau),
+// K0h = (perp^2 + X^2 - D0^2) / D0^2: a polynomial in u whose root is the retarded
+// time's.  One step of order 5 in FP32 from u = 0, then in FP64 steps of order 3
+// (mixed) or 5 (FULL) until one is below 2^-9 or 2^-11, after which about |d|^3 and
+// |d|^5 remain: one such step on 99 % of the pairs of the grid workloads.  Returns
+// false (the caller takes the safeguarded solver) when they do not settle.
+template <int N, typename F>
+__device__ __forceinline__ void accel_taylor(F Xh, F K0h, F gh, F t, F tau0, F u, F f[5])
+{
+    const F tau = tau0 * u + tau0;
+    const F gd = gh * (t - tau);
+    // m and its derivatives in u
+    const F m = (gh * ((F)1 + u)) * (t + (t - tau)), mp = gd + gd, mpp = (F)-2 * gh * tau0, xm = Xh + m;
+    f[0] = u * ((F)2 + u) - (m * (Xh + xm) + K0h);
+    f[1] = (F)-2 * mp * xm + ((F)2 + (F)2 * u);
+    f[2] = (F)1 - (mpp * xm + mp * mp);
+    if constexpr (N >= 4) f[3] = -mp * mpp;
+    if constexpr (N >= 5) f[4] = (F)-0.25 * mpp * mpp;
+}
+
+template <bool FULL>
+__device__ __forceinline__ bool solve_accel_poly(const SrcRec &S, const Geo &g, Kin &k)
+{
+    const double t = S.t, acc = S.accel, L = S.Lmax;
+    const double W2 = fma(g.w1, g.w1, g.w2);
+    const double ct = C_LIGHT * t;
+    constexpr int N64 = FULL ? 5 : 3;
+    k.flags = 0u;
+    k.cph = 1.0;
+    k.sph = 0.0;
+    double tp = 0.0;
+    bool ok = true;
+    int it = 0;
+    if (t > 0.0 && W2 < ct * ct) {
+        const double X = g.w1 - L;
+        const double Dn2 = fma(X, X, g.w2);
+        const double D0 = sqrt_rough(Dn2);
+        const double iD0 = rcp_steer(D0), tau0 = D0 * INV_C;
+        const double Xh = X * iD0, K0h = fma(-D0, D0, Dn2) * (iD0 * iD0), gh = acc * (0.5 * INV_C);
+        float f32[5], n32, d32;
+        accel_taylor<5, float>((float)Xh, (float)K0h, (float)gh, (float)t, (float)tau0, 0.f, f32);
+        pade_step<5, float>(f32, n32, d32);
+        double u = (double)(n32 * __builtin_amdgcn_rcpf(d32));
+        ok = false;
+        if (!(u > -0.999 && u < 100.0)) u = 0.0;
+        do {
+            ++it;
+            double f[5], num, den;
+            accel_taylor<N64, double>(Xh, K0h, gh, t, tau0, u, f);
+            pade_step<N64, double>(f, num, den);
+            const double d = num * (FULL ? rcp_steer(den) : __builtin_amdgcn_rcp(den));
+            u += d;
+            ok = fabs(d) <= (FULL ? 0x1p-11 : 0x1p-9);
+        } while (!ok && it < 8);
+        const double tau = fma(tau0, u, tau0);
+        tp = t - tau;
+        // the polynomial's other roots are not retarded times
+        ok = ok && u > -1.0 && tp >= -0x1p-40 * t;
+        if (FULL) k.tp = tp;
+        tp = fmax(tp, 0.0);
+    } else {
+        k.tp = FULL ? t - sqrt(W2) * INV_C : 0.0;
+    }
+    k.iters = 1 + max(it, 1);
+    const double sd = 0.5 * acc * tp * tp;
+    for (int i = 0; i < 3; ++i) k.R[i] = g.w[i] - sd * S.e1[i];
+    if constexpr (FULL) {
+        const double vel = acc * tp, ac = (tp > 0.0) ? acc : 0.0;
+        for (int i = 0; i < 3; ++i) {
+            k.v[i] = vel * S.e1[i];
+            k.a[i] = ac * S.e1[i];
+        }
+    } else {
+        const float bf = (float)(acc * tp * INV_C);
+        for (int i = 0; i < 3; ++i) {
+            k.bf[i] = bf * S.bw1[i];
+            k.df[i] = (tp > 0.0) ? S.aw1[i] : 0.f;
+        }
+        k.omb = fmaf(-bf, bf, 1.f);
     }
     return ok;
 }
 
-// (cos, sin) of the phase theta0 - kh u: (c0, s0) rotated by a = -kh u, |a| <= 0.75,
-// through a^11 and a^12 (truncation below 2e-17).
-__device__ __forceinline__ void rot_phase(double c0, double s0, double a, double &c, double &s)
-{
-    const double a2 = a * a;
-    const double sa = a * fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, -1.0 / 39916800.0, 1.0 / 362880.0),
-                                                          -1.0 / 5040.0), 1.0 / 120.0), -1.0 / 6.0), 1.0);
-    const double ca = fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, 1.0 / 479001600.0, -1.0 / 3628800.0),
-                                                                   1.0 / 40320.0), -1.0 / 720.0), 1.0 / 24.0), -0.5), 1.0);
-    c = c0 * ca - s0 * sa;
-    s = s0 * ca + c0 * sa;
-}
-
-// The same rotation for the mixed path, through a^9 and a^10 (truncation below
-// 1.1e-9 for |a| <= 0.75 and 1.3e-11 for |a| <= 0.5, against FP32 outputs).
-__device__ __forceinline__ void rot_phase_short(double c0, double s0, double a, double &c, double &s)
-{
-    const double a2 = a * a;
-    const double sa = a * fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, 1.0 / 362880.0, -1.0 / 5040.0), 1.0 / 120.0),
-                                          -1.0 / 6.0), 1.0);
-    const double ca = fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, -1.0 / 3628800.0, 1.0 / 40320.0),
-                                                          -1.0 / 720.0), 1.0 / 24.0), -0.5), 1.0);
-    c = c0 * ca - s0 * sa;
-    s = s0 * ca + c0 * sa;
-}
-
-// f(u) and f'(u) of the correction form in FP64 at phase (cd, sd).
-template <int KIND>
-__device__ __forceinline__ void u_f64(const Geo &g, double ud, double cd, double sd, double &fv, double &fp)
-{
-    if (KIND == K_CIRCULAR) {
-        const double P = fma(g.w1h, cd, g.w2h * sd), Q = fma(g.w2h, cd, -g.w1h * sd);
-        fv = fma(ud, 2.0 + ud, fma(2.0 * g.Ah, P, -g.K0h));
-        fp = fma(-2.0 * g.Ah * g.kh, Q, 2.0 + 2.0 * ud);
-    } else {
-        const double gx = fma(-g.Ah, cd, g.w1h);
-        fv = fma(ud, 2.0 + ud, fma(2.0 * g.Ah * g.w1h, cd, fma(-g.Ah * g.Ah * cd, cd, -g.K0h)));
-        fp = fma(2.0 * g.Ah * g.kh * sd, gx, 2.0 + 2.0 * ud);
-    }
-}
-
-template <int KIND>
-__device__ __forceinline__ bool solve_u_mixed(const SrcRec &S, const Geo &g, Kin &k)
-{
-    // phase at tau0 for this observation time (FP64)
-    const double c0 = S.cT * g.cw + S.sT * g.sw;
-    const double s0 = S.sT * g.cw - S.cT * g.sw;
-    float u;
-    int n32;
-    const bool ok = u_stage_f32<KIND>(g, c0, s0, 0x1p-7f, u, n32);
-    const double a = -g.kh * (double)u;
-    if (!ok || !(fabs(a) <= 0.75) || !(u > -0.5f)) return false;
-    // one Newton step in FP64 from the exact phase (f' in FP64 too: an FP32 f' + f'' d
-    // from the last Halley step was tried, and where the terms of f' cancel its
-    // rounding left the vector potential's pointwise error 30 times larger)
-    double cd, sd;
-    rot_phase_short(c0, s0, a, cd, sd);
-    double ud = (double)u, fv, fp;
-    u_f64<KIND>(g, ud, cd, sd, fv, fp);
-    // v_rcp_f64 unrefined (relative error below 2^-26): the step is of the size
-    // of the FP32 stage's remaining error, so this moves u by far less than 1e-13
-    const double du = -fv * __builtin_amdgcn_rcp(fp);
-    ud += du;
-    // rotate the phase by the correction's angle e (second order: |e| is of the
-    // order of kh times the FP32 steps' error, so e^3 / 6 stays far below FP32
-    // resolution)
-    const double e = -g.kh * du, ce = fma(-0.5 * e, e, 1.0);
-    const double cn = cd * ce - sd * e, sn = sd * ce + cd * e;
-    const double tau = fma(g.tau0, ud, g.tau0);
-    k.flags = 0u;
-    k.iters = n32 + 1;
-    k.tp = S.t - tau;
-    k.cph = cn;
-    k.sph = sn;
-    const double A = S.amp;
-    const float cf = (float)cn, sf = (float)sn;
-    if (KIND == K_CIRCULAR) {
-        for (int i = 0; i < 3; ++i) {
-            k.R[i] = g.w[i] - A * (cn * S.e1[i] + sn * S.e2[i]);
-            k.bf[i] = cf * S.bw2[i] - sf * S.bw1[i];
-            k.df[i] = -(cf * S.aw1[i] + sf * S.aw2[i]);
-        }
-    } else {
-        for (int i = 0; i < 3; ++i) {
-            k.R[i] = g.w[i] - A * cn * S.e1[i];
-            k.bf[i] = -sf * S.bw1[i];
-            k.df[i] = -cf * S.aw1[i];
-        }
-    }
-    return true;
-}
-
-// FP64 path, circular and linear orbits: the correction form with the FP32
-// steps above, then two Newton steps in FP64 (the first from the exact phase
-// rotated by the polynomial, the second from a fourth-order rotation by the
-// first step's angle e: the truncation e^5 / 120 is below 1e-17 for |e| <= 1e-3,
-// and a larger angle sends the point to the safeguarded solver).  Newton squares
-// the error, so the FP32 steps' remaining error (about their last step cubed,
-// and a phase error of about 1e-7 rad from FP32 rounding) is at rounding level
-// after the second step.  The root is accepted when Newton's bound on the remaining error,
-// |f''| du^2 / (2 |f'|) with |f''| <= 2 + 2 Ah kh^2 M (M = |(w1h, w2h)| for the
-// circular orbit, |w1h| + Ah for the linear one), is below 2^-54, about half an
-// ulp of u near 1, and the second step's angle is below 2^-27 (its phase follows
-// by a first-order rotation); otherwise (and when the FP32 steps do not settle)
-// the caller takes the safeguarded Halley solver.  R, v and a come out in FP64.
-template <int KIND>
-__device__ __forceinline__ bool solve_u_full(const SrcRec &S, const Geo &g, Kin &k)
-{
-    const double c0 = S.cT * g.cw + S.sT * g.sw;
-    const double s0 = S.sT * g.cw - S.cT * g.sw;
-    float u;
-    int n32;
-    // the FP32 steps run to 2^-10 here (two FP64 Newton steps then meet the 2^-54
-    // bound below; from 2^-7 more points missed it and took the safeguarded solver)
-    const bool ok = u_stage_f32<KIND>(g, c0, s0, 0x1p-10f, u, n32);
-    const double a = -g.kh * (double)u;
-    if (!ok || !(fabs(a) <= 0.75) || !(u > -0.5f)) return false;
-    double cd, sd;
-    rot_phase(c0, s0, a, cd, sd);
-    double ud = (double)u, fv, fp;
-    // first step: the phase follows by a fourth-order rotation (its angle is below
-    // 1e-3 on acceptance, so the truncation e^5 / 120 is below 1e-17)
-    u_f64<KIND>(g, ud, cd, sd, fv, fp);
-    double du = -fv * rcp_steer(fp);
-    ud += du;
-    double e = -g.kh * du;
-    bool small = fabs(e) <= 1e-3;
-    {
-        const double e2 = e * e;
-        const double ce = fma(e2, fma(e2, 1.0 / 24.0, -0.5), 1.0), se = e * fma(e2, -1.0 / 6.0, 1.0);
-        const double cn = cd * ce - sd * se, sn = sd * ce + cd * se;
-        cd = cn;
-        sd = sn;
-    }
-    // second step: its angle is below 2^-27 on acceptance, so a first-order
-    // rotation is exact to e^2 / 2 < 3e-17
-    u_f64<KIND>(g, ud, cd, sd, fv, fp);
-    du = -fv * rcp_steer(fp);
-    ud += du;
-    e = -g.kh * du;
-    small = small && fabs(e) <= 0x1p-27;
-    {
-        const double cn = fma(-sd, e, cd), sn = fma(cd, e, sd);
-        cd = cn;
-        sd = sn;
-    }
-    const double M = KIND == K_CIRCULAR ? sqrt_rough(fma(g.w1h, g.w1h, g.w2h * g.w2h)) * (1.0 + 1e-6)
-                                        : fabs(g.w1h) + g.Ah;
-    const double f2 = fma(2.0 * g.Ah * g.kh * g.kh, M, 2.0);
-    if (!small || !(ud > -0.5) || !(f2 * du * du <= 0x1p-53 * fabs(fp))) return false;
-    const double tau = fma(g.tau0, ud, g.tau0);
-    k.flags = 0u;
-    k.iters = n32 + 2;
-    k.tp = S.t - tau;
-    k.cph = cd;
-    k.sph = sd;
-    const double A = S.amp, om = S.omega;
-    for (int i = 0; i < 3; ++i) {
-        if (KIND == K_CIRCULAR) {
-            const double ro = A * (cd * S.e1[i] + sd * S.e2[i]);
-            k.R[i] = g.w[i] - ro;
-            k.v[i] = om * A * (-sd * S.e1[i] + cd * S.e2[i]);
-            k.a[i] = -om * om * ro;
-        } else {
-            k.R[i] = g.w[i] - A * cd * S.e1[i];
-            k.v[i] = -A * om * sd * S.e1[i];
-            k.a[i] = -A * om * om * cd * S.e1[i];
-        }
-    }
-    return true;
-}
-
-// Mixed path, uniform acceleration from rest: the same correction form,
-// tau = tau0 (1 + u) with tau0 = D0 / c the light time from the charge's
-// position at t (distance D0).  With L = a t^2 / 2 travelled by t and
-//   m = a tau (2t - tau) / 2   (tau <= t),   m = L   (tau > t, before the start),
-// the charge sits at L - m along e1 at t - tau, so with X = w1 - L
-//   f(u) = u (2 + u) - mh (2 Xh + mh) - K0h,  mh = m / D0 = (a / 2c)(1 + u)(2t - tau),
-// K0h = (perp^2 + X^2 - D0^2) / D0^2, where m and its first derivative are
-// continuous at the start of the motion.  FP32 Halley steps, then one FP64
-// Newton step, as for the oscillating families.  f has one root with u > -1
-// and f' > 0 around it (f' = 2 (c^2 tau - x1 v) / (c tau0)^2 with |x1 v| < c D),
-// so a lane whose FP32 steps did not settle continues with FP64 Newton steps
-// (up to 30) instead of a separate bracketed solver, whose registers would
-// spill the kernel; only if those fail too is the point flagged.
-// FULL (the FP64 path): the FP32 steps run to 2^-10 and the FP64 Newton steps
-// continue until a step is below 2^-50 (1 + |u|), three in the usual case (the
-// second leaves about the square of the FP32 stage's error, the third confirms);
-// returns false if they do not, and the caller takes the safeguarded solver.
-template <bool FULL = false>
-__device__ __forceinline__ bool solve_u_accel(const SrcRec &S, const Geo &g, Kin &k)
-{
-    const double t = S.t, acc = S.accel, L = S.Lmax;
-    const double X = g.w1 - L;
-    const double Dn2 = fma(X, X, g.w2);
-    const double D0 = sqrt_rough(Dn2);
-    if (!(D0 > 0.0)) return false;
-    const double iD0 = rcp_steer(D0), tau0 = D0 * INV_C;
-    const double Xh = X * iD0, K0h = fma(-D0, D0, Dn2) * (iD0 * iD0), gh = acc * (0.5 * INV_C), Lh = L * iD0;
-    const float Xf = (float)Xh, K0f = (float)K0h, gf = (float)gh, Lf = (float)Lh, tf = (float)t, t0f = (float)tau0;
-    float u = 0.f;
-    bool ok = false;
-    int n_it = 0;
-    for (int it = 0; it < 6; ++it) {
-        ++n_it;
-        const float tau = fmaf(t0f, u, t0f);
-        const bool moving = tau < tf;
-        const float m = moving ? gf * (1.f + u) * (2.f * tf - tau) : Lf;
-        const float mp = moving ? 2.f * gf * (tf - tau) : 0.f;
-        const float mpp = moving ? -2.f * gf * t0f : 0.f;
-        const float xm = Xf + m;
-        const float fv = fmaf(u, 2.f + u, fmaf(-m, Xf + xm, -K0f));
-        const float fp = fmaf(-2.f * mp, xm, 2.f + 2.f * u);
-        const float fpp = fmaf(-2.f, fmaf(mpp, xm, mp * mp), 2.f);
-        const float fp2 = fp * fp;
-        float den = fmaf(2.f, fp2, -fv * fpp);
-        den = den > fp2 ? den : 2.f * fp2;
-        const float d = -2.f * fv * fp * __builtin_amdgcn_rcpf(den);
-        u += d;
-        if (fabsf(d) <= (FULL ? 0x1p-10f : 0x1p-7f)) {
-            ok = true;
-            break;
-        }
-    }
-    // FP64 Newton: one step after settled FP32 steps (FULL: until converged, at most
-    // three), else until it settles
-    double ud = (ok && u > -0.5f) ? (double)u : 0.0;
-    const int n_newton = (ok && u > -0.5f) ? (FULL ? 3 : 1) : 30;
-    bool conv = !FULL && n_newton == 1;
-    for (int it = 0; it < n_newton; ++it) {
-        ++n_it;
-        const double tau = fma(tau0, ud, tau0);
-        const bool moving = tau < t;
-        const double m = moving ? gh * (1.0 + ud) * (2.0 * t - tau) : Lh;
-        const double mp = moving ? 2.0 * gh * (t - tau) : 0.0;
-        const double xm = Xh + m;
-        const double fv = fma(ud, 2.0 + ud, fma(-m, Xh + xm, -K0h));
-        const double fp = fma(-2.0 * mp, xm, 2.0 + 2.0 * ud);
-        const double du = -fv * rcp_steer(fp);
-        ud += du;
-        if (!conv && fabs(du) <= 0x1p-50 * (1.0 + fabs(ud))) {
-            conv = true;
-            break;
-        }
-    }
-    if (!(ud > -0.5)) conv = false;
-    const double tau = fma(tau0, ud, tau0);
-    const double tp = t - tau;
-    const double sd = (tp > 0.0) ? 0.5 * acc * tp * tp : 0.0;
-    const double vel = (tp > 0.0) ? acc * tp : 0.0;
-    const double ac = (tp > 0.0) ? acc : 0.0;
-    k.flags = conv ? 0u : FLAG_NOCONV;
-    k.iters = n_it;
-    k.tp = tp;
-    k.cph = 1.0;
-    k.sph = 0.0;
-    for (int i = 0; i < 3; ++i) {
-        k.R[i] = g.w[i] - sd * S.e1[i];
-        k.v[i] = vel * S.e1[i];
-        k.a[i] = ac * S.e1[i];
-    }
-    return conv;
-}
-
-// The rare fallback of the correction solves for the oscillating families (a
-// solve that did not settle): the safeguarded solver on a geometry rebuilt here
-// with its bracket, so that the main path neither builds the bracket nor keeps
-// the frame coordinates live across the times.
+// The rare fallback of the correction solves (a solve that did not settle): the
+// safeguarded solver, for the orbits on a geometry built here with its bracket,
+// so that the main path neither builds the bracket nor keeps the frame
+// coordinates live across the times.
 template <bool FULL, int KIND>
-__device__ __forceinline__ void retarded_fallback(const SrcRec &S, const double x[3], int max_iter, double tol_rel,
-                                                  Kin &k)
+__device__ __forceinline__ void retarded_fallback(const SrcRec &S, const Geo &g, const double x[3], int max_iter,
+                                                  double tol_rel, Kin &k)
 {
-    Geo gf;
-    geo_prepare_k<KIND>(S, x, gf);
-    if constexpr (KIND == K_CIRCULAR) solve_circular<FULL>(S, gf, max_iter, tol_rel, k);
-    else solve_linear<FULL>(S, gf, max_iter, tol_rel, k);
+    if constexpr (KIND == K_ACCEL) {
+        solve_accel<FULL>(S, g, max_iter, tol_rel, k);
+        if constexpr (!FULL) {
+            float bb = 0.f;
+            for (int i = 0; i < 3; ++i) {
+                k.bf[i] = (float)(k.v[i] * INV_C);
+                k.df[i] = (float)(k.a[i] * INV_C);
+                bb = fmaf(k.bf[i], k.bf[i], bb);
+            }
+            k.omb = 1.f - bb;
+        }
+    } else {
+        GeoSafe gf;
+        geo_safe<KIND>(S, x, gf);
+        if constexpr (KIND == K_CIRCULAR) solve_circular<FULL>(S, gf, max_iter, tol_rel, k);
+        else solve_linear<FULL>(S, gf, max_iter, tol_rel, k);
+    }
+    if (!FULL) k.iters |= ITER_FALLBACK;
 }
 
 // Retarded kinematics of a source S of family KIND (its record for the
-// observation time) seen from point x, with g = geo_prepare_k<KIND, BRACKET,
-// PHASE64>(record of any time of this source, x).  FULL: FP64 tolerance (square
-// roots to about one ulp); otherwise the mixed path's relaxed tolerance.
-// CORR (FULL only): the correction solves first, their fallback on a rebuilt
-// geometry (g needs no bracket); without it the safeguarded Halley solvers on g
-// directly (g with its bracket; fewer live registers, for kernels whose occupancy
-// the correction solve would cost).  The mixed path (FULL = false) always takes
-// the correction solves, with PHASE64 = false allowed.
-template <bool FULL, bool CORR, int KIND>
+// observation time) seen from point x, with g = geo_prepare_k<KIND>(record of any
+// time of this source, x).  FULL: to FP64 rounding; otherwise for FP32 fields
+// (phases good to about 1e-9).  Only the fallback can fail to converge: its flags
+// are added to `flags` there, off the usual path.
+template <bool FULL, int KIND>
 __device__ __forceinline__ void retarded_kind(const SrcRec &S, const Geo &g, const double x[3], int max_iter,
-                                              double tol_rel, Kin &k)
+                                              double tol_rel, Kin &k, uint32_t &flags)
 {
     if constexpr (KIND == K_CIRCULAR || KIND == K_LINEAR_OSC) {
-        if (FULL && !CORR) {
-            if constexpr (KIND == K_CIRCULAR) solve_circular<true>(S, g, max_iter, tol_rel, k);
-            else solve_linear<true>(S, g, max_iter, tol_rel, k);
-        } else if (FULL) {
-            if (!solve_u_full<KIND>(S, g, k)) retarded_fallback<true, KIND>(S, x, max_iter, tol_rel, k);
-        } else if (!solve_u_mixed<KIND>(S, g, k)) {
-            retarded_fallback<false, KIND>(S, x, max_iter, tol_rel, k);
-            k.iters |= ITER_FALLBACK;
+        if (!solve_orbit<KIND, FULL>(S, g, k)) {
+            retarded_fallback<FULL, KIND>(S, g, x, max_iter, tol_rel, k);
+            flags |= k.flags;
         }
     } else if constexpr (KIND == K_ACCEL) {
-        if (FULL) {
-            if (!CORR || !solve_u_accel<true>(S, g, k)) solve_accel<FULL>(S, g, max_iter, tol_rel, k);
-        } else {
-            solve_u_accel(S, g, k);
-            kin_beta_from_va(k);
+        if (!solve_accel_poly<FULL>(S, g, k)) {
+            retarded_fallback<FULL, KIND>(S, g, x, max_iter, tol_rel, k);
+            flags |= k.flags;
         }
     } else if constexpr (KIND == K_UNIFORM_VELOCITY) {
         solve_uniform<FULL>(S, x, k);
-        if (!FULL)
-            for (int i = 0; i < 3; ++i) {     // kin_beta_from_va's values, from the record
+        if (!FULL) {
+            for (int i = 0; i < 3; ++i) {     // beta from the record
                 k.bf[i] = S.bw1[i];
                 k.df[i] = 0.f;
             }
+            k.omb = S.omb;
+        }
     } else {
         for (int i = 0; i < 3; ++i) { k.R[i] = g.w[i]; k.v[i] = 0.0; k.a[i] = 0.0; k.bf[i] = 0.f; k.df[i] = 0.f; }
+        k.omb = 1.f;
         k.tp = S.t - sqrt(g.w[0] * g.w[0] + g.w[1] * g.w[1] + g.w[2] * g.w[2]) * INV_C;
         k.cph = 1.0;
         k.sph = 0.0;
@@ -1030,7 +983,9 @@ __device__ __forceinline__ F lw_terms(const Kin &k, F kq, int field_kind, F out[
     const F ic = (F)INV_C;
     const F nb = n0 * b0 + n1 * b1 + n2 * b2;
     const F kappa = (F)1 - nb;
-    const F bb = b0 * b0 + b1 * b1 + b2 * b2;
+    F omb;                                                  // 1 - beta^2
+    if constexpr (sizeof(F) == 4) omb = k.omb;
+    else omb = (F)1 - (b0 * b0 + b1 * b1 + b2 * b2);
     const F u0 = n0 - b0, u1 = n1 - b1, u2 = n2 - b2;
     const F nd = n0 * d0 + n1 * d1 + n2 * d2;
     const F ik = recip<F>(kappa);
@@ -1039,18 +994,20 @@ __device__ __forceinline__ F lw_terms(const Kin &k, F kq, int field_kind, F out[
     const F f = phi * ik * ik;                              // kq / (kappa^3 R)
     F cu, cd;                                               // E = f (u cu - beta_dot cd)
     if (field_kind == F_COULOMB) {
-        cu = ((F)1 - bb) * iD;
+        cu = omb * iD;
         cd = (F)0;
     } else if (field_kind == F_RADIATION) {
         cu = nd * ic;
         cd = kappa * ic;
     } else {
-        cu = ((F)1 - bb) * iD + nd * ic;
+        cu = omb * iD + nd * ic;
         cd = kappa * ic;
     }
-    const F E0 = f * (u0 * cu - d0 * cd);
-    const F E1 = f * (u1 * cu - d1 * cd);
-    const F E2 = f * (u2 * cu - d2 * cd);
+    cu *= f;
+    cd *= f;
+    const F E0 = u0 * cu - d0 * cd;
+    const F E1 = u1 * cu - d1 * cd;
+    const F E2 = u2 * cu - d2 * cd;
     const F m0 = IC ? n0 * ic : n0, m1 = IC ? n1 * ic : n1, m2 = IC ? n2 * ic : n2;  // n / c
     const F pc = IC ? phi * ic : phi;
     out[0] = phi;

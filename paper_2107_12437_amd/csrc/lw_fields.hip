@@ -61,9 +61,6 @@ __global__ void prep_kernel(const lw_traj *__restrict__ ch, int nch, const doubl
             R.v[i] = T.v[i];
             R.rt[i] = T.c0[i] + T.v[i] * t;
         }
-        R.e3[0] = T.e1[1] * T.e2[2] - T.e1[2] * T.e2[1];
-        R.e3[1] = T.e1[2] * T.e2[0] - T.e1[0] * T.e2[2];
-        R.e3[2] = T.e1[0] * T.e2[1] - T.e1[1] * T.e2[0];
         R.amp = T.amp;
         R.omega = T.omega;
         double s, c_;
@@ -72,6 +69,19 @@ __global__ void prep_kernel(const lw_traj *__restrict__ ch, int nch, const doubl
         R.sT = s;
         R.accel = T.accel;
         R.Lmax = (t > 0.0) ? 0.5 * T.accel * t * t : 0.0;
+        R.koc = T.omega * INV_C;
+        R.koc2 = R.koc * R.koc;
+        R.akoc = 2.0 * T.amp * R.koc2;
+        const double beta = T.amp * R.koc;
+        R.omb = (float)fma(-beta, beta, 1.0);
+        if (T.kind == K_CIRCULAR || T.kind == K_LINEAR_OSC) {
+            R.accel = R.koc * (ORBIT_TAB / TWO_PI);
+            R.Lmax = 1.0 / T.omega;
+            for (int i = 0; i < 3; ++i) {
+                R.v[i] = T.amp * T.e1[i];
+                R.rt[i] = T.kind == K_CIRCULAR ? T.amp * T.e2[i] : beta * beta;
+            }
+        }
         const double bw = T.amp * T.omega * INV_C, aw = bw * T.omega;
         for (int i = 0; i < 3; ++i) {
             R.bw1[i] = (float)(bw * T.e1[i]);
@@ -85,8 +95,14 @@ __global__ void prep_kernel(const lw_traj *__restrict__ ch, int nch, const doubl
             const double vv = T.v[0] * T.v[0] + T.v[1] * T.v[1] + T.v[2] * T.v[2];
             R.amp = C_LIGHT * C_LIGHT - vv;
             R.omega = rcp_steer(R.amp);
+            R.omb = (float)(R.amp * (INV_C * INV_C));
             for (int i = 0; i < 3; ++i) R.bw1[i] = (float)(T.v[i] * INV_C);
         }
+        if (T.kind == K_ACCEL)
+            for (int i = 0; i < 3; ++i) {
+                R.bw1[i] = (float)T.e1[i];
+                R.aw1[i] = (float)(T.accel * INV_C * T.e1[i]);
+            }
         recs[r] = R;
     }
     if (flags)
@@ -123,22 +139,20 @@ template <typename F, int TCH, bool HIST, int KIND, bool LSUM>
 __device__ __forceinline__ void charge_times(double *lsum, const SrcRec *__restrict__ R0, int nch, int c, const double x[3],
                                              int nti, int field_kind, int outputs, int max_iter, double tol_rel,
                                              double mask_r, bool live, double (&sum)[TCH][10],
-                                             uint32_t (&fl)[TCH], unsigned int *s_hist)
+                                             uint32_t (&fl)[TCH], uint64_t (&near)[TCH], unsigned int *s_hist)
 {
     Geo g;
-    // no bracket (the correction solves' fallback builds its own); the mixed path
-    // also takes its start phase to about 1e-11
-    geo_prepare_k<KIND, false, sizeof(F) == 8>(R0[c], x, g);
+    geo_prepare_k<KIND>(R0[c], x, g);
 #pragma unroll
     for (int j = 0; j < TCH; ++j) {
         if (j == 0 || j < nti) {
             const SrcRec &S = R0[(int64_t)j * nch + c];
             Kin k;
-            retarded_kind<sizeof(F) == 8, true, KIND>(S, g, x, max_iter, tol_rel, k);
+            retarded_kind<sizeof(F) == 8, KIND>(S, g, x, max_iter, tol_rel, k, fl[j]);
             F o[10];
             // A and B without their factor 1/c: the sums are scaled once at the end
             const F D = lw_terms<F, false>(k, sizeof(F) == 4 ? (F)S.kqf : (F)S.kq, field_kind, o);
-            fl[j] |= k.flags | ((D >= (F)mask_r) ? 0u : FLAG_MASKED);
+            near[j] |= __ballot(!(D >= (F)mask_r));
             if constexpr (HIST) {
                 if (live) {
                     const int bin = (k.iters & ITER_FALLBACK) ? ITER_BIN_FALLBACK : min(k.iters, ITER_BIN_FALLBACK - 1);
@@ -203,9 +217,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_for(s
     double *lsum = s_sums + (threadIdx.x >> 6) * (TCH * 10 * 64) + (threadIdx.x & 63);
     double sum[TCH][10];
     uint32_t fl[TCH];
+    uint64_t near[TCH];      // lanes with some charge closer than the mask radius (a scalar register pair)
 #pragma unroll
     for (int j = 0; j < TCH; ++j) {
         fl[j] = 0u;
+        near[j] = 0u;
 #pragma unroll
         for (int q = 0; q < 10; ++q) {
             if constexpr (LSUM) lsum[(j * 10 + q) * 64] = 0.0;
@@ -220,23 +236,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_for(s
         switch (R0[c].kind) {
         case K_CIRCULAR:
             charge_times<F, TCH, HIST, K_CIRCULAR, LSUM>(lsum, R0, nch, c, x, nti, field_kind, outputs, max_iter, tol_rel,
-                                                   mask_r, live, sum, fl, s_hist);
+                                                   mask_r, live, sum, fl, near, s_hist);
             break;
         case K_LINEAR_OSC:
             charge_times<F, TCH, HIST, K_LINEAR_OSC, LSUM>(lsum, R0, nch, c, x, nti, field_kind, outputs, max_iter, tol_rel,
-                                                     mask_r, live, sum, fl, s_hist);
+                                                     mask_r, live, sum, fl, near, s_hist);
             break;
         case K_ACCEL:
             charge_times<F, TCH, HIST, K_ACCEL, LSUM>(lsum, R0, nch, c, x, nti, field_kind, outputs, max_iter, tol_rel,
-                                                mask_r, live, sum, fl, s_hist);
+                                                mask_r, live, sum, fl, near, s_hist);
             break;
         case K_UNIFORM_VELOCITY:
             charge_times<F, TCH, HIST, K_UNIFORM_VELOCITY, LSUM>(lsum, R0, nch, c, x, nti, field_kind, outputs, max_iter,
-                                                           tol_rel, mask_r, live, sum, fl, s_hist);
+                                                           tol_rel, mask_r, live, sum, fl, near, s_hist);
             break;
         default:
             charge_times<F, TCH, HIST, K_STATIONARY, LSUM>(lsum, R0, nch, c, x, nti, field_kind, outputs, max_iter, tol_rel,
-                                                     mask_r, live, sum, fl, s_hist);
+                                                     mask_r, live, sum, fl, near, s_hist);
             break;
         }
     }
@@ -251,7 +267,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_for(s
     for (int j = 0; j < TCH; ++j) {
         if (j < nti) {
             F *dst = out + (int64_t)(t0 + j) * nrows * npts + p;
-            const bool masked = (fl[j] & FLAG_MASKED) != 0u;
+            const bool masked = (near[j] >> (threadIdx.x & 63)) & 1u;
             int r = 0;
             auto put = [&](double v) {
                 __builtin_nontemporal_store(masked ? qnan<F>() : (F)v, dst + (int64_t)r * npts);
@@ -274,7 +290,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_for(s
                 put((S[6] * S[7] - S[4] * S[9]) * IMU0);
                 put((S[4] * S[8] - S[5] * S[7]) * IMU0);
             }
-            fl_all |= fl[j];
+            fl_all |= fl[j] | (masked ? FLAG_MASKED : 0u);
         }
     }
     if (flags && fl_all) atomicOr(flags + p, fl_all);
