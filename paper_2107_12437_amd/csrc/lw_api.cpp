@@ -84,9 +84,9 @@ struct lw_ctx {
     bool stage_pending = false;
     uint32_t *d_err = nullptr;
     lw::FieldLaunch field_launch{256, 2};  // untuned shape: the fastest on the grid benchmark in both precisions
-    hipStream_t side = nullptr;        // small instances run here, joined back into the caller's stream
+    hipStream_t side = nullptr, side2 = nullptr;   // persistent instances beside the stepped ones, joined back
     hipStream_t capture = nullptr;     // graph capture of stepped runs
-    hipEvent_t join_a = nullptr, join_b = nullptr;
+    hipEvent_t join_a = nullptr, join_b = nullptr, join_c = nullptr;
     hipGraph_t graph = nullptr;        // last stepped run's graph, released once the stream passed it
     hipGraphExec_t graph_exec = nullptr;
     hipEvent_t graph_done = nullptr;
@@ -410,7 +410,9 @@ lw_status lw_destroy(lw_ctx *ctx)
     if (ctx->graph_done) (void)hipEventDestroy(ctx->graph_done);
     if (ctx->join_a) (void)hipEventDestroy(ctx->join_a);
     if (ctx->join_b) (void)hipEventDestroy(ctx->join_b);
+    if (ctx->join_c) (void)hipEventDestroy(ctx->join_c);
     if (ctx->side) (void)hipStreamDestroy(ctx->side);
+    if (ctx->side2) (void)hipStreamDestroy(ctx->side2);
     if (ctx->adj_side) (void)hipStreamDestroy(ctx->adj_side);
     if (ctx->adj_built) (void)hipEventDestroy(ctx->adj_built);
     if (ctx->adj_swept) (void)hipEventDestroy(ctx->adj_swept);
@@ -906,7 +908,12 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
         const lw_status tst = tune_stepped(ctx, h_dip, n_dip, h_inst_off, n_inst, dt, opts, ring, s, &stepped_min);
         if (tst != LW_OK) return tst;
     }
-    std::vector<int32_t> lds_list, tgt, tgt_lo, tgt_n;
+    bool moving = false;
+    for (int i = 0; i < n_dip; ++i) moving = moving || motion_reach(h_dip[i]) > 0.0;
+    // the smallest instances (one wave each) apart from the others, whose kernel is
+    // slower for them: 256 pairs beside one 5-dipole instance would all take it
+    const int tiny_n = moving ? 0 : lw::dipole_small_max_n();
+    std::vector<int32_t> tiny_list, lds_list, tgt, tgt_lo, tgt_n;
     std::vector<int64_t> tgt_base;
     int max_lds_n = 0;
     int64_t ring_doubles = 0;
@@ -914,6 +921,10 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
         const int a0 = h_inst_off[k], n = h_inst_off[k + 1] - a0;
         if (n == 0) continue;
         if (n < stepped_min && lw::ring_lds_bytes(n, ring) <= lds_limit) {
+            if (n <= tiny_n) {
+                tiny_list.push_back(k);
+                continue;
+            }
             lds_list.push_back(k);
             max_lds_n = std::max(max_lds_n, n);
         } else {
@@ -949,7 +960,7 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
 
     const size_t in_bytes = align_up(sizeof(lw_dipole) * (size_t)n_dip, 256);
     const size_t off_bytes = align_up(sizeof(int32_t) * (size_t)(n_inst + 1), 256);
-    const size_t list_bytes = align_up(sizeof(int32_t) * (lds_list.size() + 1), 256);
+    const size_t list_bytes = align_up(sizeof(int32_t) * (tiny_list.size() + lds_list.size() + 1), 256);
     const size_t t32_bytes = align_up(sizeof(int32_t) * (n_tgt + 1), 256);
     const size_t t64_bytes = align_up(sizeof(int64_t) * (n_tgt + 1), 256);
     const size_t stage_bytes = in_bytes + off_bytes + list_bytes + 3 * t32_bytes + t64_bytes;
@@ -975,7 +986,8 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     o += in_bytes;
     std::memcpy(stage + o, h_inst_off, sizeof(int32_t) * (size_t)(n_inst + 1));
     o += off_bytes;
-    std::copy(lds_list.begin(), lds_list.end(), (int32_t *)(stage + o));
+    std::copy(tiny_list.begin(), tiny_list.end(), (int32_t *)(stage + o));
+    std::copy(lds_list.begin(), lds_list.end(), (int32_t *)(stage + o) + tiny_list.size());
     o += list_bytes;
     std::copy(tgt.begin(), tgt.end(), (int32_t *)(stage + o));
     o += t32_bytes;
@@ -1019,26 +1031,38 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
 
     const double max_vel = opts->max_vel > 0.0 ? opts->max_vel : C_LIGHT / 100.0;
     const int max_iter = 60;
-    LW_HIP(lw::launch_dipole_prep(d_in, n_dip, d_dev, s));
+    LW_HIP(lw::launch_dipole_prep(d_in, n_dip, dt, d_dev, s));
     const lw::RunOut out{d_moment, d_dot, d_energy, d_drive, d_wabs, d_wrad, opts->out_stride, n_dip};
     // a resumed run's row 0 comes from its state, before either path updates it
     if (resume) LW_HIP(lw::launch_state_rows(d_dev, d_off, n_inst, d_state, ring, out, ctx->d_err, s));
-    const bool both = !lds_list.empty() && n_tgt > 0;
-    hipStream_t small_s = s;
-    if (both) {
-        if (!ctx->side) LW_HIP(hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
-        if (!ctx->join_a) LW_HIP(hipEventCreateWithFlags(&ctx->join_a, hipEventDisableTiming));
-        if (!ctx->join_b) LW_HIP(hipEventCreateWithFlags(&ctx->join_b, hipEventDisableTiming));
-        LW_HIP(hipEventRecord(ctx->join_a, s));
-        LW_HIP(hipStreamWaitEvent(ctx->side, ctx->join_a, 0));
-        small_s = ctx->side;
-    }
-    bool moving = false;
-    for (int i = 0; i < n_dip; ++i) moving = moving || motion_reach(h_dip[i]) > 0.0;
     const bool mixed = opts->precision == LW_MIXED;
-    LW_HIP(lw::launch_dipole_instances(d_dev, d_off, d_list, (int)lds_list.size(), max_lds_n, true, nullptr, nullptr,
+    // up to three kinds of instances run at once: the last kind present on the
+    // caller's stream, the others on side streams forked from it and joined back
+    const bool fork_lds = !lds_list.empty() && n_tgt > 0;
+    const bool fork_tiny = !tiny_list.empty() && (n_tgt > 0 || !lds_list.empty());
+    if (fork_lds || fork_tiny) {
+        if (!ctx->join_a) LW_HIP(hipEventCreateWithFlags(&ctx->join_a, hipEventDisableTiming));
+        LW_HIP(hipEventRecord(ctx->join_a, s));
+    }
+    auto forked = [&](bool fork, hipStream_t &side, hipEvent_t &join, hipStream_t &on) -> lw_status {
+        on = s;
+        if (!fork) return LW_OK;
+        if (!side) LW_HIP(hipStreamCreateWithFlags(&side, hipStreamNonBlocking));
+        if (!join) LW_HIP(hipEventCreateWithFlags(&join, hipEventDisableTiming));
+        LW_HIP(hipStreamWaitEvent(side, ctx->join_a, 0));
+        on = side;
+        return LW_OK;
+    };
+    hipStream_t lds_s = s, tiny_s = s;
+    st = forked(fork_lds, ctx->side, ctx->join_b, lds_s);
+    if (st == LW_OK) st = forked(fork_tiny, ctx->side2, ctx->join_c, tiny_s);
+    if (st != LW_OK) return st;
+    LW_HIP(lw::launch_dipole_instances(d_dev, d_off, d_list + tiny_list.size(), (int)lds_list.size(), max_lds_n, true,
+                                       nullptr, nullptr, ring, steps, dt, max_vel, max_iter, out, moving, mixed,
+                                       d_state, resume, ctx->d_err, lds_s));
+    LW_HIP(lw::launch_dipole_instances(d_dev, d_off, d_list, (int)tiny_list.size(), tiny_n, true, nullptr, nullptr,
                                        ring, steps, dt, max_vel, max_iter, out, moving, mixed, d_state, resume,
-                                       ctx->d_err, small_s));
+                                       ctx->d_err, tiny_s));
     if (n_tgt > 0) {
         if (!ctx->capture) LW_HIP(hipStreamCreateWithFlags(&ctx->capture, hipStreamNonBlocking));
         if (!ctx->graph_done) LW_HIP(hipEventCreateWithFlags(&ctx->graph_done, hipEventDisableTiming));
@@ -1049,9 +1073,13 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
                                        &ctx->graph_exec));
         LW_HIP(hipEventRecord(ctx->graph_done, s));
     }
-    if (both) {
-        LW_HIP(hipEventRecord(ctx->join_b, ctx->side));
+    if (fork_lds) {
+        LW_HIP(hipEventRecord(ctx->join_b, lds_s));
         LW_HIP(hipStreamWaitEvent(s, ctx->join_b, 0));
+    }
+    if (fork_tiny) {
+        LW_HIP(hipEventRecord(ctx->join_c, tiny_s));
+        LW_HIP(hipStreamWaitEvent(s, ctx->join_c, 0));
     }
     if (d_state) LW_HIP(lw::launch_state_header(d_state, ring, n_dip, steps, resume, s));
     return LW_OK;
@@ -1268,7 +1296,7 @@ static lw_status vjp_pipelined(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_di
     const int64_t *d_pair_off = (const int64_t *)(stage_dev + dip_b + off_b);
     const int64_t *d_pair_off0 = (const int64_t *)(stage_dev + dip_b + off_b + po_b);
     const double *d_times = (const double *)(stage_dev + dip_b + off_b + 2 * po_b);
-    LW_HIP(lw::launch_dipole_prep(d_in, n_dip, d_dev, s));
+    LW_HIP(lw::launch_dipole_prep(d_in, n_dip, dt, d_dev, s));
     lw_run_opts fo = *opts;
     if (whole) {
         // forward run with every step stored, then the whole history

@@ -30,7 +30,7 @@ namespace lw {
 
 size_t dip_dev_bytes(int n) { return dip_dev_array_bytes(n) + sizeof(double) * SF_COUNT * (size_t)n; }
 
-__global__ void dipole_prep_kernel(const lw_dipole *__restrict__ in, int n, DipDev *__restrict__ dev,
+__global__ void dipole_prep_kernel(const lw_dipole *__restrict__ in, int n, double dt, DipDev *__restrict__ dev,
                                    double *__restrict__ soa)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -59,15 +59,16 @@ __global__ void dipole_prep_kernel(const lw_dipole *__restrict__ in, int n, DipD
     o.mph = moves ? D.motion_phase : 0.0;
     o.mspeed = moves ? fabs(D.motion_omega) * am : 0.0;
     o.ehalf = 0.5 / o.f;
+    rk4_coefs(o.omega0 * o.omega0, o.gamma0, o.f, dt, o.rk);
     dev[i] = o;
     const double f[SF_COUNT] = {o.origin[0], o.origin[1], o.origin[2], o.axis[0], o.axis[1], o.axis[2], o.cfp,
                                 o.cfm,       o.d0,        o.q,         o.mamp[0], o.mamp[1], o.mamp[2], o.mw, o.mph};
     for (int k = 0; k < SF_COUNT; ++k) soa[(int64_t)k * n + i] = f[k];
 }
 
-hipError_t launch_dipole_prep(const lw_dipole *d_in, int n, DipDev *d_dev, hipStream_t s)
+hipError_t launch_dipole_prep(const lw_dipole *d_in, int n, double dt, DipDev *d_dev, hipStream_t s)
 {
-    hipLaunchKernelGGL(dipole_prep_kernel, dim3((n + 255) / 256), dim3(256), 0, s, d_in, n, d_dev,
+    hipLaunchKernelGGL(dipole_prep_kernel, dim3((n + 255) / 256), dim3(256), 0, s, d_in, n, dt, d_dev,
                        dip_soa(d_dev, n));
     return hipGetLastError();
 }
@@ -338,8 +339,30 @@ __device__ __forceinline__ double charge_field(const DipLds &Si, const double R[
 // taken at the target's origin at that time.  MOVING: origins may move; without
 // it every origin is taken as fixed (the kernels for fixed origins carry none
 // of the moving-origin code).
+// Separation of a target at X from a fixed source j: |Delta|^2, |Delta| and its
+// reciprocal, and the projections Delta . p_j, Delta . p_i and p_i . p_j that the
+// scalar drive needs (constant over a run when both origins are fixed).
+struct PairGeo {
+    double L2, L, iL, sD, sI, pij;
+};
+
+__device__ __forceinline__ PairGeo pair_geo(const double X[3], const DipLds &Si, const DipLds &Sj)
+{
+    PairGeo P;
+    const double dx = X[0] - Sj.ox, dy = X[1] - Sj.oy, dz = X[2] - Sj.oz;
+    P.L2 = dx * dx + dy * dy + dz * dz;
+    root_rsqrt<true>(P.L2, P.L, P.iL);
+    P.iL = fma(P.iL, fma(-P.L, P.iL, 1.0), P.iL);
+    P.sD = dx * Sj.px + dy * Sj.py + dz * Sj.pz;     // Delta . p_j
+    P.sI = dx * Si.px + dy * Si.py + dz * Si.pz;     // Delta . p_i
+    P.pij = Si.px * Sj.px + Si.py * Sj.py + Si.pz * Sj.pz;
+    return P;
+}
+
 // p_i . E (Eq. (E), total field, FP64) at the origin of target i of the charge
-// (cf, kq) of a fixed source j, from its stored state h at the retarded time.
+// (cf, kq) of a fixed source j, from its stored state h at the retarded time.  Every
+// term is formed as its difference from p_i . Delta / L^3, the field of the charge at
+// rest at the source's origin, which is added last (as small_field).
 // The charge moves along p_j, so beta and beta_dot are multiples of p_j and
 // every vector product of Eq. (E) reduces to the scalars
 //   w = R . p_j = sD - rho,  p_i . R = sI - rho pij,  pij = p_i . p_j,
@@ -349,40 +372,27 @@ __device__ __forceinline__ double charge_field(const DipLds &Si, const double R[
 //   f = kq / (kappa^3 |R|), q = pij - (p_i . n)(n . p_j),
 // where the radiation term's beta parts cancel exactly (q is p_i . the part
 // of p_j across n).
-__device__ __forceinline__ double drive_scalar(double L2, double sD, double sI, double pij, double cf, double kq,
-                                               const double h[3])
+__device__ __forceinline__ double drive_scalar(const PairGeo &P, double cf, double kq, const double h[3])
 {
-    const double rho = cf * h[0];
+    const double x = cf * h[0] * P.iL, mu = P.sD * P.iL, muI = P.sI * P.iL;
+    const double y = x * fma(-2.0, mu, x);
     double D, iD;
-    root_rsqrt<true>(fma(rho, rho - 2.0 * sD, L2), D, iD);
+    root_rsqrt<true>(1.0 + y, D, iD);
     iD = fma(iD, fma(-D, iD, 1.0), iD);
-    const double b = cf * h[1] * INV_C, e = cf * h[2] * INV_C;
-    const double wn = (sD - rho) * iD;                  // n . p_j
-    const double pin = (sI - rho * pij) * iD;           // p_i . n
-    const double kappa = 1.0 - b * wn;
-    const double ik = recip<double>(kappa);
-    const double f = kq * iD * ik * ik * ik;
-    const double q = pij - pin * wn;
-    return f * ((pin - b * pij) * (1.0 - b * b) * iD - e * q * INV_C);
-}
-
-// Separation of a target at X from a fixed source j: |Delta|^2, |Delta|, and
-// the projections Delta . p_j, Delta . p_i and p_i . p_j that the scalar drive
-// needs (constant over a run when both origins are fixed).
-struct PairGeo {
-    double L2, L, sD, sI, pij;
-};
-
-__device__ __forceinline__ PairGeo pair_geo(const double X[3], const DipLds &Si, const DipLds &Sj)
-{
-    PairGeo P;
-    const double dx = X[0] - Sj.ox, dy = X[1] - Sj.oy, dz = X[2] - Sj.oz;
-    P.L2 = dx * dx + dy * dy + dz * dz;
-    P.sD = dx * Sj.px + dy * Sj.py + dz * Sj.pz;     // Delta . p_j
-    P.L = sqrt(P.L2);
-    P.sI = dx * Si.px + dy * Si.py + dz * Si.pz;     // Delta . p_i
-    P.pij = Si.px * Sj.px + Si.py * Sj.py + Si.pz * Sj.pz;
-    return P;
+    const double b = cf * h[1] * INV_C, e = cf * h[2] * (INV_C * INV_C) * P.L;
+    const double j = -y * recip<double>(1.0 + D) * iD;   // 1 / D - 1
+    const double wn = (mu - x) * iD;                     // n . p_j
+    const double dp = fma(j, muI, -(x * P.pij) * iD);    // p_i . n - muI
+    const double pin = muI + dp;
+    const double jj = fma(j, j, j + j);
+    const double z = b * wn, kappa = 1.0 - z, ik = recip<double>(kappa);
+    const double k = z * fma(kappa, kappa, 1.0 + kappa) * (ik * ik * ik);   // 1 / kappa^3 - 1
+    const double q = fma(-pin, wn, P.pij);
+    double B = fma(pin, jj, dp);
+    B = fma(-b * (1.0 + jj), fma(b, fma(-b, P.pij, pin), P.pij), B);
+    B = fma(-e * q, iD, B);
+    B = fma(k, muI + B, B);
+    return kq * (P.iL * P.iL) * (muI + B);
 }
 
 // p_i . E of the charge (cf, kq) of the fixed source j at separation P, at
@@ -395,18 +405,88 @@ __device__ __forceinline__ double fixed_drive(const Hist &H, const PairGeo &P, i
     g.k = seg_none<I>();
     double h[3];
     charge_fixed(H, j, d0, nstep, base, P.L2, P.L, P.sD, cf, max_iter, g, h, err);
-    return drive_scalar(P.L2, P.sD, P.sI, P.pij, cf, kq, h);
+    return drive_scalar(P, cf, kq, h);
+}
+
+// The drive (small_field times kl = kq / L^2) of the charge cf of a fixed source whose root
+// lies in the segment of rows r0, r1, from the step u0 at one light time of L.
+// Returns false, for the caller's general solvers, outside small_root's and
+// small_field's range or when the root leaves the segment.
+template <bool DIFF>
+__device__ __forceinline__ bool small_charge(const SmallK &c, double mu, double muI, double w, double u0, double cf, double kl,
+                                             const PairGeo &P, const double r0[3], const double r1[3], double &drive)
+{
+    const double ci = cf * P.iL;
+    SmallRoot r;
+    small_root<false>(c, mu, w, u0, ci * r0[0], ci * (r1[0] - r0[0]), 0.0, 0.0, r);
+    const double b = cf * INV_C * fma(r.u, r1[1] - r0[1], r0[1]);
+    const double e = cf * (INV_C * INV_C) * P.L * fma(r.u, r1[2] - r0[2], r0[2]);
+    // a root within rounding of a segment end belongs to either side
+    const bool ok = fma(fabs(b), c.lz, r.out) <= 1.0 && fabs(r.u - 0.5) <= 0.5 + 1e-9;
+    drive = kl * small_field<DIFF>(c, mu, muI, P.pij, r, b, e);
+    return ok;
+}
+
+// The segment of a fixed source that one light time of L before stage theta points to,
+// if it is stored or before t = 0 (the static pre-history, rows d0, 0, 0): the start u0
+// in it and its rows.
+__device__ __forceinline__ bool stored_segment(const Hist &H, const PairGeo &P, int j, int64_t nstep, double theta,
+                                               double w, double d0, double &u0, double r0[3], double r1[3],
+                                               uint32_t &err)
+{
+    const double f = floor(theta - w);
+    const int kf = (int)f;
+    if (!(f < 0.0)) return false;
+    if (nstep + kf >= 0 && -kf > H.mask) err |= ERR_HISTORY;
+    const double *p0 = H.ring + ((int64_t)((nstep + kf) & H.mask) * H.n + j) * 3;
+    const double *p1 = H.ring + ((int64_t)((nstep + kf + 1) & H.mask) * H.n + j) * 3;
+    const bool pre = nstep + kf < 0;
+    for (int c = 0; c < 3; ++c) {
+        r0[c] = pre ? (c == 0 ? d0 : 0.0) : p0[c];
+        r1[c] = pre ? (c == 0 ? d0 : 0.0) : p1[c];
+    }
+    u0 = theta - w - f;
+    return true;
+}
+
+// Both charges of a fixed source at one stage time by small_charge.  False: the
+// caller takes the general solvers.
+template <bool DIFF>
+__device__ __forceinline__ bool small_source(const SmallK &c, const Hist &H, const PairGeo &P, int j, double d0, double cfp, double cfm,
+                                             double kq, int64_t nstep, double theta, double &e, uint32_t &err)
+{
+    const double w = P.L * (INV_C * H.inv_dt), mu = P.sD * P.iL, muI = P.sI * P.iL, kl = kq * (P.iL * P.iL);
+    double u0, r0[3], r1[3], ep, em;
+    if (!stored_segment(H, P, j, nstep, theta, w, d0, u0, r0, r1, err)) return false;
+    const bool op = small_charge<DIFF>(c, mu, muI, w, u0, cfp, kl, P, r0, r1, ep);
+    const bool om = small_charge<DIFF>(c, mu, muI, w, u0, cfm, -kl, P, r0, r1, em);
+    e = ep + em;
+    return op && om;
+}
+
+// The same for one charge (kq with its sign).
+__device__ __forceinline__ bool small_one(const SmallK &c, const Hist &H, const PairGeo &P, int j, double d0, double cf, double kq,
+                                          int64_t nstep, double theta, double &e, uint32_t &err)
+{
+    const double w = P.L * (INV_C * H.inv_dt);
+    double u0, r0[3], r1[3];
+    if (!stored_segment(H, P, j, nstep, theta, w, d0, u0, r0, r1, err)) return false;
+    return small_charge<false>(c, P.sD * P.iL, P.sI * P.iL, w, u0, cf, kq * (P.iL * P.iL), P, r0, r1, e);
 }
 
 template <bool MOVING>
-__device__ double pair_drive(const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double cf, double kq,
+__device__ __forceinline__ double pair_drive(const SmallK &c, const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double cf, double kq,
                              int64_t nstep, double theta, int max_iter, uint32_t &err)
 {
     const double base = (double)nstep + theta;
     double X[3] = {Si.ox, Si.oy, Si.oz};
     if (MOVING) origin_at(Si, base * H.dt, X);
-    if (!MOVING || Sj.mw == 0.0)
-        return fixed_drive(H, pair_geo(X, Si, Sj), j, Sj.d0, cf, kq, nstep, base, max_iter, err);
+    if (!MOVING || Sj.mw == 0.0) {
+        const PairGeo P = pair_geo(X, Si, Sj);
+        double e;
+        if (small_one(c, H, P, j, Sj.d0, cf, kq, nstep, theta, e, err)) return e;
+        return fixed_drive(H, P, j, Sj.d0, cf, kq, nstep, base, max_iter, err);
+    }
     if constexpr (MOVING) {
         double R[3], v[3], a[3];
         charge_moving(H, Sj, j, cf, nstep, base, X, max_iter, R, v, a, err);
@@ -527,7 +607,7 @@ __device__ __forceinline__ double mixed_field(const MixedGeo &G, double cfp, dou
 }
 
 template <bool MOVING>
-__device__ double dipole_drive_mixed(const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double kq,
+__device__ __forceinline__ double dipole_drive_mixed(const SmallK &c, const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double kq,
                                      int64_t nstep, double theta, int max_iter, uint32_t &err)
 {
     const double base = (double)nstep + theta;
@@ -542,6 +622,8 @@ __device__ double dipole_drive_mixed(const Hist &H, const DipLds &Si, const DipL
             return e + charge_field(Si, R, v, a, -kq);
         }
     }
+    double e;
+    if (small_source<true>(c, H, pair_geo(X, Si, Sj), j, Sj.d0, Sj.cfp, Sj.cfm, kq, nstep, theta, e, err)) return e;
     const MixedGeo G = mixed_geo(X, Si, Sj);
     Seg g;
     g.k = seg_none<int64_t>();
@@ -557,7 +639,7 @@ __device__ double dipole_drive_mixed(const Hist &H, const DipLds &Si, const DipL
 // lie about 1e-4 of a step apart), so the lane loads the segment once.  The
 // per-charge terms are those of pair_drive.
 template <bool MOVING>
-__device__ double dipole_drive_fp64(const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double kq,
+__device__ __forceinline__ double dipole_drive_fp64(const SmallK &c, const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double kq,
                                     int64_t nstep, double theta, int max_iter, uint32_t &err)
 {
     const double base = (double)nstep + theta;
@@ -572,18 +654,15 @@ __device__ double dipole_drive_fp64(const Hist &H, const DipLds &Si, const DipLd
             return e + charge_field(Si, R, v, a, -kq);
         }
     }
-    const double dx = X[0] - Sj.ox, dy = X[1] - Sj.oy, dz = X[2] - Sj.oz;
-    const double L2 = dx * dx + dy * dy + dz * dz;
-    const double sD = dx * Sj.px + dy * Sj.py + dz * Sj.pz;     // Delta . p_j
-    const double sI = dx * Si.px + dy * Si.py + dz * Si.pz;     // Delta . p_i
-    const double pij = Si.px * Sj.px + Si.py * Sj.py + Si.pz * Sj.pz;
-    const double L = sqrt(L2);
+    const PairGeo P = pair_geo(X, Si, Sj);
+    double e;
+    if (small_source<false>(c, H, P, j, Sj.d0, Sj.cfp, Sj.cfm, kq, nstep, theta, e, err)) return e;
     Seg g;
     g.k = seg_none<int64_t>();
     double hp[3], hm[3];
-    charge_fixed(H, j, Sj.d0, nstep, base, L2, L, sD, Sj.cfp, max_iter, g, hp, err);
-    charge_fixed(H, j, Sj.d0, nstep, base, L2, L, sD, Sj.cfm, max_iter, g, hm, err);
-    return drive_scalar(L2, sD, sI, pij, Sj.cfp, kq, hp) + drive_scalar(L2, sD, sI, pij, Sj.cfm, -kq, hm);
+    charge_fixed(H, j, Sj.d0, nstep, base, P.L2, P.L, P.sD, Sj.cfp, max_iter, g, hp, err);
+    charge_fixed(H, j, Sj.d0, nstep, base, P.L2, P.L, P.sD, Sj.cfm, max_iter, g, hm, err);
+    return drive_scalar(P, Sj.cfp, kq, hp) + drive_scalar(P, Sj.cfm, -kq, hm);
 }
 
 // The segments charge_fixed starts from at both stage times of a step (those
@@ -627,70 +706,135 @@ __device__ __forceinline__ void seg_stages(const Hist &H, int j, double d0, I ns
     if (kf >= nstep) gf.k = seg_none<I>();
 }
 
-// Both stage times of a step (t_n + dt/2 and t_n + dt) for both charges of a
-// fixed source, with the operations of two dipole_drive_fp64 calls (so the
-// same results).  The history rows of both stages' first segments are loaded
-// together at the start, so the second stage does not wait on memory after the
-// first stage's solves: 176 against 184 us per step on 64 clusters of 12,530
-// dipoles, although the lane then holds 147 VGPRs (3 waves per SIMD, against 4
-// at 115).  Loading each stage's two rows separately (144 VGPRs) was slower,
-// 196 us, and so was solving all four charges before their fields, 179 us.
-__device__ __forceinline__ void dipole_drive_fp64_stages(const Hist &H, const DipLds &Si, const DipLds &Sj, int j,
-                                                         double kq, int64_t nstep, int max_iter, uint32_t &err,
-                                                         double &e_half, double &e_full)
-{
-    const double dx = Si.ox - Sj.ox, dy = Si.oy - Sj.oy, dz = Si.oz - Sj.oz;
-    const double L2 = dx * dx + dy * dy + dz * dz;
-    const double sD = dx * Sj.px + dy * Sj.py + dz * Sj.pz;     // Delta . p_j
-    const double sI = dx * Si.px + dy * Si.py + dz * Si.pz;     // Delta . p_i
-    const double pij = Si.px * Sj.px + Si.py * Sj.py + Si.pz * Sj.pz;
-    const double L = sqrt(L2);
-    const double base_h = (double)nstep + 0.5, base_f = (double)nstep + 1.0;
-    Seg gh, gf;
-    seg_stages(H, j, Sj.d0, nstep, base_h, base_f, L, gh, gf, err);
-    double hp[3], hm[3];
-    charge_fixed(H, j, Sj.d0, nstep, base_h, L2, L, sD, Sj.cfp, max_iter, gh, hp, err);
-    charge_fixed(H, j, Sj.d0, nstep, base_h, L2, L, sD, Sj.cfm, max_iter, gh, hm, err);
-    e_half = drive_scalar(L2, sD, sI, pij, Sj.cfp, kq, hp) + drive_scalar(L2, sD, sI, pij, Sj.cfm, -kq, hm);
-    charge_fixed(H, j, Sj.d0, nstep, base_f, L2, L, sD, Sj.cfp, max_iter, gf, hp, err);
-    charge_fixed(H, j, Sj.d0, nstep, base_f, L2, L, sD, Sj.cfm, max_iter, gf, hm, err);
-    e_full = drive_scalar(L2, sD, sI, pij, Sj.cfp, kq, hp) + drive_scalar(L2, sD, sI, pij, Sj.cfm, -kq, hm);
-}
-
-// The mixed drive of a fixed source at both stage times of a step, with the
-// operations of two dipole_drive_mixed calls and the segment loads of
-// dipole_drive_fp64_stages: 189 against 207 us per step on 64 clusters of
-// 12,530 dipoles, against a lane per (stage, source).
-__device__ __forceinline__ void dipole_drive_mixed_stages(const Hist &H, const DipLds &Si, const DipLds &Sj, int j,
-                                                          double kq, int64_t nstep, int max_iter, uint32_t &err,
-                                                          double &e_half, double &e_full)
+// Both stage drives of a fixed source through the general solvers.
+template <bool MIXED>
+__device__ __forceinline__ void drive_stages_general(const Hist &H, const DipLds &Si, const DipLds &Sj, int j,
+                                                     double kq, int64_t nstep, int max_iter, uint32_t &err,
+                                                     double &e_half, double &e_full)
 {
     const double X[3] = {Si.ox, Si.oy, Si.oz};
-    const MixedGeo G = mixed_geo(X, Si, Sj);
+    const PairGeo P = pair_geo(X, Si, Sj);
     const double base_h = (double)nstep + 0.5, base_f = (double)nstep + 1.0;
     Seg gh, gf;
-    seg_stages(H, j, Sj.d0, nstep, base_h, base_f, G.L, gh, gf, err);
+    seg_stages(H, j, Sj.d0, nstep, base_h, base_f, P.L, gh, gf, err);
     double hp[3], hm[3];
-    charge_fixed(H, j, Sj.d0, nstep, base_h, G.L2, G.L, G.sD, Sj.cfp, max_iter, gh, hp, err);
-    charge_fixed(H, j, Sj.d0, nstep, base_h, G.L2, G.L, G.sD, Sj.cfm, max_iter, gh, hm, err);
-    e_half = mixed_field(G, Sj.cfp, Sj.cfm, hp, hm, kq);
-    charge_fixed(H, j, Sj.d0, nstep, base_f, G.L2, G.L, G.sD, Sj.cfp, max_iter, gf, hp, err);
-    charge_fixed(H, j, Sj.d0, nstep, base_f, G.L2, G.L, G.sD, Sj.cfm, max_iter, gf, hm, err);
-    e_full = mixed_field(G, Sj.cfp, Sj.cfm, hp, hm, kq);
+    charge_fixed(H, j, Sj.d0, nstep, base_h, P.L2, P.L, P.sD, Sj.cfp, max_iter, gh, hp, err);
+    charge_fixed(H, j, Sj.d0, nstep, base_h, P.L2, P.L, P.sD, Sj.cfm, max_iter, gh, hm, err);
+    if constexpr (MIXED) e_half = mixed_field(mixed_geo(X, Si, Sj), Sj.cfp, Sj.cfm, hp, hm, kq);
+    else e_half = drive_scalar(P, Sj.cfp, kq, hp) + drive_scalar(P, Sj.cfm, -kq, hm);
+    charge_fixed(H, j, Sj.d0, nstep, base_f, P.L2, P.L, P.sD, Sj.cfp, max_iter, gf, hp, err);
+    charge_fixed(H, j, Sj.d0, nstep, base_f, P.L2, P.L, P.sD, Sj.cfm, max_iter, gf, hm, err);
+    if constexpr (MIXED) e_full = mixed_field(mixed_geo(X, Si, Sj), Sj.cfp, Sj.cfm, hp, hm, kq);
+    else e_full = drive_scalar(P, Sj.cfp, kq, hp) + drive_scalar(P, Sj.cfm, -kq, hm);
+}
+
+// Both stage times of a step (t_n + dt/2 and t_n + dt) for both charges of a
+// fixed source.  The usual lane takes small_charge on three stored rows, which hold
+// both stages' segments and are loaded together.  False: the segments are not all
+// stored, or a root leaves its segment or small_root's range, and the source goes
+// through the general solvers.  445 VALU instructions
+// per source and step, 688 with the general solvers' closed forms.
+template <bool DIFF>
+__device__ __forceinline__ bool drive_stages(const SmallK &c, const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double kq,
+                                             int64_t nstep, uint32_t &err, double &e_half, double &e_full)
+{
+    const double X[3] = {Si.ox, Si.oy, Si.oz};
+    const PairGeo P = pair_geo(X, Si, Sj);
+    const double w = P.L * (INV_C * H.inv_dt);
+    const double fh = floor(0.5 - w), ff = floor(1.0 - w);
+    const int kh = (int)fh;
+    bool ok = ff < 0.0;
+    {
+        const int64_t k = nstep + kh;
+        const double *p0 = H.ring + ((int64_t)(k & H.mask) * H.n + j) * 3;
+        const double *p1 = H.ring + ((int64_t)((k + 1) & H.mask) * H.n + j) * 3;
+        const double *p2 = H.ring + ((int64_t)((k + 2) & H.mask) * H.n + j) * 3;
+        double r0[3] = {p0[0], p0[1], p0[2]}, r1[3] = {p1[0], p1[1], p1[2]};
+        const double r2[3] = {p2[0], p2[1], p2[2]};
+        const bool next = ff != fh;                 // (by half a step: the same segment or the next)
+        double s0[3], s1[3];
+        for (int q = 0; q < 3; ++q) {
+            s0[q] = next ? r1[q] : r0[q];
+            s1[q] = next ? r2[q] : r1[q];
+        }
+        if (k < 0) {
+            // the static pre-history (d0, 0, 0), where the whole wave or none of it is for
+            // most of a run
+            const bool pre = k + (next ? 1 : 0) < 0;
+            for (int q = 0; q < 3; ++q) {
+                const double z = q == 0 ? Sj.d0 : 0.0;
+                r0[q] = r1[q] = z;
+                if (pre) s0[q] = s1[q] = z;
+            }
+        }
+        const double mu = P.sD * P.iL, muI = P.sI * P.iL;
+        const double uh = 0.5 - w - fh, uf = 1.0 - w - ff, kl = kq * (P.iL * P.iL);
+        double hp, hm, fp, fm;
+        ok = small_charge<DIFF>(c, mu, muI, w, uh, Sj.cfp, kl, P, r0, r1, hp) && ok;
+        ok = small_charge<DIFF>(c, mu, muI, w, uh, Sj.cfm, -kl, P, r0, r1, hm) && ok;
+        ok = small_charge<DIFF>(c, mu, muI, w, uf, Sj.cfp, kl, P, s0, s1, fp) && ok;
+        ok = small_charge<DIFF>(c, mu, muI, w, uf, Sj.cfm, -kl, P, s0, s1, fm) && ok;
+        e_half = hp + hm;
+        e_full = fp + fm;
+    }
+    if (nstep + kh >= 0 && -kh > H.mask) err |= ERR_HISTORY;
+    return ok;
+}
+
+// Both stage drives at target i of its instance's M other dipoles (fixed origins), one
+// source per lane of LANES and round, added to acc0, acc1.  The sources that
+// drive_stages does not take go through the general solvers after the others, 64
+// rounds at a time: in one loop the general solvers' registers would add to the usual
+// path's.
+template <int LANES, bool MIXED>
+__device__ __forceinline__ void target_stages(const SmallK &c, const Hist &H, const DipLds &Si,
+                                              const double *__restrict__ soa, int n_dip, int i0, int i, int M, int lane,
+                                              int64_t nstep, int max_iter, uint32_t &err, double &acc0, double &acc1)
+{
+    int j;
+    DipLds Sj;
+    double qj;
+    auto source = [&](int jj) {
+        j = jj < i ? jj : jj + 1;
+        Sj = soa_lds(soa, n_dip, (uint32_t)(i0 + j));
+        qj = soa_get(soa, n_dip, SF_Q, (uint32_t)(i0 + j));
+    };
+    for (int base = lane; base < M; base += 64 * LANES) {
+        const int end = min(M, base - lane + 64 * LANES);
+        uint64_t left = 0u;
+        int round = 0;
+        for (int jj = base; jj < end; jj += LANES, ++round) {
+            source(jj);
+            double eh, ef;
+            const bool ok = drive_stages<MIXED>(c, H, Si, Sj, j, qj * K_COUL, nstep, err, eh, ef);
+            if (!ok) left |= (uint64_t)1 << round;
+            acc0 += ok ? eh : 0.0;
+            acc1 += ok ? ef : 0.0;
+        }
+        while (left) {
+            const int r = __ffsll((unsigned long long)left) - 1;
+            left &= left - 1u;
+            source(base + r * LANES);
+            double eh, ef;
+            drive_stages_general<MIXED>(H, Si, Sj, j, qj * K_COUL, nstep, max_iter, err, eh, ef);
+            acc0 += eh;
+            acc1 += ef;
+        }
+    }
 }
 
 // Drive contribution of work unit w of source j: in FP64 one unit per charge
 // (w = 0: +q, 1: -q), in the mixed form one unit per source dipole.
 template <bool MOVING, bool MIXED>
-__device__ __forceinline__ double unit_drive(const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double qj,
+__device__ __forceinline__ double unit_drive(const SmallK &c, const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double qj,
                                              int w, int64_t nstep, double theta, int max_iter, uint32_t &err)
 {
     if constexpr (MIXED) {
-        return dipole_drive_mixed<MOVING>(H, Si, Sj, j, qj * K_COUL, nstep, theta, max_iter, err);
+        return dipole_drive_mixed<MOVING>(c, H, Si, Sj, j, qj * K_COUL, nstep, theta, max_iter, err);
     } else {
         const double cf = w ? Sj.cfm : Sj.cfp;
         const double kq = (w ? -qj : qj) * K_COUL;
-        return pair_drive<MOVING>(H, Si, Sj, j, cf, kq, nstep, theta, max_iter, err);
+        return pair_drive<MOVING>(c, H, Si, Sj, j, cf, kq, nstep, theta, max_iter, err);
     }
 }
 
@@ -700,17 +844,17 @@ template <bool MIXED> constexpr int units_per_source() { return MIXED ? 1 : 2; }
 // targets have many sources, so fewer, fuller units pay; the persistent kernel
 // keeps a lane per charge, which shortens the serial chain of small instances).
 template <bool MOVING, bool MIXED>
-__device__ __forceinline__ double source_drive(const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double qj,
+__device__ __forceinline__ double source_drive(const SmallK &c, const Hist &H, const DipLds &Si, const DipLds &Sj, int j, double qj,
                                                int64_t nstep, double theta, int max_iter, uint32_t &err)
 {
-    if constexpr (MIXED) return dipole_drive_mixed<MOVING>(H, Si, Sj, j, qj * K_COUL, nstep, theta, max_iter, err);
-    else return dipole_drive_fp64<MOVING>(H, Si, Sj, j, qj * K_COUL, nstep, theta, max_iter, err);
+    if constexpr (MIXED) return dipole_drive_mixed<MOVING>(c, H, Si, Sj, j, qj * K_COUL, nstep, theta, max_iter, err);
+    else return dipole_drive_fp64<MOVING>(c, H, Si, Sj, j, qj * K_COUL, nstep, theta, max_iter, err);
 }
 
 // Drive fields of all targets of the instance at stage times theta in
 // `thetas[0..nth)` (in steps after nstep), written to Eout[th * n + i].
 template <int BLOCK, bool MOVING, bool MIXED>
-__device__ void drive_all(const Hist &H, const DipLds *S, const double *qv, int n, int64_t nstep,
+__device__ void drive_all(const SmallK &c, const Hist &H, const DipLds *S, const double *qv, int n, int64_t nstep,
                           const double *thetas, int nth, double *Eout, int max_iter, uint32_t &err)
 {
     constexpr int U = units_per_source<MIXED>();
@@ -733,7 +877,7 @@ __device__ void drive_all(const Hist &H, const DipLds *S, const double *qv, int 
             for (int m = sub; m < M; m += Lg) {
                 const int jj = m / U, w = m % U;
                 const int j = jj < i ? jj : jj + 1;
-                acc += unit_drive<MOVING, MIXED>(H, S[i], S[j], j, qv[j], w, nstep, thetas[th], max_iter, err);
+                acc += unit_drive<MOVING, MIXED>(c, H, S[i], S[j], j, qv[j], w, nstep, thetas[th], max_iter, err);
             }
         }
         for (int off = 1; off < Lg; off <<= 1) acc += __shfl_xor(acc, off, 64);
@@ -786,6 +930,7 @@ __global__ __launch_bounds__(BLOCK) void lo_instances_kernel(const DipDev *__res
     if (tid == 0) s_err = 0u;
     __syncthreads();
 
+    const SmallK sk = small_k<true>();
     Hist H{ringp, n, ring - 1, dt, 1.0 / dt};
     uint32_t err = 0u;
     const int64_t ring3 = (int64_t)ring * n * 3;
@@ -807,7 +952,7 @@ __global__ __launch_bounds__(BLOCK) void lo_instances_kernel(const DipDev *__res
         // t = 0: drive from the static pre-history, then sample 0 = (d0, 0, d_ddot(0))
         {
             const double th0[1] = {0.0};
-            drive_all<BLOCK, MOVING, MIXED>(H, S, qv, n, 0, th0, 1, Ecur, max_iter, err);
+            drive_all<BLOCK, MOVING, MIXED>(sk, H, S, qv, n, 0, th0, 1, Ecur, max_iter, err);
         }
         __syncthreads();
         for (int i = tid; i < n; i += BLOCK) {
@@ -826,23 +971,15 @@ __global__ __launch_bounds__(BLOCK) void lo_instances_kernel(const DipDev *__res
 
     const double thetas[2] = {0.5, 1.0};
     for (int64_t nstep = n0; nstep < n0 + steps; ++nstep) {
-        drive_all<BLOCK, MOVING, MIXED>(H, S, qv, n, nstep, thetas, 2, Enew, max_iter, err);
+        drive_all<BLOCK, MOVING, MIXED>(sk, H, S, qv, n, nstep, thetas, 2, Enew, max_iter, err);
         __syncthreads();
         for (int i = tid; i < n; i += BLOCK) {
             const double w2 = Kc[i], g = Kc[n + i], f = Kc[2 * n + i], vfac = Kc[3 * n + i], ms = Kc[4 * n + i];
             const double *h = ringp + ((int64_t)(nstep & (ring - 1)) * n + i) * 3;
             const double Em = Enew[i], Ee = Enew[n + i], Ec = Ecur[i];
             const double y0 = h[0], y1 = h[1];
-            // classic RK4 on y = (d, d_dot), y' = (d_dot, f E_d(t) - gamma0 d_dot - w0^2 d)
-            const double k1d = y1, k1v = f * Ec - g * y1 - w2 * y0;
-            const double y0b = y0 + 0.5 * dt * k1d, y1b = y1 + 0.5 * dt * k1v;
-            const double k2d = y1b, k2v = f * Em - g * y1b - w2 * y0b;
-            const double y0c = y0 + 0.5 * dt * k2d, y1c = y1 + 0.5 * dt * k2v;
-            const double k3d = y1c, k3v = f * Em - g * y1c - w2 * y0c;
-            const double y0d = y0 + dt * k3d, y1d = y1 + dt * k3v;
-            const double k4d = y1d, k4v = f * Ee - g * y1d - w2 * y0d;
-            const double dn = y0 + dt / 6.0 * (k1d + 2.0 * k2d + 2.0 * k3d + k4d);
-            const double vn = y1 + dt / 6.0 * (k1v + 2.0 * k2v + 2.0 * k3v + k4v);
+            double dn, vn;
+            rk4_step(dev[i0 + i].rk, y0, y1, Ec, Em, Ee, dn, vn);
             const double an = f * Ee - g * vn - w2 * dn;
             double *hn = ringp + ((int64_t)((nstep + 1) & (ring - 1)) * n + i) * 3;
             hn[0] = dn;
@@ -881,23 +1018,51 @@ __global__ __launch_bounds__(BLOCK) void lo_instances_kernel(const DipDev *__res
 
 // ---------------------------------------------------------------------------
 // Instances of at most SMALL_MAX_N fixed dipoles, one wave each.  A step of such
-// an instance is a serial chain (drive, then RK4, then the next drive reads the
-// new sample), so its time is the instructions its one wave issues.  Here
-// every lane holds one work unit for the whole run (target i, stage theta,
-// source j, charge w: 2 n (n - 1) units in groups of Lg lanes, drive_all's FP64
-// layout), with the unit's separation and projections computed once, and lanes
-// 0..n-1 keep their dipole's state, constants and energy sums in registers.
-// The stage sums reach the RK4 lanes by cross-lane reads.
-//   FP64: the arithmetic of every drive, sum and RK4 step is that of
-//         lo_instances_kernel, in the same order, so both give the same bits.
-//   MIXED: the two lanes of a source's charges each solve their charge's
-//         retarded time, swap the stored states (d, d_dot, d_ddot) there, and
-//         the +q lane evaluates the source's mixed drive (mixed_field).  The
-//         general kernel solves both charges in one lane on one cached history
-//         segment; here each lane loads its own, which finds the same root (to
-//         its last bit but for roots within rounding of a segment end).
+// an instance is a serial chain (drive, stage sums, RK4, then the next drive reads the
+// new sample), so its time is that chain and the instructions its one wave
+// issues.  Every lane holds one work unit for the whole run: target i, source j,
+// charge w in groups of Lg lanes, stage t_n + dt/2 in lanes 0..31 and t_n + dt in
+// lanes 32..63.
+//  - The pair's geometry, the history segment its retarded time lies in relative to
+//    the current step, and the start u0 there are constants of the unit; the
+//    segment's first row is the row the lane loaded a step earlier, so one new row
+//    is read per step.  Roots come from small_root, without a branch between
+//    stored segments and the extrapolation past the newest sample (ext lanes: the
+//    segment's rows coincide and cdt, hdt2 add the Taylor terms).  A root that leaves
+//    its segment moves the lane's segment for good (twice per period at most, and
+//    only for separations within 1e-4 of a step boundary).
+//  - Steps that read before t = 0, and roots that small_root does not take, go
+//    through the general solvers.
+//  - Group sums by cross-lane moves (DPP, v_permlane32_swap), not LDS permutes; all
+//    lanes of group i integrate dipole i (rk4_step), with its state, constants and energy
+//    sums in registers, and share its stores: one LDS and one output store a step, each
+//    lane its own value and pointer.
+// 256 pairs x 4,000 steps, FP64: 2.56 ms (0.63 us per step: 171 VALU and 44 scalar
+// instructions, half of the time their dependent chain), 4.81 ms with the closed form and
+// two divergent paths, LDS permutes and the RK4 stages in sequence.
+//   MIXED: small_field's DIFF form; in the general solvers the +q lane evaluates the
+//   source's mixed drive from both charges' states.
 // ---------------------------------------------------------------------------
-constexpr int SMALL_MAX_N = 4;     // 2 n * Lg <= 64 lanes for n <= 4
+constexpr int SMALL_MAX_N = 4;     // n * Lg <= 32 lanes a stage for n <= 4
+
+// x from the lane at xor 1, 2 or 4 (sums over quads make 4 a mirror of 8 lanes)
+template <int CTRL> __device__ __forceinline__ double dpp_move(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141;
+
+// x of lanes 0..31 and of lanes 32..63, each in both halves
+__device__ __forceinline__ void both_halves(double x, double &low, double &high)
+{
+    const unsigned lo = (unsigned)__double2loint(x), hi = (unsigned)__double2hiint(x);
+    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    low = __hiloint2double((int)b[0], (int)a[0]);
+    high = __hiloint2double((int)b[1], (int)a[1]);
+}
 
 template <bool MIXED>
 __global__ __launch_bounds__(64) void lo_small_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ off,
@@ -936,6 +1101,7 @@ __global__ __launch_bounds__(64) void lo_small_kernel(const DipDev *__restrict__
     if (tid == 0) s_err = 0u;
     __syncthreads();
 
+    const SmallK sk = small_k<true>();
     Hist H{ringp, n, ring - 1, dt, 1.0 / dt};
     uint32_t err = 0u;
     int64_t n0 = 0;
@@ -953,7 +1119,7 @@ __global__ __launch_bounds__(64) void lo_small_kernel(const DipDev *__restrict__
     } else {
         {
             const double th0[1] = {0.0};
-            drive_all<BLOCK, false, MIXED>(H, S, qv, n, 0, th0, 1, Ecur, max_iter, err);
+            drive_all<BLOCK, false, MIXED>(sk, H, S, qv, n, 0, th0, 1, Ecur, max_iter, err);
         }
         __syncthreads();
         for (int i = tid; i < n; i += BLOCK) {
@@ -970,46 +1136,46 @@ __global__ __launch_bounds__(64) void lo_small_kernel(const DipDev *__restrict__
     }
     __syncthreads();
 
-    // this lane's work unit, as drive_all lays them out for two stage times
-    const int M = 2 * (n - 1), G = 2 * n;
-    int lg = 0;
+    // this lane's work unit
+    const int M = 2 * (n - 1);
+    int lg = 1;
     while ((1 << lg) < M) ++lg;
-    const int Lg = 1 << lg;
-    const int grp = tid >> lg, sub = tid & (Lg - 1);
-    const bool active = grp < G && sub < M;
-    int uj = 0;
-    double ucf = 0.0, ukq = 0.0, ud0 = 0.0, utheta = 0.0, ucfp = 0.0, ucfm = 0.0;
-    PairGeo P{0.0, 0.0, 0.0, 0.0, 0.0};
-    MixedGeo MG{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    const int th = tid >> 5, ui = (tid & 31) >> lg, sub = tid & ((1 << lg) - 1);
+    const bool live = ui < n, active = live && sub < M;
     const bool plus = (sub & 1) == 0;           // the +q lane of its source's pair
+    const int me = live ? ui : 0;
+    int uj = 0;
+    double ucf = 0.0, ukq = 0.0, ud0 = 0.0, utheta = 0.0;
+    PairGeo P{1.0, 1.0, 1.0, 0.0, 0.0, 0.0};
+    double mu = 0.0, muI = 0.0, kql2 = 0.0, w = 1.0, ci = 0.0, cb = 0.0, ce = 0.0;
     if (active) {
-        const int th = grp >= n ? 1 : 0, i = grp - th * n;
-        const int jj = sub >> 1, w = sub & 1;
-        uj = jj < i ? jj : jj + 1;
-        const DipLds Si = S[i], Sj = S[uj];
-        ucf = w ? Sj.cfm : Sj.cfp;
+        const int jj = sub >> 1, wq = sub & 1;
+        uj = jj < ui ? jj : jj + 1;
+        const DipLds Si = S[ui], Sj = S[uj];
+        ucf = wq ? Sj.cfm : Sj.cfp;
         ud0 = Sj.d0;
         utheta = th ? 1.0 : 0.5;
+        ukq = (wq ? -qv[uj] : qv[uj]) * K_COUL;
         const double X[3] = {Si.ox, Si.oy, Si.oz};
-        if constexpr (MIXED) {
-            ukq = qv[uj] * K_COUL;                  // the +q charge's (mixed_field)
-            ucfp = Sj.cfp;
-            ucfm = Sj.cfm;
-            MG = mixed_geo(X, Si, Sj);
-            P.L2 = MG.L2;
-            P.L = MG.L;
-            P.sD = MG.sD;
-        } else {
-            ukq = (w ? -qv[uj] : qv[uj]) * K_COUL;
-            P = pair_geo(X, Si, Sj);
-        }
+        P = pair_geo(X, Si, Sj);
+        mu = P.sD * P.iL;
+        muI = P.sI * P.iL;
+        kql2 = ukq * (P.iL * P.iL);
+        w = P.L * (INV_C * H.inv_dt);
+        ci = ucf * P.iL;
+        cb = ucf * INV_C;
+        ce = ucf * (INV_C * INV_C) * P.L;
     }
-    // lanes 0..n-1: dipole tid's state at the run's first step, constants and sums
-    const bool owner = tid < n;
-    const int me = owner ? tid : 0;
+    // the segment, relative to the current step: rows kf and kf + 1, or the newest
+    // row alone (kf = 0, extrapolation)
+    int kf = active ? (int)floor(utheta - w) : -1;
+    if (active && -kf > ring - 1) err |= ERR_HISTORY;     // (the ring covers every light time of the instance)
+    double u0 = utheta - w - (double)kf, cdt = 0.0, hdt2 = 0.0, quad = 0.0, mid = 0.5, half = 0.5 + 1e-9;
+    // group i's lanes: dipole i's state at the run's first step, constants and sums
     double y0 = 0.0, y1 = 0.0, y2 = 0.0, Ec = 0.0, wab = 0.0, wra = 0.0;
-    double w2 = 0.0, gm = 0.0, fq = 0.0, vfac = 0.0, ms = 0.0, eh = 0.0;
-    if (owner) {
+    double w2 = 0.0, gm = 0.0, fq = 0.0, vfac = 0.0, ms = 0.0, eh = 0.0, rk[9];
+    for (int q = 0; q < 9; ++q) rk[q] = 0.0;
+    if (live) {
         const DipDev &D = dev[i0 + me];
         w2 = D.omega0 * D.omega0;
         gm = D.gamma0;
@@ -1017,6 +1183,7 @@ __global__ __launch_bounds__(64) void lo_small_kernel(const DipDev *__restrict__
         vfac = D.vfac;
         ms = D.mspeed;
         eh = D.ehalf;
+        for (int q = 0; q < 9; ++q) rk[q] = D.rk[q];
         const double *h = ringp + ((int64_t)(n0 & (ring - 1)) * n + me) * 3;
         y0 = h[0];
         y1 = h[1];
@@ -1025,60 +1192,154 @@ __global__ __launch_bounds__(64) void lo_small_kernel(const DipDev *__restrict__
         wab = Wab[me];
         wra = Wra[me];
     }
-    const int src_mid = me << lg, src_end = (n + me) << lg;
-    const double hdt = 0.5 * dt, dt6 = dt / 6.0, hdtl = 0.5 * dt * K_LARMOR;
+    const bool owner = live && th == 0 && sub == 0;
+    // what this lane stores of its dipole: role 0 d, 1 d_dot, 2 the energy (and d_ddot
+    // into the ring), 3 E_d; roles 0 and 1 the energy sums when they are asked for
+    const int role = !live ? 4 : (th << lg) + sub;
+    double *po = role == 0 ? out.d : role == 1 ? out.v : role == 2 ? out.E : role == 3 ? out.Ed : nullptr;
+    double *pw = role == 0 ? out.wabs : role == 1 ? out.wrad : nullptr;
+    const bool sums = out.wabs || out.wrad;
+    const int64_t orow = out.n_dip + i0 + me;    // row 1's entry
+    if (po) po += orow;
+    if (pw) pw += orow;
+    const int ring3 = ring * n * 3;
+    const double hdt = 0.5 * dt, hdtl = 0.5 * dt * K_LARMOR;
+    const double vlim = max_vel > 0.0 ? max_vel : __builtin_huge_val();
     const uint32_t stop_bits = ERR_NONFINITE | ERR_VELOCITY | ERR_HISTORY;
 
     // the steps, with 32-bit step indices when the run's last step fits
     auto run_steps = [&](auto index_type) {
       using I = decltype(index_type);
+      double g0[3] = {0.0, 0.0, 0.0}, g1[3] = {0.0, 0.0, 0.0};   // the segment's rows (d, d_dot, d_ddot)
+      bool rows = false;                           // g0, g1 and nx are this step's
+      unsigned nx = 0;                             // ring index of the row the next step adds
+      unsigned wx = (unsigned)((((I)n0 + 1) & (I)(ring - 1)) * n + me) * 3u + (role < 3 ? role : 0);
+      I togo = (I)(out.stride < (int64_t)std::numeric_limits<I>::max() ? out.stride : (int64_t)std::numeric_limits<I>::max());
+      const I stride = togo;
+      auto row_index = [&](I k) { return (unsigned)((k & (I)(ring - 1)) * n + uj) * 3u; };
+      // index of the row one step later than that at index x
+      auto later = [&](unsigned x) {
+          const unsigned y = x + 3u * (unsigned)n;
+          return min(y, y - (unsigned)ring3);      // (unsigned: y below the ring's end stays)
+      };
+      auto load_rows = [&](I nstep) {
+          const I k = nstep + kf;
+          const unsigned a = row_index(k), b = row_index(kf < 0 ? k + 1 : k);
+          const bool pre = k < 0;                  // static before t = 0
+          for (int q = 0; q < 3; ++q) {
+              g0[q] = pre ? (q == 0 ? ud0 : 0.0) : ringp[a + q];
+              g1[q] = pre ? (q == 0 ? ud0 : 0.0) : ringp[b + q];
+          }
+          nx = later(b);
+          cdt = kf < 0 ? 0.0 : dt;
+          hdt2 = kf < 0 ? 0.0 : 0.5 * dt * dt;
+          quad = kf < 0 ? 0.0 : 1.0;
+          // roots of this segment: u in [0, 1], from 0 in the extrapolation, up to t = 0
+          // in the pre-history (a root within rounding of an end belongs to either side)
+          mid = pre ? (double)-k - 1000.0 : kf < 0 ? 0.5 : 1000.0;
+          half = (pre || kf >= 0 ? 1000.0 : 0.5) + 1e-9;
+      };
       for (I nstep = (I)n0; nstep < (I)(n0 + steps); ++nstep) {
         double acc = 0.0;
-        if constexpr (MIXED) {
-            double h[3] = {0.0, 0.0, 0.0};
-            if (active) {
-                SegT<I> g;
-                g.k = seg_none<I>();
-                charge_fixed(H, uj, ud0, nstep, (double)nstep + utheta, P.L2, P.L, P.sD, ucf, max_iter, g, h, err);
+        bool done = false;
+        for (int hop = 0; hop < 4; ++hop) {
+            if (!rows) load_rows(nstep);
+            rows = true;
+            SmallRoot r;
+            small_root<true>(sk, mu, w, u0, ci * g0[0], ci * fma(g0[1], cdt, g1[0] - g0[0]), ci * (g0[2] * hdt2), quad,
+                             r);
+            const double b = cb * fma(r.u, fma(g0[2], cdt, g1[1] - g0[1]), g0[1]);
+            const double e = ce * fma(r.u, g1[2] - g0[2], g0[2]);
+            acc = kql2 * small_field<MIXED>(sk, mu, muI, P.pij, r, b, e);
+            const bool ok = fma(fabs(b), sk.lz, r.out) <= 1.0 && fabs(r.u - mid) <= half;
+            if (!__any(active && !ok)) {
+                done = true;
+                break;
             }
-            double ho[3];
-            for (int q = 0; q < 3; ++q) ho[q] = __shfl_xor(h[q], 1, 64);
-            if (active && plus) acc += mixed_field(MG, ucfp, ucfm, h, ho, ukq);
+            // not this segment's root (the lane moves for good), or out of range
+            rows = false;
+            if (__any(active && !(fma(fabs(b), sk.lz, r.out) <= 1.0))) break;
+            const int move = !active || ok ? 0 : r.u < mid ? -1 : 1;
+            if (__any(kf + move > 0 || -(kf + move) > ring - 1)) break;   // (no such segment: the general solvers)
+            kf += move;
+            u0 -= (double)move;
+        }
+        if (!__any(active && !done)) {
+            if (!active) acc = 0.0;
         } else {
-            if (active) acc += fixed_drive(H, P, uj, ud0, ucf, ukq, nstep, (double)nstep + utheta, max_iter, err);
+            // offsets or speeds beyond small_root's range
+            rows = false;
+            acc = 0.0;
+            if constexpr (MIXED) {
+                double h[3] = {0.0, 0.0, 0.0};
+                if (active) {
+                    SegT<I> g;
+                    g.k = seg_none<I>();
+                    charge_fixed(H, uj, ud0, nstep, (double)nstep + utheta, P.L2, P.L, P.sD, ucf, max_iter, g, h, err);
+                }
+                double ho[3];
+                for (int q = 0; q < 3; ++q) ho[q] = dpp_move<DPP_XOR1>(h[q]);
+                if (active && plus) {
+                    const DipLds Si = S[ui], Sj = S[uj];
+                    const double X[3] = {Si.ox, Si.oy, Si.oz};
+                    acc = mixed_field(mixed_geo(X, Si, Sj), Sj.cfp, Sj.cfm, h, ho, ukq);   // (the +q charge's)
+                }
+            } else {
+                if (active) acc = fixed_drive(H, P, uj, ud0, ucf, ukq, nstep, (double)nstep + utheta, max_iter, err);
+            }
         }
-        for (int o = 1; o < Lg; o <<= 1) acc += __shfl_xor(acc, o, 64);
-        const double Em = __shfl(acc, src_mid, 64), Ee = __shfl(acc, src_end, 64);
-        if (owner) {
-            // classic RK4 on y = (d, d_dot), as lo_instances_kernel
-            const double k1d = y1, k1v = fq * Ec - gm * y1 - w2 * y0;
-            const double y0b = y0 + hdt * k1d, y1b = y1 + hdt * k1v;
-            const double k2d = y1b, k2v = fq * Em - gm * y1b - w2 * y0b;
-            const double y0c = y0 + hdt * k2d, y1c = y1 + hdt * k2v;
-            const double k3d = y1c, k3v = fq * Em - gm * y1c - w2 * y0c;
-            const double y0d = y0 + dt * k3d, y1d = y1 + dt * k3v;
-            const double k4d = y1d, k4v = fq * Ee - gm * y1d - w2 * y0d;
-            const double dn = y0 + dt6 * (k1d + 2.0 * k2d + 2.0 * k3d + k4d);
-            const double vn = y1 + dt6 * (k1v + 2.0 * k2v + 2.0 * k3v + k4v);
-            const double an = fq * Ee - gm * vn - w2 * dn;
-            double *hn = ringp + ((I)((nstep + 1) & (ring - 1)) * n + me) * 3;
-            hn[0] = dn;
-            hn[1] = vn;
-            hn[2] = an;
-            if (!(isfinite(dn) && isfinite(vn) && isfinite(an))) err |= ERR_NONFINITE;
-            if (max_vel > 0.0 && ms + vfac * fabs(vn) > max_vel) err |= ERR_VELOCITY;
-            wab = wab + hdt * (y1 * Ec + vn * Ee);
-            wra = wra + hdtl * (y2 * y2 + an * an);
-            const int64_t row = out_row((int64_t)nstep + 1 - n0, out.stride);
-            if (row >= 0) put_row(out, row, i0 + me, dn, vn, run_energy(w2, eh, dn, vn), Ee, wab, wra);
-            y0 = dn;
-            y1 = vn;
-            y2 = an;
-            Ec = Ee;
-        }
+        acc += dpp_move<DPP_XOR1>(acc);
+        if (lg > 1) acc += dpp_move<DPP_XOR2>(acc);
+        if (lg > 2) acc += dpp_move<DPP_MIRROR8>(acc);
+        double Em, Ee, dn, vn;
+        both_halves(acc, Em, Ee);
+        rk4_step(rk, y0, y1, Ec, Em, Ee, dn, vn);
+        const double an = fq * Ee - gm * vn - w2 * dn;
+        const double dv = role == 0 ? dn : vn;
+        if (role < 3) ringp[wx] = role == 2 ? an : dv;
+        wx = later(wx);
         // the new samples are read by other lanes of this wave in the next step
         __syncthreads();
-        if (__any((err & stop_bits) != 0u)) break;
+        if (rows) {
+            if (__any(active && kf < 0 && nstep + kf < 0)) {
+                rows = false;                      // (the pre-history ends: both rows anew)
+            } else {
+                // a stored segment's second row becomes its first
+                const double a = ringp[nx], b = ringp[nx + 1], c = ringp[nx + 2];
+                g0[0] = kf < 0 ? g1[0] : a;
+                g0[1] = kf < 0 ? g1[1] : b;
+                g0[2] = kf < 0 ? g1[2] : c;
+                g1[0] = a;
+                g1[1] = b;
+                g1[2] = c;
+                nx = later(nx);
+            }
+        }
+        wab = wab + hdt * (y1 * Ec + vn * Ee);
+        wra = wra + hdtl * (y2 * y2 + an * an);
+        if (--togo == 0) {
+            togo = stride;
+            const double en = run_energy(w2, eh, dn, vn);
+            if (po) {
+                *po = role < 2 ? dv : role == 2 ? en : Ee;
+                po += out.n_dip;
+            }
+            if (sums && pw) {
+                *pw = role == 0 ? wab : wra;
+                pw += out.n_dip;
+            }
+        }
+        y0 = dn;
+        y1 = vn;
+        y2 = an;
+        Ec = Ee;
+        // d_ddot is not finite whenever d, d_dot or the drive is not
+        const bool nf = !isfinite(an), fast = ms + vfac * fabs(vn) > vlim;
+        if (__any(nf || fast || (err & stop_bits) != 0u)) {
+            if (nf) err |= ERR_NONFINITE;
+            if (fast) err |= ERR_VELOCITY;
+            break;
+        }
       }
     };
     if (n0 + steps < (int64_t)INT32_MAX) run_steps(int{});
@@ -1144,10 +1405,10 @@ __global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict
     // A launch with few targets (`wide`: at most one workgroup per SIMD) is a
     // latency chain, and the shortest chain that fits the block wins: in FP64
     // one charge per lane (4 drives' worth of lanes per source), else one source
-    // per (stage, lane); the mixed form always takes one source per (stage, lane)
-    // there.
-    const int layout = MIXED ? (wide ? 1 : 0)
-                             : (wide && 2 * nth * M <= BLOCK ? 2 : (wide && nth * M <= BLOCK ? 1 : 0));
+    // per (stage, lane); in the mixed form one source per (stage, lane).  Sources that
+    // do not fit so take both stages in a lane (900 dipoles, mixed: 38.9 us per step
+    // with a lane per stage).
+    const int layout = !wide ? 0 : (!MIXED && 2 * nth * M <= BLOCK) ? 2 : (nth * M <= BLOCK) ? 1 : 0;
     const int units = layout == 2 ? 2 * nth * M : (layout == 1 ? nth * M : M);
     // the target's own state (only this workgroup writes it, and only at its
     // end): when the last lane has no pair work it reads the state into LDS
@@ -1164,28 +1425,20 @@ __global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict
         own[4] = W[2 * gi];
         own[5] = W[2 * gi + 1];
     }
+    const SmallK c = small_k<true>();
     double acc0 = 0.0, acc1 = 0.0;                   // stage t_n + dt/2 (or t = 0), stage t_n + dt
     if (layout == 0) {
-        // a lane takes one source for both stage times, which share its
-        // constants and separation (and often the history segment)
-        for (int jj = tid; jj < M; jj += BLOCK) {
-            const int j = jj < i ? jj : jj + 1;
-            const DipLds Sj = soa_lds(soa, out.n_dip, (uint32_t)(i0 + j));
-            const double qj = soa_get(soa, out.n_dip, SF_Q, (uint32_t)(i0 + j));
-            if constexpr (!MOVING) {
-                if (!init) {
-                    double eh, ef;
-                    if constexpr (MIXED)
-                        dipole_drive_mixed_stages(H, Si, Sj, j, qj * K_COUL, nstep, max_iter, err, eh, ef);
-                    else
-                        dipole_drive_fp64_stages(H, Si, Sj, j, qj * K_COUL, nstep, max_iter, err, eh, ef);
-                    acc0 += eh;
-                    acc1 += ef;
-                    continue;
-                }
+        // a lane takes one source for both stage times
+        if (MOVING || init) {
+            for (int jj = tid; jj < M; jj += BLOCK) {
+                const int j = jj < i ? jj : jj + 1;
+                const DipLds Sj = soa_lds(soa, out.n_dip, (uint32_t)(i0 + j));
+                const double qj = soa_get(soa, out.n_dip, SF_Q, (uint32_t)(i0 + j));
+                acc0 += source_drive<MOVING, MIXED>(c, H, Si, Sj, j, qj, nstep, init ? 0.0 : 0.5, max_iter, err);
+                if (!init) acc1 += source_drive<MOVING, MIXED>(c, H, Si, Sj, j, qj, nstep, 1.0, max_iter, err);
             }
-            acc0 += source_drive<MOVING, MIXED>(H, Si, Sj, j, qj, nstep, init ? 0.0 : 0.5, max_iter, err);
-            if (!init) acc1 += source_drive<MOVING, MIXED>(H, Si, Sj, j, qj, nstep, 1.0, max_iter, err);
+        } else {
+            target_stages<BLOCK, MIXED>(c, H, Si, soa, out.n_dip, i0, i, M, tid, nstep, max_iter, err, acc0, acc1);
         }
     } else if (layout == 2) {
         // FP64, few targets: a lane per (stage, source, charge)
@@ -1197,7 +1450,7 @@ __global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict
             const double qj = soa_get(soa, out.n_dip, SF_Q, (uint32_t)(i0 + j));
             const double cf = w ? Sj.cfm : Sj.cfp, kq = (w ? -qj : qj) * K_COUL;
             const double theta = init ? 0.0 : (th ? 1.0 : 0.5);
-            const double e = pair_drive<MOVING>(H, Si, Sj, j, cf, kq, nstep, theta, max_iter, err);
+            const double e = pair_drive<MOVING>(c, H, Si, Sj, j, cf, kq, nstep, theta, max_iter, err);
             if (th) acc1 += e; else acc0 += e;
         }
     } else {
@@ -1208,7 +1461,7 @@ __global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict
             const DipLds Sj = soa_lds(soa, out.n_dip, (uint32_t)(i0 + j));
             const double qj = soa_get(soa, out.n_dip, SF_Q, (uint32_t)(i0 + j));
             const double theta = init ? 0.0 : (th ? 1.0 : 0.5);
-            const double e = source_drive<MOVING, MIXED>(H, Si, Sj, j, qj, nstep, theta, max_iter, err);
+            const double e = source_drive<MOVING, MIXED>(c, H, Si, Sj, j, qj, nstep, theta, max_iter, err);
             if (th) acc1 += e; else acc0 += e;
         }
     }
@@ -1216,9 +1469,11 @@ __global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict
     // early read, so that the loads are in flight during the block sums (read
     // after the barrier they added one memory round trip to every workgroup)
     double st[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double om = 0.0, gm = 0.0, fq = 0.0, dd0 = 0.0, eh = 0.0, ms = 0.0, vf = 0.0;
+    double om = 0.0, gm = 0.0, fq = 0.0, dd0 = 0.0, eh = 0.0, ms = 0.0, vf = 0.0, rk[9];
+    for (int q = 0; q < 9; ++q) rk[q] = 0.0;
     if (tid == 0) {
         const DipDev &D = dev[gi];
+        for (int q = 0; q < 9; ++q) rk[q] = D.rk[q];
         om = D.omega0;
         gm = D.gamma0;
         fq = D.f;
@@ -1282,15 +1537,8 @@ __global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict
                 W0 = st[4];
                 W1 = st[5];
             }
-            const double k1d = y1, k1v = f * Ec - g * y1 - w2 * y0;
-            const double y0b = y0 + 0.5 * dt * k1d, y1b = y1 + 0.5 * dt * k1v;
-            const double k2d = y1b, k2v = f * Em - g * y1b - w2 * y0b;
-            const double y0c = y0 + 0.5 * dt * k2d, y1c = y1 + 0.5 * dt * k2v;
-            const double k3d = y1c, k3v = f * Em - g * y1c - w2 * y0c;
-            const double y0d = y0 + dt * k3d, y1d = y1 + dt * k3v;
-            const double k4d = y1d, k4v = f * Ee - g * y1d - w2 * y0d;
-            const double dn = y0 + dt / 6.0 * (k1d + 2.0 * k2d + 2.0 * k3d + k4d);
-            const double vn = y1 + dt / 6.0 * (k1v + 2.0 * k2v + 2.0 * k3v + k4v);
+            double dn, vn;
+            rk4_step(rk, y0, y1, Ec, Em, Ee, dn, vn);
             const double an = f * Ee - g * vn - w2 * dn;
             double *hn = rp + ((int64_t)((nstep + 1) & (ring_depth - 1)) * n + i) * 3;
             hn[0] = dn;
@@ -1308,6 +1556,71 @@ __global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict
             const int64_t row = out_row(rel, out.stride);
             if (row >= 0) put_row(out, row, gi, dn, vn, run_energy(w2, eh, dn, vn), Ee, wa, wr);
         }
+    }
+    if (err) atomicOr(d_err, err);
+}
+
+// Launches with many targets of fixed dipoles: one wave per target, four to a
+// workgroup.  Such a launch is bound by VALU issue as far as memory latency is hidden:
+// a wave's start (its target's constants, three dependent loads) and end (the
+// target's state, the lane sums, the step) are a chain of several microseconds, which
+// one wave per target pays once for its ceil((n - 1) / 64) rounds, where a workgroup per
+// target paid it in four waves for a quarter of the rounds each.  64 clusters of
+// 12,530 dipoles, per step: 147 us, 156 with a workgroup per
+// target (both on drive_stages; 170 before it).  What bounds it now is half VALU issue
+// (81 us) and half the row gathers (six loads of 64 lines per round).
+template <bool MIXED>
+__global__ __launch_bounds__(256, 4) void lo_wave_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
+                                                         const int32_t *__restrict__ tgt_lo,
+                                                         const int32_t *__restrict__ tgt_n,
+                                                         const int64_t *__restrict__ ring_base, int n_tgt,
+                                                         double *__restrict__ ring, double *__restrict__ Ecur,
+                                                         double *__restrict__ W, const int64_t *__restrict__ step_ctr,
+                                                         int kstep, int ring_depth, double dt, double max_vel,
+                                                         int max_iter, RunOut out, const double *__restrict__ soa,
+                                                         uint32_t *__restrict__ d_err)
+{
+    const int lane = threadIdx.x & 63;
+    const int b = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
+    if (b >= n_tgt) return;
+    const int gi = tgt[b], i0 = tgt_lo[b], n = tgt_n[b], i = gi - i0;
+    const int64_t nstep = *step_ctr + kstep;
+    double *rp = ring + ring_base[b];
+    const Hist H{rp, n, ring_depth - 1, dt, 1.0 / dt};
+    const DipLds Si = dip_lds(dev[gi]);
+    const SmallK c = small_k<false>();
+    uint32_t err = 0u;
+    double acc0 = 0.0, acc1 = 0.0;
+    target_stages<64, MIXED>(c, H, Si, soa, out.n_dip, i0, i, n - 1, lane, nstep, max_iter, err, acc0, acc1);
+    // the target's constants and state, in flight during the sums
+    const DipDev &D = dev[gi];
+    double rk[9];
+    for (int q = 0; q < 9; ++q) rk[q] = D.rk[q];
+    const double w2 = D.omega0 * D.omega0, g = D.gamma0, f = D.f, eh = D.ehalf, ms = D.mspeed, vf = D.vfac;
+    const double *h = rp + ((int64_t)(nstep & (ring_depth - 1)) * n + i) * 3;
+    const double y0 = h[0], y1 = h[1], a0 = h[2], Ec = Ecur[gi], W0 = W[2 * gi], W1 = W[2 * gi + 1];
+    for (int o = 32; o > 0; o >>= 1) {
+        acc0 += __shfl_xor(acc0, o, 64);
+        acc1 += __shfl_xor(acc1, o, 64);
+    }
+    if (lane == 0) {
+        double dn, vn;
+        rk4_step(rk, y0, y1, Ec, acc0, acc1, dn, vn);
+        const double an = f * acc1 - g * vn - w2 * dn;
+        double *hn = rp + ((int64_t)((nstep + 1) & (ring_depth - 1)) * n + i) * 3;
+        hn[0] = dn;
+        hn[1] = vn;
+        hn[2] = an;
+        Ecur[gi] = acc1;
+        if (!(isfinite(dn) && isfinite(vn) && isfinite(an))) err |= ERR_NONFINITE;
+        if (max_vel > 0.0 && ms + vf * fabs(vn) > max_vel) err |= ERR_VELOCITY;
+        // energy bookkeeping (Sec. 2.5), trapezoid rule over the step
+        const double wa = W0 + 0.5 * dt * (y1 * Ec + vn * acc1);
+        const double wr = W1 + 0.5 * dt * K_LARMOR * (a0 * a0 + an * an);
+        W[2 * gi] = wa;
+        W[2 * gi + 1] = wr;
+        const int64_t row = out_row(nstep + 1 - step_ctr[1], out.stride);
+        if (row >= 0) put_row(out, row, gi, dn, vn, run_energy(w2, eh, dn, vn), acc1, wa, wr);
     }
     if (err) atomicOr(d_err, err);
 }
@@ -1397,6 +1710,17 @@ hipError_t launch_dipole_steps(const DipDev *d_dev, const int32_t *d_tgt, const 
     const int wide = n_tgt <= 1024 ? 1 : 0;
     const double *soa = dip_soa(const_cast<DipDev *>(d_dev), out.n_dip);
     auto step = [&](hipStream_t q, int k, int init) {
+        if (!wide && !init && !moving) {
+            const dim3 g4((unsigned)((n_tgt + 3) / 4));
+            if (mixed)
+                hipLaunchKernelGGL(lo_wave_kernel<true>, g4, block, 0, q, d_dev, d_tgt, d_tgt_lo, d_tgt_n, d_ring_base,
+                                   n_tgt, d_ring, d_Ecur, d_W, d_step, k, ring, dt, max_vel, max_iter, out, soa, d_err);
+            else
+                hipLaunchKernelGGL(lo_wave_kernel<false>, g4, block, 0, q, d_dev, d_tgt, d_tgt_lo, d_tgt_n,
+                                   d_ring_base, n_tgt, d_ring, d_Ecur, d_W, d_step, k, ring, dt, max_vel, max_iter, out,
+                                   soa, d_err);
+            return;
+        }
         with_flags(moving, mixed, [&](auto mv, auto mx) {
             hipLaunchKernelGGL((lo_step_kernel<B, decltype(mv)::value, decltype(mx)::value>), grid, block, 0, q,
                                d_dev, d_tgt, d_tgt_lo, d_tgt_n, d_ring_base, d_ring, d_Ecur, d_W, d_step, k, ring, dt,
@@ -1466,6 +1790,8 @@ static hipError_t launch_lo(bool ring_lds, bool moving, bool mixed, dim3 grid, s
     return hipGetLastError();
 }
 
+int dipole_small_max_n() { return SMALL_MAX_N; }
+
 hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, const int32_t *d_list, int n_list,
                                    int max_n, bool ring_lds, const int64_t *d_ring_off, double *d_ring_global,
                                    int ring, int64_t steps, double dt, double max_vel, int max_iter,
@@ -1475,7 +1801,7 @@ hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, co
     if (n_list <= 0) return hipSuccess;
     const size_t shmem = (size_t)ring_lds_bytes(max_n, ring_lds ? ring : 0);
     const dim3 grid((unsigned)n_list);
-    if (ring_lds && !moving && max_n <= SMALL_MAX_N) {
+    if (ring_lds && !moving && max_n <= dipole_small_max_n()) {
         if (mixed)
             hipLaunchKernelGGL(lo_small_kernel<true>, grid, dim3(64), shmem, s, d_dev, d_off, d_list, ring, steps, dt,
                                max_vel, max_iter, out, d_state, resume ? 1 : 0, d_err);

@@ -24,6 +24,7 @@ struct DipDev {
     double mw, mph;
     double mspeed;   // largest origin speed, mw |mamp|
     double ehalf;    // 0.5 / f, the factor of the energy (run_energy)
+    double rk[9];    // one RK4 step's increments of d and d_dot (rk4_step)
 };
 
 // Per-dipole constants of the instance, staged in LDS.
@@ -202,6 +203,154 @@ constexpr double K_LARMOR = 1.0 / (6.0 * PI * EPS0 * C_LIGHT * C_LIGHT * C_LIGHT
 __device__ __forceinline__ double run_energy(double w2, double ehalf, double d, double v)
 {
     return fma(w2 * d, d, v * v) * ehalf;
+}
+
+// One classic RK4 step of Eq. (LO_equation), y' = (d_dot, f E_d(t) - gamma0 d_dot -
+// omega0^2 d) with the drives Ec, Em, Ee at t, t + dt/2, t + dt, is linear in the state
+// and the drives.  c holds the coefficients of its increments, of d (on d, d_dot,
+// Ec, Em) and of d_dot (on d, d_dot, Ec, Em, Ee).  Increments, not the propagator: the
+// leading 1 of the propagator would round away the low bits of the rest the same
+// way at every step.  Everything but the terms of Em and Ee is known before the
+// drives are, so two dependent operations follow the drives here, against about 20
+// through the stages.
+__device__ __forceinline__ void rk4_stages(double w2, double g, double f, double dt, double y0, double y1, double Ec,
+                                           double Em, double Ee, double &dd, double &dv)
+{
+    const double k1d = y1, k1v = f * Ec - g * y1 - w2 * y0;
+    const double y0b = y0 + 0.5 * dt * k1d, y1b = y1 + 0.5 * dt * k1v;
+    const double k2d = y1b, k2v = f * Em - g * y1b - w2 * y0b;
+    const double y0c = y0 + 0.5 * dt * k2d, y1c = y1 + 0.5 * dt * k2v;
+    const double k3d = y1c, k3v = f * Em - g * y1c - w2 * y0c;
+    const double y0d = y0 + dt * k3d, y1d = y1 + dt * k3v;
+    const double k4d = y1d, k4v = f * Ee - g * y1d - w2 * y0d;
+    dd = dt / 6.0 * (k1d + 2.0 * k2d + 2.0 * k3d + k4d);
+    dv = dt / 6.0 * (k1v + 2.0 * k2v + 2.0 * k3v + k4v);
+}
+
+__device__ __forceinline__ void rk4_coefs(double w2, double g, double f, double dt, double c[9])
+{
+    double skip;
+    rk4_stages(w2, g, f, dt, 1.0, 0.0, 0.0, 0.0, 0.0, c[0], c[4]);
+    rk4_stages(w2, g, f, dt, 0.0, 1.0, 0.0, 0.0, 0.0, c[1], c[5]);
+    rk4_stages(w2, g, f, dt, 0.0, 0.0, 1.0, 0.0, 0.0, c[2], c[6]);
+    rk4_stages(w2, g, f, dt, 0.0, 0.0, 0.0, 1.0, 0.0, c[3], c[7]);
+    rk4_stages(w2, g, f, dt, 0.0, 0.0, 0.0, 0.0, 1.0, skip, c[8]);
+}
+
+__device__ __forceinline__ void rk4_step(const double c[9], double y0, double y1, double Ec, double Em, double Ee,
+                                         double &dn, double &vn)
+{
+    const double pd = fma(c[2], Ec, fma(c[1], y1, c[0] * y0));
+    const double pv = fma(c[6], Ec, fma(c[5], y1, c[4] * y0));
+    dn = y0 + fma(c[3], Em, pd);
+    vn = y1 + fma(c[8], Ee, fma(c[7], Em, pv));
+}
+
+// Charges close to their dipole's origin.  With lengths in units of the separation
+// L of the target from the source's origin and mu = cos of the angle between them and
+// the source's axis, a charge at offset x has the distance D = sqrt(1 + y), y = x (x -
+// 2 mu), and the offset is a known function of the retarded step, x(u) = X0 + u (X1 + u
+// X2): linear within a history segment (X2 = 0), quadratic past the newest sample.
+// The retarded condition D = 1 + q, u = u0 - w q (w = L / (c dt); u0: the step at q = 0)
+// is solved by expanding about q = 0, where everything but x is a constant of the
+// pair: q0 = sqrt(1 + y) - 1 and 1 / D by their series in y (through y^5: below 2e-17
+// at |y| <= 2^-9), the slope zeta = dq/dq = -w x' (x - mu) / D by its geometric series, and
+// for a quadratic x (quad = 1; 0 gives a linear one the bits of QUAD = false) the
+// second-order term p q0^2.
+// So the root takes no square root and no division: 35 instructions, against 70
+// with two refined v_rsq_f64 and a reciprocal for the closed form on a segment and
+// the distance from it.  The range is |x| 2^10 + |zeta| 2^13 + |q - q0| 2^27 + |p q0^2|
+// 2^40 <= 1, within which the terms left out stay below 2^-53 (an offset of 1e-12 m
+// is inside from about 1 nm, a speed of 2e-6 c always); beyond it (r.out > 1, or not a
+// number) the caller takes the general solvers.
+struct SmallRoot {
+    double u, x, q, iD;    // step, offset, distance 1 + q (units of L) and its reciprocal at the root
+    double out;            // above 1: outside the range
+};
+
+// The series' coefficients, held in registers over the caller's loop (opaque to the
+// compiler, which would rebuild each 64-bit constant by two scalar moves next to its
+// use): VGPRs for a kernel of one wave per SIMD, where each scalar move is an issue
+// slot of the wave's chain, scalar registers otherwise.
+struct SmallK {
+    double q1, q2, q3, q4;        // sqrt(1 + y) - 1 = y (1/2 + q1 y + ...)
+    double i1, i2, i3, i4;        // 1 / sqrt(1 + y) - 1 = y (-1/2 + i1 y + ...)
+    double lx, lz, ld, lp;        // reciprocal limits of |x|, |zeta| and |b|, |q - q0|, |p q0^2|
+    double k0, k1, k2, k3;        // 1 / kappa^3 - 1 = z (k0 + k1 z + ...)
+};
+template <bool VGPR> __device__ __forceinline__ void hold(double &k)
+{
+    if constexpr (VGPR) asm volatile("" : "+v"(k));
+    else asm volatile("" : "+s"(k));
+}
+template <bool VGPR> __device__ __forceinline__ SmallK small_k()
+{
+    SmallK c{-1.0 / 8.0, 1.0 / 16.0, -5.0 / 128.0, 7.0 / 256.0, 3.0 / 8.0, -5.0 / 16.0, 35.0 / 128.0, -63.0 / 256.0,
+             0x1p10, 0x1p13, 0x1p27, 0x1p40, 3.0, 6.0, 10.0, 15.0};
+    hold<VGPR>(c.q1); hold<VGPR>(c.q2); hold<VGPR>(c.q3); hold<VGPR>(c.q4);
+    hold<VGPR>(c.i1); hold<VGPR>(c.i2); hold<VGPR>(c.i3); hold<VGPR>(c.i4);
+    hold<VGPR>(c.lx); hold<VGPR>(c.lz); hold<VGPR>(c.ld); hold<VGPR>(c.lp);
+    hold<VGPR>(c.k0); hold<VGPR>(c.k1); hold<VGPR>(c.k2); hold<VGPR>(c.k3);
+    return c;
+}
+
+template <bool QUAD>
+__device__ __forceinline__ void small_root(const SmallK &c, double mu, double w, double u0, double X0, double X1,
+                                           double X2, double quad, SmallRoot &r)
+{
+    double x, xs;
+    if constexpr (QUAD) {
+        x = fma(u0, fma(u0, X2, X1), X0);
+        xs = fma(u0 + u0, X2, X1);
+    } else {
+        x = fma(u0, X1, X0);
+        xs = X1;
+    }
+    const double y = x * fma(-2.0, mu, x), y2 = y * y;
+    const double q0 = y * fma(y2, fma(y2, c.q4, fma(y, c.q3, c.q2)), fma(y, c.q1, 0.5));
+    const double i0 = fma(y, fma(y2, fma(y2, c.i4, fma(y, c.i3, c.i2)), fma(y, c.i1, -0.5)), 1.0);
+    const double t = (x - mu) * i0;
+    const double wx = -w * xs;
+    const double zeta = wx * t;
+    double dq = q0 * fma(zeta, fma(zeta, zeta, zeta), zeta);
+    r.out = fma(fabs(x), c.lx, fabs(zeta) * c.lz);
+    if constexpr (QUAD) {
+        const double p2 = quad * fma(w * w * X2, t, 0.5 * (wx * wx) * fma(-t, t, 1.0)) * (q0 * q0);
+        r.out = fma(fabs(p2), c.lp, r.out);
+        dq = fma(p2, 1.0 + zeta, dq);
+    }
+    r.out = fma(fabs(dq), c.ld, r.out);
+    const double q = q0 + dq;
+    r.u = fma(-w, q, u0);
+    r.x = QUAD ? fma(r.u, fma(r.u, X2, X1), X0) : fma(r.u, X1, X0);
+    r.q = q;
+    r.iD = fma(i0, fma(-(1.0 + q), i0, 1.0), i0);
+}
+
+// p_i . E of a charge at the root of small_root, per kq / L^2 (Eq. (E) on the source's
+// axis, as drive_scalar): muI = p_i . Delta / L, b = v / c and e = a L / c^2 along the
+// axis, |b| <= 2^-13 (1 / kappa^3 by its series through b^4).  Every term is formed as
+// its difference from the field muI of the charge at rest at the origin, so only
+// the last sum rounds relative to one charge's field.  DIFF leaves that sum out: muI
+// cancels exactly between a dipole's two charges, and what is left rounds
+// relative to the dipole's field, 1e3 to 1e6 times smaller (the mixed form).
+template <bool DIFF>
+__device__ __forceinline__ double small_field(const SmallK &c, double mu, double muI, double pij, const SmallRoot &r,
+                                              double b, double e)
+{
+    const double j = -r.q * r.iD;                       // 1 / D - 1
+    const double wn = (mu - r.x) * r.iD;                // n . p_j
+    const double dp = fma(j, muI, -(r.x * pij) * r.iD); // p_i . n - muI
+    const double pin = muI + dp;
+    const double jj = fma(j, j, j + j);                 // 1 / D^2 - 1
+    const double z = b * wn;
+    const double k = z * fma(z, fma(z, fma(z, c.k3, c.k2), c.k1), c.k0);      // 1 / kappa^3 - 1
+    const double q = fma(-pin, wn, pij);
+    double B = fma(pin, jj, dp);
+    B = fma(-b * (1.0 + jj), fma(b, fma(-b, pij, pin), pij), B);
+    B = fma(-e * q, r.iD, B);
+    B = fma(k, muI + B, B);
+    return DIFF ? B : muI + B;
 }
 
 // Output row of the state after `rel` steps of the call, or -1 when the

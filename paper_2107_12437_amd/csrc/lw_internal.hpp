@@ -69,7 +69,10 @@ hipError_t launch_fields_vjp(const SrcRec *d_recs, int nch, const double *d_pts,
 struct DipDev;     // device-side oscillator constants
 size_t dip_dev_bytes(int n);   // the DipDev array and its structure-of-arrays copy
 int ring_lds_bytes(int n, int ring);
-hipError_t launch_dipole_prep(const lw_dipole *d_in, int n, DipDev *d_dev, hipStream_t s);
+hipError_t launch_dipole_prep(const lw_dipole *d_in, int n, double dt, DipDev *d_dev, hipStream_t s);
+// Largest instance of the one-wave kernel (fixed origins, ring in LDS), which a list
+// whose max_n is at most this takes.
+int dipole_small_max_n();
 // One launch of the per-instance persistent kernel over the instances listed in
 // d_list[0..n_list); max_n is the largest of them.  With ring_lds the history
 // ring lives in LDS, otherwise at d_ring_global + d_ring_off[block].
