@@ -666,8 +666,7 @@ lw_status lw_fields_vjp(lw_ctx *ctx, const lw_traj *h_charges, int32_t n_charges
         LW_HIP(lw::launch_fill_zero(d_grad, (int64_t)n_charges * lw::vjp_params(), s));
         return LW_OK;
     }
-    const int tchunk = 4;
-    const size_t part_bytes = align_up(sizeof(double) * lw::vjp_partial_doubles(n_pts, n_times, n_charges, tchunk), 256);
+    const size_t part_bytes = align_up(sizeof(double) * lw::vjp_partial_doubles(n_pts, n_times, n_charges), 256);
     lw::SrcRec *d_recs = nullptr;
     void *d_partial = nullptr;
     st = stage_records(ctx, h_charges, n_charges, h_times, n_times, nullptr, n_pts, part_bytes, s, &d_recs, &d_partial);
@@ -675,7 +674,7 @@ lw_status lw_fields_vjp(lw_ctx *ctx, const lw_traj *h_charges, int32_t n_charges
     const double mask_r = opts->mask_radius < 0.0 ? 1e-10 : opts->mask_radius;
     const double tol_rel = 4.0 * 2.220446049250313e-16;     // the adjoint recomputes the forward in FP64
     LW_HIP(lw::launch_fields_vjp(d_recs, n_charges, d_pts, n_pts, n_times, *opts, tol_rel, mask_r, d_cot,
-                                 (double *)d_partial, tchunk, d_grad, s));
+                                 (double *)d_partial, d_grad, s));
     return LW_OK;
 }
 

@@ -60,10 +60,10 @@ hipError_t launch_fill_zero(double *d, int64_t n, hipStream_t s);
 // Vector-Jacobian product of the grid fields with respect to the 11 trajectory
 // parameters of every charge (lw_adjoint.hip).
 int vjp_params();
-size_t vjp_partial_doubles(int64_t npts, int nt, int nch, int tchunk);
+size_t vjp_partial_doubles(int64_t npts, int nt, int nch);
 hipError_t launch_fields_vjp(const SrcRec *d_recs, int nch, const double *d_pts, int64_t npts, int nt,
                              const lw_opts &o, double tol_rel, double mask_r, const void *d_cot, double *d_partial,
-                             int tchunk, double *d_grad, hipStream_t s);
+                             double *d_grad, hipStream_t s);
 
 // Lorentz-oscillator runs.
 struct DipDev;     // device-side oscillator constants
