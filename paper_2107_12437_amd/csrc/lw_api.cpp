@@ -575,6 +575,10 @@ lw_status lw_fields(lw_ctx *ctx, const lw_traj *h_charges, int32_t n_charges, co
     auto it = ctx->tuned.find(key);
     if (it != ctx->tuned.end()) {
         L = it->second;
+    } else if (ctx->autotune && lw::fields_by_lane(n_pts, n_times, n_charges)) {
+        // a size that takes its own launch whatever the shape: nothing to time
+        ctx->tuned[key] = L;
+        save_tune_entry(ctx, key, L);
     } else if (ctx->autotune) {
         // time every candidate shape once (after one untimed launch) on this call's
         // own inputs; the final launch below writes the result

@@ -296,6 +296,175 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_for(s
     if (flags && fl_all) atomicOr(flags + p, fl_all);
 }
 
+// The per-(time, charge) part of a charge's record at this lane's own time, over the
+// charge's uniform part.
+template <int KIND>
+__device__ __forceinline__ SrcRec lane_record(const SrcRec *__restrict__ R0, int nch, int c, int ti)
+{
+    SrcRec S = R0[c];
+    const SrcRec &T = R0[(int64_t)ti * nch + c];
+    S.t = T.t;
+    if constexpr (KIND == K_CIRCULAR || KIND == K_LINEAR_OSC) {
+        S.cT = T.cT;
+        S.sT = T.sT;
+    } else if constexpr (KIND == K_ACCEL) {
+        S.Lmax = T.Lmax;
+    } else if constexpr (KIND == K_UNIFORM_VELOCITY) {
+        for (int i = 0; i < 3; ++i) S.rt[i] = T.rt[i];
+    }
+    return S;
+}
+
+template <typename F, int KIND>
+__device__ __forceinline__ void charge_lane(double *lsum, const SrcRec *__restrict__ R0, int nch, int c, int ti,
+                                            const double x[3], int field_kind, int outputs, int max_iter,
+                                            double tol_rel, double mask_r, uint32_t &fl, bool &near)
+{
+    const SrcRec S = lane_record<KIND>(R0, nch, c, ti);
+    Geo g;
+    geo_prepare_k<KIND>(S, x, g);
+    Kin k;
+    retarded_kind<sizeof(F) == 8, KIND>(S, g, x, max_iter, tol_rel, k, fl);
+    F o[10];
+    const F D = lw_terms<F, false>(k, sizeof(F) == 4 ? (F)S.kqf : (F)S.kq, field_kind, o);
+    near = near || !(D >= (F)mask_r);
+    auto add = [&](int q) {
+        __hip_atomic_fetch_add(lsum + q * 64, (double)o[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    if (outputs & OUT_PHI) add(0);
+    if (outputs & OUT_A)
+#pragma unroll
+        for (int q = 1; q < 4; ++q) add(q);
+    if (outputs & (OUT_E | OUT_S))
+#pragma unroll
+        for (int q = 4; q < 7; ++q) add(q);
+    if (outputs & (OUT_B | OUT_S))
+#pragma unroll
+        for (int q = 7; q < 10; ++q) add(q);
+}
+
+// Calls too small to fill the chip, and calls whose points leave the lanes of
+// fields_kernel's waves idle (few points, many times).  A lane is one (point, time), so
+// waves are full whatever the number of points, and the waves of a workgroup share the
+// charges (wave w takes charges w, w + W, ...), each with its own sums, added in a fixed
+// order at the end.  Such a call is a chain of dependent instructions per charge on a
+// fraction of the SIMDs: 6 points x 1,500 times x 12 charges, FP64, took 44 us by
+// fields_kernel and takes 8.3 here; a single charge on 64 x 64 points takes 4.9.
+template <typename F>
+__global__ __launch_bounds__(512) void fields_lane_kernel(const SrcRec *__restrict__ recs, int nch,
+                                                          const double *__restrict__ pts, int64_t npts, int nt,
+                                                          int field_kind, int outputs, int nrows, int max_iter,
+                                                          double tol_rel, double mask_r, F *__restrict__ out,
+                                                          uint32_t *__restrict__ flags)
+{
+    extern __shared__ double s_sums[];                 // [waves][10][64]
+    __shared__ uint32_t s_flags[8][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+    const int64_t item = (int64_t)blockIdx.x * 64 + lane, n_items = npts * nt;
+    const bool live = item < n_items;
+    // (a lane past the end repeats the last item and stores nothing)
+    const int64_t it = live ? item : n_items - 1;
+    const int ti = (int)(it / npts);
+    const int64_t p = it - (int64_t)ti * npts;
+    const double x[3] = {pts[p], pts[npts + p], pts[2 * npts + p]};
+    double *lsum = s_sums + wave * 640 + lane;
+#pragma unroll
+    for (int q = 0; q < 10; ++q) lsum[q * 64] = 0.0;
+    uint32_t fl = 0u;
+    bool near = false;
+    for (int c = wave; c < nch; c += W) {
+        switch (recs[c].kind) {
+        case K_CIRCULAR:
+            charge_lane<F, K_CIRCULAR>(lsum, recs, nch, c, ti, x, field_kind, outputs, max_iter, tol_rel, mask_r, fl, near);
+            break;
+        case K_LINEAR_OSC:
+            charge_lane<F, K_LINEAR_OSC>(lsum, recs, nch, c, ti, x, field_kind, outputs, max_iter, tol_rel, mask_r, fl, near);
+            break;
+        case K_ACCEL:
+            charge_lane<F, K_ACCEL>(lsum, recs, nch, c, ti, x, field_kind, outputs, max_iter, tol_rel, mask_r, fl, near);
+            break;
+        case K_UNIFORM_VELOCITY:
+            charge_lane<F, K_UNIFORM_VELOCITY>(lsum, recs, nch, c, ti, x, field_kind, outputs, max_iter, tol_rel, mask_r,
+                                               fl, near);
+            break;
+        default:
+            charge_lane<F, K_STATIONARY>(lsum, recs, nch, c, ti, x, field_kind, outputs, max_iter, tol_rel, mask_r, fl, near);
+            break;
+        }
+    }
+    s_flags[wave][lane] = fl | (near ? FLAG_MASKED : 0u);
+    __syncthreads();
+    // the waves' sums into the first wave's, row by row
+    for (int q = wave; q < 10; q += W) {
+        double v = s_sums[q * 64 + lane];
+        for (int w = 1; w < W; ++w) v += s_sums[w * 640 + q * 64 + lane];
+        s_sums[q * 64 + lane] = v;
+    }
+    for (int w = 0; w < W; ++w) fl |= s_flags[w][lane];
+    __syncthreads();
+    if (!live || wave != 0) return;
+    const bool masked = (fl & FLAG_MASKED) != 0u;
+    F *dst = out + (int64_t)ti * nrows * npts + p;
+    int r = 0;
+    auto put = [&](double v) {
+        __builtin_nontemporal_store(masked ? qnan<F>() : (F)v, dst + (int64_t)r * npts);
+        ++r;
+    };
+    double S[10];
+#pragma unroll
+    for (int q = 0; q < 10; ++q) {
+        const double v = lsum[q * 64];
+        S[q] = (q >= 1 && q <= 3) || q >= 7 ? v * INV_C : v;
+    }
+    if (outputs & OUT_PHI) put(S[0]);
+    if (outputs & OUT_A) { put(S[1]); put(S[2]); put(S[3]); }
+    if (outputs & OUT_E) { put(S[4]); put(S[5]); put(S[6]); }
+    if (outputs & OUT_B) { put(S[7]); put(S[8]); put(S[9]); }
+    if (outputs & OUT_S) {
+        constexpr double IMU0 = EPS0 * C_LIGHT * C_LIGHT;
+        put((S[5] * S[9] - S[6] * S[8]) * IMU0);
+        put((S[6] * S[7] - S[4] * S[9]) * IMU0);
+        put((S[4] * S[8] - S[5] * S[7]) * IMU0);
+    }
+    if (flags && fl) atomicOr(flags + p, fl);
+}
+
+// Waves per workgroup that fields_lane_kernel takes a call with, or 0 where
+// fields_kernel takes it.  The charges are shared by up to 8 waves while the call then
+// has at most 5,120 (five per SIMD; more only add workgroups' sums).  The call is this
+// kernel's while it has at most 1,536 waves of (point, time) lanes to share (one per
+// SIMD, 1,024, with a single charge), or where its lanes fill at most 5/8 of the waves
+// that a lane per point needs.  Prepared calls of 16 charges, FP64 (mixed), us by
+// fields_kernel at its default shape -> here:
+//   4,096 points x 1 time   35.3 -> 17.6 (32.5 -> 16.8)    65,536 x 1   37.3 -> 25.6 (33.8 -> 23.1)
+//   64 points x 256 times   38.8 -> 19.9 (35.6 -> 18.8)    64 x 1,500   46.8 -> 36.7 (41.8 -> 33.9)
+//   65,536 x 2 (2,048 waves) 36.6 -> 35.0 (33.0 -> 30.7)   262,144 x 1  45.9 -> 52.8 (37.2 -> 46.7)
+// and of 12 charges at 4,000 times: 6/64 of the lanes full (40,000 times) 279 -> 114
+// (236 -> 115), 20/64 63.3 -> 45.0 (57.2 -> 45.9), 80/128 81.8 -> 70.5 (72.7 -> 71.1),
+// 90/128 83.6 -> 76.7 (73.4 -> 75.8), 100/128 81.7 -> 78.3 (73.3 -> 80.7).
+static int lane_waves(int64_t npts, int nt, int nch)
+{
+    const int64_t by_lane = (npts * nt + 63) / 64, by_point = (npts + 63) / 64 * nt;
+    int w = 1;
+    while (2 * w <= nch && w < 8 && by_lane * 2 * w <= 5120) w *= 2;
+    if (8 * by_lane <= 5 * by_point) return by_lane < ((int64_t)1 << 31) ? w : 0;
+    return by_lane <= (w > 1 ? 1536 : 1024) ? w : 0;
+}
+
+template <typename F>
+static hipError_t launch_lane(int waves, const SrcRec *d_recs, int nch, const double *d_pts, int64_t npts, int nt,
+                              const lw_opts &o, double tol_rel, double mask_r, F *d_out, uint32_t *d_flags,
+                              hipStream_t s)
+{
+    const int max_iter = o.max_iter > 0 ? o.max_iter : 100;
+    hipLaunchKernelGGL(fields_lane_kernel<F>, dim3((unsigned)((npts * nt + 63) / 64)), dim3(64 * waves),
+                       sizeof(double) * 640 * waves, s, d_recs, nch, d_pts, npts, nt, o.field_kind,
+                       output_mask(o.outputs), output_rows(o.outputs), max_iter, tol_rel, mask_r, d_out, d_flags);
+    return hipGetLastError();
+}
+
+bool fields_by_lane(int64_t npts, int nt, int nch) { return lane_waves(npts, nt, nch) > 0; }
+
 hipError_t launch_prep(const lw_traj *d_ch, int nch, const double *d_times, int nt, SrcRec *d_recs,
                        uint32_t *d_flags, int64_t npts, hipStream_t s)
 {
@@ -339,9 +508,15 @@ static hipError_t launch_fields_f(const SrcRec *d_recs, int nch, const double *d
                                   const lw_opts &o, double tol_rel, double mask_r, F *d_out, uint32_t *d_flags,
                                   const FieldLaunch &L, hipStream_t s, unsigned long long *d_hist)
 {
-    if (d_hist)
-        return launch_fields_t<F, 1, true>(d_recs, nch, d_pts, npts, nt, o, tol_rel, mask_r, d_out, d_flags, 256, s,
-                                           d_hist);
+    if (d_hist) {
+        // the counting instance; a call of fields_lane_kernel's is launched again by it, so
+        // that counting leaves the outputs' bits alone
+        const hipError_t e = launch_fields_t<F, 1, true>(d_recs, nch, d_pts, npts, nt, o, tol_rel, mask_r, d_out,
+                                                         d_flags, 256, s, d_hist);
+        if (e != hipSuccess || !fields_by_lane(npts, nt, nch)) return e;
+    }
+    if (const int waves = lane_waves(npts, nt, nch))
+        return launch_lane<F>(waves, d_recs, nch, d_pts, npts, nt, o, tol_rel, mask_r, d_out, d_flags, s);
     if (L.tchunk >= 4)
         return launch_fields_t<F, 4>(d_recs, nch, d_pts, npts, nt, o, tol_rel, mask_r, d_out, d_flags, L.block, s);
     if (L.tchunk >= 2)

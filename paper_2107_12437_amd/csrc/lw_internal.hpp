@@ -50,6 +50,9 @@ constexpr int ITER_BINS = LW_ITER_BINS, ITER_BIN_FALLBACK = LW_ITER_BIN_FALLBACK
 hipError_t launch_fields(const SrcRec *d_recs, int nch, const double *d_pts, int64_t npts, int nt,
                          const lw_opts &o, double tol_rel, double mask_r, void *d_out, uint32_t *d_flags,
                          const FieldLaunch &L, hipStream_t s, unsigned long long *d_hist = nullptr);
+// Whether launch_fields takes a call of this size by (point, time) lanes, whatever the
+// launch shape.
+bool fields_by_lane(int64_t npts, int nt, int nch);
 size_t src_rec_bytes();
 // Output rows of an outputs mask (0: Phi | A | E | B).
 int output_mask(int outputs);
