@@ -182,8 +182,40 @@ def _stream_ptr(device) -> ct.c_void_p:
     return ct.c_void_p(torch.cuda.current_stream(device).cuda_stream)
 
 
+# lw_traj as rows of 18 doubles; the first holds the kind (int32, little endian) and padding
+_TRAJ_COLS = (("q", 1, None), ("c0", 2, 5), ("e1", 5, 8), ("e2", 8, 11), ("amp", 11, None), ("omega", 12, None),
+              ("phase", 13, None), ("accel", 14, None), ("v", 15, 18))
+
+
+def _pack_columns(charges: dict, n: int):
+    """The records by whole columns, for plain real numpy columns of at least n rows; None
+    for anything else (lists, tensors, other shapes)."""
+    kind = charges["kind"]
+    if type(kind) is not np.ndarray or kind.ndim != 1 or kind.dtype.kind not in "iu":
+        return None
+    a = np.zeros((n, 18), dtype=np.float64)
+    a.view(np.int32)[:, 0] = kind
+    for key, lo, hi in _TRAJ_COLS:
+        col = charges[key]
+        if type(col) is not np.ndarray or col.dtype.char not in "dfbhilqBHILQ" or len(col.shape) != (1 if hi is None else 2) \
+                or len(col) < n or (hi is not None and col.shape[1] != hi - lo):
+            return None
+        if hi is None:
+            a[:, lo] = col if len(col) == n else col[:n]
+        else:
+            a[:, lo:hi] = col if len(col) == n else col[:n]
+    return (Traj * n).from_buffer(a), n
+
+
 def pack_charges(charges: dict):
+    """lw_traj records of the charges as a ctypes array.  From two charges on, plain numpy
+    columns are packed a column at a time: a record at a time takes 3.4 us per charge, the
+    columns 4.5 us for any small number of charges."""
     n = len(charges["kind"])
+    if n >= 2:
+        packed = _pack_columns(charges, n)
+        if packed is not None:
+            return packed
     arr = (Traj * max(n, 1))()
     for i in range(n):
         t = arr[i]
