@@ -59,7 +59,7 @@ __global__ void dipole_prep_kernel(const lw_dipole *__restrict__ in, int n, doub
     o.mph = moves ? D.motion_phase : 0.0;
     o.mspeed = moves ? fabs(D.motion_omega) * am : 0.0;
     o.ehalf = 0.5 / o.f;
-    rk4_coefs(o.omega0 * o.omega0, o.gamma0, o.f, dt, o.rk);
+    rk4_coefs(o.omega0, o.gamma0, o.f, dt, o.rk);
     dev[i] = o;
     const double f[SF_COUNT] = {o.origin[0], o.origin[1], o.origin[2], o.axis[0], o.axis[1], o.axis[2], o.cfp,
                                 o.cfm,       o.d0,        o.q,         o.mamp[0], o.mamp[1], o.mamp[2], o.mw, o.mph};

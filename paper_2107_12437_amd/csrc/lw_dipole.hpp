@@ -227,14 +227,22 @@ __device__ __forceinline__ void rk4_stages(double w2, double g, double f, double
     dv = dt / 6.0 * (k1v + 2.0 * k2v + 2.0 * k3v + k4v);
 }
 
-__device__ __forceinline__ void rk4_coefs(double w2, double g, double f, double dt, double c[9])
+// The two leading coefficients, dt (1 + e) of d_dot in d and -omega^2 dt (1 + e) of d in
+// d_dot, rounded once: through the stages they carry three or four roundings, and an
+// error of theirs is a phase error that grows with every step.
+__device__ __forceinline__ void rk4_coefs(double om, double g, double f, double dt, double c[9])
 {
     double skip;
+    const double w2 = om * om;
     rk4_stages(w2, g, f, dt, 1.0, 0.0, 0.0, 0.0, 0.0, c[0], c[4]);
     rk4_stages(w2, g, f, dt, 0.0, 1.0, 0.0, 0.0, 0.0, c[1], c[5]);
     rk4_stages(w2, g, f, dt, 0.0, 0.0, 1.0, 0.0, 0.0, c[2], c[6]);
     rk4_stages(w2, g, f, dt, 0.0, 0.0, 0.0, 1.0, 0.0, c[3], c[7]);
     rk4_stages(w2, g, f, dt, 0.0, 0.0, 0.0, 0.0, 1.0, skip, c[8]);
+    const double e = dt * (-0.5 * g + dt * ((g * g - w2) / 6.0 + dt * (2.0 * g * w2 - g * g * g) / 24.0));
+    const double p = w2 * dt, p_lo = fma(w2, dt, -p) + fma(om, om, -w2) * dt;
+    c[1] = fma(dt, e, dt);
+    c[4] = -(p + fma(p, e, p_lo));
 }
 
 __device__ __forceinline__ void rk4_step(const double c[9], double y0, double y1, double Ec, double Em, double Ee,
