@@ -84,9 +84,10 @@ struct lw_ctx {
     bool stage_pending = false;
     uint32_t *d_err = nullptr;
     lw::FieldLaunch field_launch{256, 2};  // untuned shape: the fastest on the grid benchmark in both precisions
-    hipStream_t side = nullptr, side2 = nullptr;   // persistent instances beside the stepped ones, joined back
+    static constexpr int DIPOLE_KINDS = 4;
+    hipStream_t side[DIPOLE_KINDS] = {};   // persistent instances beside the stepped ones, joined back
     hipStream_t capture = nullptr;     // graph capture of stepped runs
-    hipEvent_t join_a = nullptr, join_b = nullptr, join_c = nullptr;
+    hipEvent_t join_a = nullptr, join[DIPOLE_KINDS] = {};
     hipGraph_t graph = nullptr;        // last stepped run's graph, released once the stream passed it
     hipGraphExec_t graph_exec = nullptr;
     hipEvent_t graph_done = nullptr;
@@ -409,10 +410,10 @@ lw_status lw_destroy(lw_ctx *ctx)
     if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
     if (ctx->graph_done) (void)hipEventDestroy(ctx->graph_done);
     if (ctx->join_a) (void)hipEventDestroy(ctx->join_a);
-    if (ctx->join_b) (void)hipEventDestroy(ctx->join_b);
-    if (ctx->join_c) (void)hipEventDestroy(ctx->join_c);
-    if (ctx->side) (void)hipStreamDestroy(ctx->side);
-    if (ctx->side2) (void)hipStreamDestroy(ctx->side2);
+    for (hipEvent_t e : ctx->join)
+        if (e) (void)hipEventDestroy(e);
+    for (hipStream_t q : ctx->side)
+        if (q) (void)hipStreamDestroy(q);
     if (ctx->adj_side) (void)hipStreamDestroy(ctx->adj_side);
     if (ctx->adj_built) (void)hipEventDestroy(ctx->adj_built);
     if (ctx->adj_swept) (void)hipEventDestroy(ctx->adj_swept);
@@ -903,9 +904,11 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     LW_HIP(hipSetDevice(ctx->device));
     hipStream_t s = (hipStream_t)stream;
 
-    // small instances whose ring fits in LDS run whole in one workgroup each;
-    // the others advance one launch per step with one workgroup per dipole
-    const int lds_limit = 64 * 1024;
+    // small instances whose ring fits in LDS run whole in one workgroup each; the others
+    // advance one launch per step.  The kernels with a lane per pair take all of a CU's
+    // 160 KB (96 instances of 5 to 12 dipoles with 256 samples, 76 KB for 12: 5.2 us per step by
+    // launches, 1.6 here); the general one, slower per step, keeps two workgroups per CU
+    auto lds_limit = [](int kind) { return kind < lw_ctx::DIPOLE_KINDS - 1 ? 160 * 1024 - 512 : 64 * 1024; };
     int stepped_min = opts->stepped_min_n == 0 ? 16 : (opts->stepped_min_n < 0 ? (1 << 30) : opts->stepped_min_n);
     if (opts->stepped_min_n == LW_STEPPED_TUNE) {
         const lw_status tst = tune_stepped(ctx, h_dip, n_dip, h_inst_off, n_inst, dt, opts, ring, s, &stepped_min);
@@ -913,23 +916,34 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     }
     bool moving = false;
     for (int i = 0; i < n_dip; ++i) moving = moving || motion_reach(h_dip[i]) > 0.0;
-    // the smallest instances (one wave each) apart from the others, whose kernel is
-    // slower for them: 256 pairs beside one 5-dipole instance would all take it
-    const int tiny_n = moving ? 0 : lw::dipole_small_max_n();
-    std::vector<int32_t> tiny_list, lds_list, tgt, tgt_lo, tgt_n;
+    // persistent instances by the kernel that is fastest for them: the smallest one
+    // wave, the next two a workgroup with a lane per pair, the rest (and all moving ones) the general
+    // kernel.  Each kind is one launch, so that no instance takes another's slower kernel
+    struct Kind {
+        int max_n = 0;                   // largest instance this kind takes
+        std::vector<int32_t> list;
+        int lo = 1 << 30, hi = 0;        // smallest and largest present
+        hipStream_t on = nullptr;
+        bool fork = false;
+    };
+    constexpr int KINDS = lw_ctx::DIPOLE_KINDS;
+    Kind kinds[KINDS];
+    for (int k = 0; k < KINDS; ++k) kinds[k].max_n = k == KINDS - 1 ? 1 << 30 : moving ? 0 : lw::dipole_kind_max_n(k);
+    std::vector<int32_t> tgt, tgt_lo, tgt_n;
     std::vector<int64_t> tgt_base;
-    int max_lds_n = 0;
+    size_t n_listed = 0;
     int64_t ring_doubles = 0;
     for (int k = 0; k < n_inst; ++k) {
         const int a0 = h_inst_off[k], n = h_inst_off[k + 1] - a0;
         if (n == 0) continue;
-        if (n < stepped_min && lw::ring_lds_bytes(n, ring) <= lds_limit) {
-            if (n <= tiny_n) {
-                tiny_list.push_back(k);
-                continue;
-            }
-            lds_list.push_back(k);
-            max_lds_n = std::max(max_lds_n, n);
+        int q = 0;
+        while (n > kinds[q].max_n) ++q;
+        if (n < stepped_min && lw::ring_lds_bytes(n, ring) <= lds_limit(q)) {
+            Kind &K = kinds[q];
+            K.list.push_back(k);
+            K.lo = std::min(K.lo, n);
+            K.hi = std::max(K.hi, n);
+            ++n_listed;
         } else {
             // a run state keeps every instance's ring at its place in the state
             const int64_t base = d_state ? lw::state_ring_off(a0, ring) - lw::STATE_HEAD : ring_doubles;
@@ -963,7 +977,7 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
 
     const size_t in_bytes = align_up(sizeof(lw_dipole) * (size_t)n_dip, 256);
     const size_t off_bytes = align_up(sizeof(int32_t) * (size_t)(n_inst + 1), 256);
-    const size_t list_bytes = align_up(sizeof(int32_t) * (tiny_list.size() + lds_list.size() + 1), 256);
+    const size_t list_bytes = align_up(sizeof(int32_t) * (n_listed + 1), 256);
     const size_t t32_bytes = align_up(sizeof(int32_t) * (n_tgt + 1), 256);
     const size_t t64_bytes = align_up(sizeof(int64_t) * (n_tgt + 1), 256);
     const size_t stage_bytes = in_bytes + off_bytes + list_bytes + 3 * t32_bytes + t64_bytes;
@@ -989,8 +1003,8 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     o += in_bytes;
     std::memcpy(stage + o, h_inst_off, sizeof(int32_t) * (size_t)(n_inst + 1));
     o += off_bytes;
-    std::copy(tiny_list.begin(), tiny_list.end(), (int32_t *)(stage + o));
-    std::copy(lds_list.begin(), lds_list.end(), (int32_t *)(stage + o) + tiny_list.size());
+    int32_t *lists = (int32_t *)(stage + o);
+    for (const Kind &K : kinds) lists = std::copy(K.list.begin(), K.list.end(), lists);
     o += list_bytes;
     std::copy(tgt.begin(), tgt.end(), (int32_t *)(stage + o));
     o += t32_bytes;
@@ -1039,33 +1053,35 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     // a resumed run's row 0 comes from its state, before either path updates it
     if (resume) LW_HIP(lw::launch_state_rows(d_dev, d_off, n_inst, d_state, ring, out, ctx->d_err, s));
     const bool mixed = opts->precision == LW_MIXED;
-    // up to three kinds of instances run at once: the last kind present on the
+    // the kinds present run at once: the stepped instances, or else the last kind, on the
     // caller's stream, the others on side streams forked from it and joined back
-    const bool fork_lds = !lds_list.empty() && n_tgt > 0;
-    const bool fork_tiny = !tiny_list.empty() && (n_tgt > 0 || !lds_list.empty());
-    if (fork_lds || fork_tiny) {
+    bool later = n_tgt > 0, any_fork = false;
+    for (int k = KINDS - 1; k >= 0; --k) {
+        kinds[k].fork = later && !kinds[k].list.empty();
+        any_fork = any_fork || kinds[k].fork;
+        later = later || !kinds[k].list.empty();
+    }
+    if (any_fork) {
         if (!ctx->join_a) LW_HIP(hipEventCreateWithFlags(&ctx->join_a, hipEventDisableTiming));
         LW_HIP(hipEventRecord(ctx->join_a, s));
     }
-    auto forked = [&](bool fork, hipStream_t &side, hipEvent_t &join, hipStream_t &on) -> lw_status {
-        on = s;
-        if (!fork) return LW_OK;
-        if (!side) LW_HIP(hipStreamCreateWithFlags(&side, hipStreamNonBlocking));
-        if (!join) LW_HIP(hipEventCreateWithFlags(&join, hipEventDisableTiming));
-        LW_HIP(hipStreamWaitEvent(side, ctx->join_a, 0));
-        on = side;
-        return LW_OK;
-    };
-    hipStream_t lds_s = s, tiny_s = s;
-    st = forked(fork_lds, ctx->side, ctx->join_b, lds_s);
-    if (st == LW_OK) st = forked(fork_tiny, ctx->side2, ctx->join_c, tiny_s);
-    if (st != LW_OK) return st;
-    LW_HIP(lw::launch_dipole_instances(d_dev, d_off, d_list + tiny_list.size(), (int)lds_list.size(), max_lds_n, true,
-                                       nullptr, nullptr, ring, steps, dt, max_vel, max_iter, out, moving, mixed,
-                                       d_state, resume, ctx->d_err, lds_s));
-    LW_HIP(lw::launch_dipole_instances(d_dev, d_off, d_list, (int)tiny_list.size(), tiny_n, true, nullptr, nullptr,
-                                       ring, steps, dt, max_vel, max_iter, out, moving, mixed, d_state, resume,
-                                       ctx->d_err, tiny_s));
+    const int32_t *d_kind = d_list;
+    for (int k = 0; k < KINDS; ++k) {
+        Kind &K = kinds[k];
+        K.on = s;
+        if (K.fork) {
+            hipStream_t &side = ctx->side[k];
+            hipEvent_t &join = ctx->join[k];
+            if (!side) LW_HIP(hipStreamCreateWithFlags(&side, hipStreamNonBlocking));
+            if (!join) LW_HIP(hipEventCreateWithFlags(&join, hipEventDisableTiming));
+            LW_HIP(hipStreamWaitEvent(side, ctx->join_a, 0));
+            K.on = side;
+        }
+        LW_HIP(lw::launch_dipole_instances(d_dev, d_off, d_kind, (int)K.list.size(), K.lo, K.hi, true, nullptr, nullptr,
+                                           ring, steps, dt, max_vel, max_iter, out, moving, mixed, d_state, resume,
+                                           ctx->d_err, K.on));
+        d_kind += K.list.size();
+    }
     if (n_tgt > 0) {
         if (!ctx->capture) LW_HIP(hipStreamCreateWithFlags(&ctx->capture, hipStreamNonBlocking));
         if (!ctx->graph_done) LW_HIP(hipEventCreateWithFlags(&ctx->graph_done, hipEventDisableTiming));
@@ -1076,14 +1092,11 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
                                        &ctx->graph_exec));
         LW_HIP(hipEventRecord(ctx->graph_done, s));
     }
-    if (fork_lds) {
-        LW_HIP(hipEventRecord(ctx->join_b, lds_s));
-        LW_HIP(hipStreamWaitEvent(s, ctx->join_b, 0));
-    }
-    if (fork_tiny) {
-        LW_HIP(hipEventRecord(ctx->join_c, tiny_s));
-        LW_HIP(hipStreamWaitEvent(s, ctx->join_c, 0));
-    }
+    for (int k = 0; k < KINDS; ++k)
+        if (kinds[k].fork) {
+            LW_HIP(hipEventRecord(ctx->join[k], kinds[k].on));
+            LW_HIP(hipStreamWaitEvent(s, ctx->join[k], 0));
+        }
     if (d_state) LW_HIP(lw::launch_state_header(d_state, ring, n_dip, steps, resume, s));
     return LW_OK;
 }

@@ -1366,6 +1366,352 @@ __global__ __launch_bounds__(64) void lo_small_kernel(const DipDev *__restrict__
 }
 
 // ---------------------------------------------------------------------------
+// Instances of SMALL_MAX_N + 1 to GROUP_MAX_N fixed dipoles, a workgroup each: lo_small_kernel's
+// step spread over waves.  A lane holds one (target i, source j, stage) for the whole
+// run, both charges of the source: their two roots are independent chains that share
+// the pair's geometry, and half the lanes of a charge per lane keep to two waves per
+// SIMD at most.  The Lg = 8 (n <= 9) or 16 lanes of target i and a stage sum its drive by
+// DPP; a wave holds both stages of 32 / Lg targets and integrates them, so only the new
+// samples cross waves, behind one barrier a step: the ring holds twice the longest light
+// time and three more samples, so the row a wave writes is not one that a wave still
+// in its drives can read, and a stop is flagged per step parity, so that every wave
+// leaves at the same step.
+// Up to 9 dipoles a step is bound by that chain, beyond by the instructions of two waves
+// per SIMD.  96 instances, FP64 (mixed), energy sums, us per step by lo_instances_kernel ->
+// here: 8 dipoles 4.0 -> 0.94 (3.9 -> 0.99), 12 dipoles 3.4 -> 1.51 (3.7 -> 1.48); 2,048
+// instances of 7 5.1 -> 3.1 (5.9 -> 3.0), 1,024 of 12 6.2 -> 6.0 (8.8 -> 5.8).  The series'
+// constants sit in scalar registers and waves_per_eu(2) caps the rest at 256 VGPRs: above
+// that a SIMD holds one wave (4.0 us for the 2,048 instances).
+// ---------------------------------------------------------------------------
+constexpr int GROUP8_MAX_N = 9, GROUP_MAX_N = 16;
+constexpr int DPP_MIRROR16 = 0x140;
+__host__ __device__ constexpr int group_lg(int n) { return n <= GROUP8_MAX_N ? 3 : 4; }
+__host__ __device__ constexpr int group_threads(int n)
+{
+    return 64 * ((n + (32 >> group_lg(n)) - 1) >> (5 - group_lg(n)));
+}
+
+// One charge of a lane's source: its segment relative to the current step (rows kf and
+// kf + 1, or the newest row alone), as in lo_small_kernel
+struct GroupCharge {
+    double ci, cb, ce;                           // offset, speed and acceleration factors
+    double u0, cdt, hdt2, quad, mid, half;
+    double g0[3], g1[3];
+    int kf;
+    unsigned nx;
+};
+
+template <bool MIXED, int LG>
+__global__ __launch_bounds__(group_threads(LG == 3 ? GROUP8_MAX_N : GROUP_MAX_N))
+__attribute__((amdgpu_waves_per_eu(2))) void lo_group_kernel(
+    const DipDev *__restrict__ dev, const int32_t *__restrict__ off, const int32_t *__restrict__ inst_list, int ring,
+    int64_t steps, double dt, double max_vel, int max_iter, RunOut out, double *__restrict__ state, int resume,
+    uint32_t *__restrict__ d_err)
+{
+    extern __shared__ double lds[];
+    const int inst = inst_list[blockIdx.x];
+    const int i0 = off[inst];
+    const int n = off[inst + 1] - i0;
+    const int tid = threadIdx.x;
+    if (n <= 0) return;
+    constexpr int lg = LG;
+    const int threads = 64 * ((n + (32 >> LG) - 1) >> (5 - LG));
+    if (n - 1 > (1 << LG) || threads > (int)blockDim.x || threads < 128) {   // (the host launches none)
+        if (tid == 0) atomicOr(d_err, (uint32_t)ERR_STATE);
+        return;
+    }
+    if (tid >= threads) return;                  // waves that the launch's largest instance needs
+
+    DipLds *S = (DipLds *)lds;                   // LDS layout as lo_instances_kernel's
+    double *qv = (double *)(S + n);
+    double *Ecur = qv + n;
+    double *Wab = Ecur + 3 * n;
+    double *Wra = Wab + n;
+    double *ringp = Wra + 7 * n;
+    __shared__ uint32_t s_err, s_stop[2];        // the run's error bits; a stop at an even or odd step
+
+    for (int j = tid; j < n; j += threads) {
+        const DipDev &D = dev[i0 + j];
+        S[j] = dip_lds(D);
+        qv[j] = D.q;
+    }
+    if (tid == 0) s_err = s_stop[0] = s_stop[1] = 0u;
+    __syncthreads();
+
+    const SmallK sk = small_k<false>();
+    Hist H{ringp, n, ring - 1, dt, 1.0 / dt};
+    uint32_t err = 0u;
+    const int64_t ring_all = (int64_t)ring * n * 3;
+    int64_t n0 = 0;
+    if (resume) {
+        n0 = (int64_t)state[0];
+        const double *sr = state + state_ring_off(i0, ring);
+        for (int64_t k = tid; k < ring_all; k += threads) ringp[k] = sr[k];
+        const int64_t oe = state_ecur_off(out.n_dip, ring), ow = state_w_off(out.n_dip, ring);
+        for (int i = tid; i < n; i += threads) {
+            Ecur[i] = state[oe + i0 + i];
+            Wab[i] = state[ow + 2 * (i0 + i)];
+            Wra[i] = state[ow + 2 * (i0 + i) + 1];
+        }
+    } else {
+        if (tid < 128) {
+            const double th0[1] = {0.0};
+            drive_all<128, false, MIXED>(sk, H, S, qv, n, 0, th0, 1, Ecur, max_iter, err);
+        }
+        __syncthreads();
+        for (int i = tid; i < n; i += threads) {
+            const DipDev &D = dev[i0 + i];
+            double *h = ringp + (int64_t)i * 3;
+            h[0] = D.d0;
+            h[1] = 0.0;
+            h[2] = D.f * Ecur[i] - D.omega0 * D.omega0 * D.d0;
+            Wab[i] = 0.0;
+            Wra[i] = 0.0;
+            put_row(out, 0, i0 + i, D.d0, 0.0, run_energy(D.omega0 * D.omega0, D.ehalf, D.d0, 0.0), Ecur[i], 0.0,
+                    0.0);
+        }
+    }
+    __syncthreads();
+
+    // this lane's target, source and stage
+    const int th = (tid >> 5) & 1, sub = tid & ((1 << lg) - 1);
+    const int ui = ((tid >> 6) << (5 - lg)) + ((tid & 31) >> lg);
+    const bool live = ui < n, active = live && sub < n - 1;
+    const int me = live ? ui : 0;
+    int uj = 0;
+    double ud0 = 0.0, utheta = 0.0, kq = 0.0, kql2 = 0.0, mu = 0.0, muI = 0.0, w = 1.0;
+    PairGeo P{1.0, 1.0, 1.0, 0.0, 0.0, 0.0};
+    GroupCharge C[2];
+    if (active) {
+        uj = sub < ui ? sub : sub + 1;
+        const DipLds Si = S[ui], Sj = S[uj];
+        ud0 = Sj.d0;
+        utheta = th ? 1.0 : 0.5;
+        kq = qv[uj] * K_COUL;
+        const double X[3] = {Si.ox, Si.oy, Si.oz};
+        P = pair_geo(X, Si, Sj);
+        mu = P.sD * P.iL;
+        muI = P.sI * P.iL;
+        kql2 = kq * (P.iL * P.iL);
+        w = P.L * (INV_C * H.inv_dt);
+    }
+    const int kf0 = active ? (int)floor(utheta - w) : -1;
+    if (active && -kf0 > ring - 1) err |= ERR_HISTORY;    // (the ring covers every light time of the instance)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const double cf = !active ? 0.0 : c ? S[uj].cfm : S[uj].cfp;
+        C[c].ci = cf * P.iL;
+        C[c].cb = cf * INV_C;
+        C[c].ce = cf * (INV_C * INV_C) * P.L;
+        C[c].kf = kf0;
+        C[c].u0 = utheta - w - (double)kf0;
+        C[c].nx = 0;
+    }
+    // group i's lanes: dipole i's state at the run's first step, constants and sums
+    double y0 = 0.0, y1 = 0.0, y2 = 0.0, Ec = 0.0, wab = 0.0, wra = 0.0;
+    double w2 = 0.0, gm = 0.0, fq = 0.0, vfac = 0.0, ms = 0.0, eh = 0.0, rk[9];
+    for (int q = 0; q < 9; ++q) rk[q] = 0.0;
+    if (live) {
+        const DipDev &D = dev[i0 + me];
+        w2 = D.omega0 * D.omega0;
+        gm = D.gamma0;
+        fq = D.f;
+        vfac = D.vfac;
+        ms = D.mspeed;
+        eh = D.ehalf;
+        for (int q = 0; q < 9; ++q) rk[q] = D.rk[q];
+        const double *h = ringp + ((int64_t)(n0 & (ring - 1)) * n + me) * 3;
+        y0 = h[0];
+        y1 = h[1];
+        y2 = h[2];
+        Ec = Ecur[me];
+        wab = Wab[me];
+        wra = Wra[me];
+    }
+    // what this lane stores of its dipole: role 0 d, 1 d_dot, 2 the energy (and d_ddot
+    // into the ring), 3 E_d; roles 0 and 1 the energy sums when they are asked for
+    const int role = !live ? 4 : (th << lg) + sub;
+    double *po = role == 0 ? out.d : role == 1 ? out.v : role == 2 ? out.E : role == 3 ? out.Ed : nullptr;
+    double *pw = role == 0 ? out.wabs : role == 1 ? out.wrad : nullptr;
+    const bool sums = out.wabs || out.wrad;
+    const int64_t orow = out.n_dip + i0 + me;    // row 1's entry
+    if (po) po += orow;
+    if (pw) pw += orow;
+    const unsigned ring3 = (unsigned)ring_all;
+    const double hdt = 0.5 * dt, hdtl = 0.5 * dt * K_LARMOR;
+    const double vlim = max_vel > 0.0 ? max_vel : __builtin_huge_val();
+    const uint32_t stop_bits = ERR_NONFINITE | ERR_VELOCITY | ERR_HISTORY;
+
+    bool rows = false, pre_any = false;          // the charges' rows are this step's; some lie before t = 0
+    unsigned wx = (unsigned)(((n0 + 1) & (ring - 1)) * n + me) * 3u + (role < 3 ? role : 0);
+    int64_t togo = out.stride;
+    // index of the row one step later than that at index x
+    auto later = [&](unsigned x) {
+        const unsigned y = x + 3u * (unsigned)n;
+        return min(y, y - ring3);                // (unsigned: y below the ring's end stays)
+    };
+    auto load_rows = [&](GroupCharge &c, int64_t nstep) {
+        const int64_t k = nstep + c.kf;
+        const unsigned a = (unsigned)((k & (ring - 1)) * n + uj) * 3u;
+        const unsigned b = c.kf < 0 ? later(a) : a;
+        const bool pre = k < 0;                  // static before t = 0
+        for (int q = 0; q < 3; ++q) {
+            c.g0[q] = pre ? (q == 0 ? ud0 : 0.0) : ringp[a + q];
+            c.g1[q] = pre ? (q == 0 ? ud0 : 0.0) : ringp[b + q];
+        }
+        c.nx = later(b);
+        c.cdt = c.kf < 0 ? 0.0 : dt;
+        c.hdt2 = c.kf < 0 ? 0.0 : 0.5 * dt * dt;
+        c.quad = c.kf < 0 ? 0.0 : 1.0;
+        // roots of this segment: u in [0, 1], from 0 in the extrapolation, up to t = 0
+        // in the pre-history (a root within rounding of an end belongs to either side)
+        c.mid = pre ? (double)-k - 1000.0 : c.kf < 0 ? 0.5 : 1000.0;
+        c.half = (pre || c.kf >= 0 ? 1000.0 : 0.5) + 1e-9;
+        return active && pre;
+    };
+    for (int64_t nstep = n0; nstep < n0 + steps; ++nstep) {
+        double acc = 0.0;
+        bool done = false;
+        for (int hop = 0; hop < 4; ++hop) {
+            if (!rows) {
+                const bool p0 = load_rows(C[0], nstep), p1 = load_rows(C[1], nstep);
+                pre_any = __any(p0 || p1);
+            }
+            rows = true;
+            double f[2], u[2];
+            bool ok[2], in[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const GroupCharge &q = C[c];
+                SmallRoot r;
+                small_root<true>(sk, mu, w, q.u0, q.ci * q.g0[0], q.ci * fma(q.g0[1], q.cdt, q.g1[0] - q.g0[0]),
+                                 q.ci * (q.g0[2] * q.hdt2), q.quad, r);
+                const double b = q.cb * fma(r.u, fma(q.g0[2], q.cdt, q.g1[1] - q.g0[1]), q.g0[1]);
+                const double e = q.ce * fma(r.u, q.g1[2] - q.g0[2], q.g0[2]);
+                f[c] = small_field<MIXED>(sk, mu, muI, P.pij, r, b, e);
+                u[c] = r.u;
+                in[c] = fma(fabs(b), sk.lz, r.out) <= 1.0;
+                ok[c] = in[c] && fabs(r.u - q.mid) <= q.half;
+            }
+            acc = kql2 * f[0] - kql2 * f[1];
+            if (!__any(active && !(ok[0] && ok[1]))) {
+                done = true;
+                break;
+            }
+            // not this segment's root (the lane moves for good), or out of range
+            rows = false;
+            if (__any(active && !(in[0] && in[1]))) break;
+            int move[2];
+            bool off_ring = false;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                move[c] = !active || ok[c] ? 0 : u[c] < C[c].mid ? -1 : 1;
+                off_ring = off_ring || C[c].kf + move[c] > 0 || -(C[c].kf + move[c]) > ring - 1;
+            }
+            if (__any(off_ring)) break;          // (no such segment: the general solvers)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                C[c].kf += move[c];
+                C[c].u0 -= (double)move[c];
+            }
+        }
+        if (!done) {
+            // offsets or speeds beyond small_root's range
+            rows = false;
+            acc = 0.0;
+            if (active) {
+                if constexpr (MIXED) {
+                    const DipLds Si = S[ui], Sj = S[uj];
+                    const double X[3] = {Si.ox, Si.oy, Si.oz}, base = (double)nstep + utheta;
+                    Seg g;
+                    g.k = seg_none<int64_t>();
+                    double hp[3], hm[3];
+                    charge_fixed(H, uj, ud0, nstep, base, P.L2, P.L, P.sD, Sj.cfp, max_iter, g, hp, err);
+                    charge_fixed(H, uj, ud0, nstep, base, P.L2, P.L, P.sD, Sj.cfm, max_iter, g, hm, err);
+                    acc = mixed_field(mixed_geo(X, Si, Sj), Sj.cfp, Sj.cfm, hp, hm, kq);
+                } else {
+                    const double base = (double)nstep + utheta;
+                    acc = fixed_drive(H, P, uj, ud0, S[uj].cfp, kq, nstep, base, max_iter, err) +
+                          fixed_drive(H, P, uj, ud0, S[uj].cfm, -kq, nstep, base, max_iter, err);
+                }
+            }
+        }
+        if (!active) acc = 0.0;
+        acc += dpp_move<DPP_XOR1>(acc);
+        acc += dpp_move<DPP_XOR2>(acc);
+        acc += dpp_move<DPP_MIRROR8>(acc);
+        if constexpr (LG > 3) acc += dpp_move<DPP_MIRROR16>(acc);
+        double Em, Ee, dn, vn;
+        both_halves(acc, Em, Ee);
+        rk4_step(rk, y0, y1, Ec, Em, Ee, dn, vn);
+        const double an = fq * Ee - gm * vn - w2 * dn;
+        const double dv = role == 0 ? dn : vn;
+        // d_ddot is not finite whenever d, d_dot or the drive is not
+        if (!isfinite(an)) err |= ERR_NONFINITE;
+        if (ms + vfac * fabs(vn) > vlim) err |= ERR_VELOCITY;
+        if (role < 3) ringp[wx] = role == 2 ? an : dv;
+        if (err & stop_bits) s_stop[nstep & 1] = 1u;
+        wx = later(wx);
+        __syncthreads();
+        if (rows) {
+            if (pre_any) {
+                rows = false;                    // (the pre-history may end: both rows anew)
+            } else {
+                // a stored segment's second row becomes its first
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    GroupCharge &q = C[c];
+                    for (int k = 0; k < 3; ++k) {
+                        const double x = ringp[q.nx + k];
+                        q.g0[k] = q.kf < 0 ? q.g1[k] : x;
+                        q.g1[k] = x;
+                    }
+                    q.nx = later(q.nx);
+                }
+            }
+        }
+        const bool stop = s_stop[nstep & 1] != 0u;
+        wab = wab + hdt * (y1 * Ec + vn * Ee);
+        wra = wra + hdtl * (y2 * y2 + an * an);
+        if (--togo == 0) {
+            togo = out.stride;
+            const double en = run_energy(w2, eh, dn, vn);
+            if (po) {
+                *po = role < 2 ? dv : role == 2 ? en : Ee;
+                po += out.n_dip;
+            }
+            if (sums && pw) {
+                *pw = role == 0 ? wab : wra;
+                pw += out.n_dip;
+            }
+        }
+        y0 = dn;
+        y1 = vn;
+        y2 = an;
+        Ec = Ee;
+        if (stop) break;
+    }
+    if (live && th == 0 && sub == 0) {
+        Ecur[me] = Ec;
+        Wab[me] = wab;
+        Wra[me] = wra;
+    }
+    if (err) atomicOr(&s_err, err);
+    __syncthreads();
+    if (state) {
+        double *sr = state + state_ring_off(i0, ring);
+        for (int64_t k = tid; k < ring_all; k += threads) sr[k] = ringp[k];
+        const int64_t oe = state_ecur_off(out.n_dip, ring), ow = state_w_off(out.n_dip, ring);
+        for (int i = tid; i < n; i += threads) {
+            state[oe + i0 + i] = Ecur[i];
+            state[ow + 2 * (i0 + i)] = Wab[i];
+            state[ow + 2 * (i0 + i) + 1] = Wra[i];
+        }
+    }
+    if (tid == 0 && s_err) atomicOr(d_err, s_err);
+}
+
+// ---------------------------------------------------------------------------
 // Large instances: one workgroup per target dipole, one launch per step.
 // The step index comes from a device counter (advanced by step_advance_kernel)
 // so that a captured sequence of steps can be replayed.  Block b advances dipole
@@ -1790,10 +2136,10 @@ static hipError_t launch_lo(bool ring_lds, bool moving, bool mixed, dim3 grid, s
     return hipGetLastError();
 }
 
-int dipole_small_max_n() { return SMALL_MAX_N; }
+int dipole_kind_max_n(int kind) { return kind == 0 ? SMALL_MAX_N : kind == 1 ? GROUP8_MAX_N : GROUP_MAX_N; }
 
 hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, const int32_t *d_list, int n_list,
-                                   int max_n, bool ring_lds, const int64_t *d_ring_off, double *d_ring_global,
+                                   int min_n, int max_n, bool ring_lds, const int64_t *d_ring_off, double *d_ring_global,
                                    int ring, int64_t steps, double dt, double max_vel, int max_iter,
                                    const RunOut &out, bool moving, bool mixed, double *d_state, bool resume,
                                    uint32_t *d_err, hipStream_t s)
@@ -1801,13 +2147,28 @@ hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, co
     if (n_list <= 0) return hipSuccess;
     const size_t shmem = (size_t)ring_lds_bytes(max_n, ring_lds ? ring : 0);
     const dim3 grid((unsigned)n_list);
-    if (ring_lds && !moving && max_n <= dipole_small_max_n()) {
-        if (mixed)
-            hipLaunchKernelGGL(lo_small_kernel<true>, grid, dim3(64), shmem, s, d_dev, d_off, d_list, ring, steps, dt,
-                               max_vel, max_iter, out, d_state, resume ? 1 : 0, d_err);
-        else
-            hipLaunchKernelGGL(lo_small_kernel<false>, grid, dim3(64), shmem, s, d_dev, d_off, d_list, ring, steps, dt,
-                               max_vel, max_iter, out, d_state, resume ? 1 : 0, d_err);
+    // more than the default 64 KB of dynamic LDS is asked for per kernel
+    auto roomy = [&](auto kernel) {
+        return shmem <= 64 * 1024 ? hipSuccess
+                                  : hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                        (int)shmem);
+    };
+    hipError_t e = hipSuccess;
+    if (ring_lds && !moving && min_n > SMALL_MAX_N && max_n <= GROUP_MAX_N) {
+        const dim3 block((unsigned)group_threads(max_n));
+        with_flags(mixed, group_lg(max_n) == 3, [&](auto mx, auto eight) {
+            auto kernel = lo_group_kernel<decltype(mx)::value, decltype(eight)::value ? 3 : 4>;
+            if ((e = roomy(kernel)) != hipSuccess) return;
+            hipLaunchKernelGGL(kernel, grid, block, shmem, s, d_dev, d_off, d_list, ring, steps, dt, max_vel, max_iter,
+                               out, d_state, resume ? 1 : 0, d_err);
+        });
+        return e != hipSuccess ? e : hipGetLastError();
+    }
+    if (ring_lds && !moving && max_n <= SMALL_MAX_N) {
+        auto kernel = mixed ? lo_small_kernel<true> : lo_small_kernel<false>;
+        if ((e = roomy(kernel)) != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, grid, dim3(64), shmem, s, d_dev, d_off, d_list, ring, steps, dt, max_vel, max_iter,
+                           out, d_state, resume ? 1 : 0, d_err);
         return hipGetLastError();
     }
     if (max_n <= 8)
