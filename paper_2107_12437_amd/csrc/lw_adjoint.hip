@@ -334,16 +334,14 @@ __device__ __forceinline__ void charge_grad(const SrcRec *__restrict__ Rc, int n
 // Lanes 0..31 get a's sum with lane + 32, lanes 32..63 b's with lane - 32.
 __device__ __forceinline__ double fold32(double a, double b)
 {
-    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    lane_swap<32>(a, b);
+    return a + b;
 }
 // Rows 0 and 2 of 16 lanes get a's sums of rows 0 + 1 and 2 + 3, rows 1 and 3 b's.
 __device__ __forceinline__ double fold16(double a, double b)
 {
-    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    lane_swap<16>(a, b);
+    return a + b;
 }
 // x of the lane that the DPP control names (rotations within a row of 16).
 template <int CTRL> __device__ __forceinline__ double turn(double x)

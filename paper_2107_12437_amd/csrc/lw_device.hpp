@@ -23,6 +23,26 @@ enum { F_TOTAL = 0, F_COULOMB = 1, F_RADIATION = 2 };
 enum { FLAG_MASKED = 1u, FLAG_NOCONV = 2u };
 enum { OUT_PHI = 1, OUT_A = 2, OUT_E = 4, OUT_B = 8, OUT_S = 16 };
 
+// Exchanges a of the lanes whose index has bit K (16 or 32) with b of the lanes K below them:
+// one v_permlane swap per 32-bit half.  (A host-only build compiles the device pass for
+// a default architecture without these instructions, hence the second form.)
+template <int K> __device__ __forceinline__ void lane_swap(double &a, double &b)
+{
+#if __has_builtin(__builtin_amdgcn_permlane32_swap) && __has_builtin(__builtin_amdgcn_permlane16_swap)
+    auto swap = [](int x, int y) {
+        if constexpr (K == 32) return __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+        else return __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    };
+    const auto lo = swap(__double2loint(a), __double2loint(b)), hi = swap(__double2hiint(a), __double2hiint(b));
+    a = __hiloint2double((int)hi[0], (int)lo[0]);
+    b = __hiloint2double((int)hi[1], (int)lo[1]);
+#else
+    const double from_b = __shfl_xor(b, K, 64), from_a = __shfl_xor(a, K, 64);
+    if (threadIdx.x & K) a = from_b;
+    else b = from_a;
+#endif
+}
+
 // Per (time, charge) source record, written by the preparation kernel and read
 // wave-uniformly (scalar loads) by the field kernels.
 struct alignas(16) SrcRec {

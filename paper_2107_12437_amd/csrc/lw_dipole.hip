@@ -1057,11 +1057,8 @@ constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141;
 // x of lanes 0..31 and of lanes 32..63, each in both halves
 __device__ __forceinline__ void both_halves(double x, double &low, double &high)
 {
-    const unsigned lo = (unsigned)__double2loint(x), hi = (unsigned)__double2hiint(x);
-    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    low = __hiloint2double((int)b[0], (int)a[0]);
-    high = __hiloint2double((int)b[1], (int)a[1]);
+    low = high = x;
+    lane_swap<32>(low, high);
 }
 
 template <bool MIXED>
