@@ -686,7 +686,8 @@ lw_status lw_fields_vjp(lw_ctx *ctx, const lw_traj *h_charges, int32_t n_charges
 // Validation of an oscillator run's arguments and its history depth: the ring
 // of stored steps covers the longest retarded time.
 static lw_status run_geometry(const char *who, const lw_dipole *h_dip, int32_t n_dip, const int32_t *h_inst_off,
-                              int32_t n_inst, double dt, int64_t steps, const lw_run_opts *opts, int *ring_out)
+                              int32_t n_inst, double dt, int64_t steps, const lw_run_opts *opts, int *ring_out,
+                              double *light_out = nullptr)
 {
     const std::string w = who;
     if (!opts || !h_dip || !h_inst_off) return fail(LW_E_INVALID, w + ": null argument");
@@ -767,6 +768,7 @@ static lw_status run_geometry(const char *who, const lw_dipole *h_dip, int32_t n
         ring = opts->ring_depth;
     }
     *ring_out = ring;
+    if (light_out) *light_out = max_sep / C_LIGHT / dt;      // longest light time, in steps
     return LW_OK;
 }
 
@@ -894,7 +896,8 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
 {
     if (!ctx || !opts || !h_dip || !h_inst_off || !d_moment) return fail(LW_E_INVALID, "lw_dipole_run: null argument");
     int ring = 0;
-    lw_status gst = run_geometry("lw_dipole_run", h_dip, n_dip, h_inst_off, n_inst, dt, steps, opts, &ring);
+    double light = 0.0;
+    lw_status gst = run_geometry("lw_dipole_run", h_dip, n_dip, h_inst_off, n_inst, dt, steps, opts, &ring, &light);
     if (gst != LW_OK) return gst;
     if (resume && !d_state) return fail(LW_E_INVALID, "lw_dipole_run: resume needs a run state");
     if (d_state && n_state < lw::state_doubles(n_dip, ring))
@@ -975,17 +978,46 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     }
     const size_t n_tgt = tgt.size();
 
+    // enough pairs a step to be bound by their throughput: units of targets x sources.  us per
+    // step, FP64, a wave per target -> units: 16 instances of 160 (0.41 M pairs, a chain of
+    // two launches) 27.5 -> 30.7, of 200 (0.64 M) 35.8 -> 31.4; one of 1,100 51.6 -> 40.9, of 3,000
+    // 235 -> 177; 250 of 64 52 -> 38, 2,000 of 24 (1.15 M) 88 -> 86
+    lw::TilePlan tiles;
+    std::vector<lw::TileUnit> units;
+    size_t n_part = 0;
+    if (!moving && n_tgt > 1024) {
+        double pairs = 0.0;
+        for (int32_t n : tgt_n) pairs += n;
+        lw::tile_shape(light, &tiles.rows, &tiles.tile);
+        if (tiles.tile > 0 && pairs >= 6e5) {
+            const int T = lw::tile_targets();
+            auto split = [&](int chunk) {
+                units.clear();
+                for (size_t b = 0; b < n_tgt; b += (size_t)tgt_n[b])
+                    for (int t0 = 0; t0 < tgt_n[b]; t0 += T)
+                        for (int s0 = 0; s0 < tgt_n[b]; s0 += chunk)
+                            units.push_back({(int32_t)b, tgt_lo[b], tgt_n[b], t0, s0, std::min(s0 + chunk, (int)tgt_n[b])});
+                tiles.chunk = chunk;
+                n_part = 2 * n_tgt * (size_t)((tgt_n[0] + chunk - 1) / chunk);
+            };
+            split(16);
+            for (int chunk = 32; chunk <= 128 && units.size() > 8192; chunk *= 2) split(chunk);
+        }
+    }
+
     const size_t in_bytes = align_up(sizeof(lw_dipole) * (size_t)n_dip, 256);
     const size_t off_bytes = align_up(sizeof(int32_t) * (size_t)(n_inst + 1), 256);
     const size_t list_bytes = align_up(sizeof(int32_t) * (n_listed + 1), 256);
     const size_t t32_bytes = align_up(sizeof(int32_t) * (n_tgt + 1), 256);
     const size_t t64_bytes = align_up(sizeof(int64_t) * (n_tgt + 1), 256);
-    const size_t stage_bytes = in_bytes + off_bytes + list_bytes + 3 * t32_bytes + t64_bytes;
+    const size_t unit_bytes = align_up(sizeof(lw::TileUnit) * units.size(), 256);
+    const size_t stage_bytes = in_bytes + off_bytes + list_bytes + 3 * t32_bytes + t64_bytes + unit_bytes;
     const size_t dev_bytes = align_up(lw::dip_dev_bytes(n_dip), 256);
     const size_t ecur_bytes = align_up(sizeof(double) * 3 * (size_t)n_dip, 256);   // E_d(t_n), then 2 energy sums
     const size_t step_bytes = 256;
     const size_t ring_bytes = d_state ? 256 : align_up(sizeof(double) * (size_t)std::max<int64_t>(ring_doubles, 1), 256);
-    lw_status st = ensure_work(ctx, stage_bytes + dev_bytes + ecur_bytes + step_bytes + ring_bytes, s);
+    const size_t part_bytes = align_up(sizeof(double) * n_part, 256);
+    lw_status st = ensure_work(ctx, stage_bytes + dev_bytes + ecur_bytes + step_bytes + part_bytes + ring_bytes, s);
     if (st != LW_OK) return st;
     // the previous stepped run's graph is released once the stream has passed it
     if (ctx->graph_exec || ctx->graph) {
@@ -1013,6 +1045,8 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     std::copy(tgt_n.begin(), tgt_n.end(), (int32_t *)(stage + o));
     o += t32_bytes;
     std::copy(tgt_base.begin(), tgt_base.end(), (int64_t *)(stage + o));
+    o += t64_bytes;
+    std::copy(units.begin(), units.end(), (lw::TileUnit *)(stage + o));
     char *work = (char *)ctx->d_work;
     st = upload(ctx, work, stage_bytes, s);
     if (st != LW_OK) return st;
@@ -1031,6 +1065,9 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     o += t32_bytes;
     const int64_t *d_tgt_base = (const int64_t *)(work + o);
     o += t64_bytes;
+    tiles.units = (const lw::TileUnit *)(work + o);
+    tiles.n_units = (int)units.size();
+    o += unit_bytes;
     lw::DipDev *d_dev = (lw::DipDev *)(work + o);
     o += dev_bytes;
     double *d_Ecur = (double *)(work + o);
@@ -1038,6 +1075,8 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     o += ecur_bytes;
     int64_t *d_step = (int64_t *)(work + o);
     o += step_bytes;
+    tiles.part = (double *)(work + o);
+    o += part_bytes;
     double *d_ring = (double *)(work + o);
     if (d_state) {
         // the stepped path works in the run state itself
@@ -1088,8 +1127,8 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
         const int chunk = 256;
         LW_HIP(lw::launch_dipole_steps(d_dev, d_tgt, d_tgt_lo, d_tgt_n, d_tgt_base, (int)n_tgt, d_ring, d_Ecur, d_W,
                                        d_step, ring, steps, dt, max_vel, max_iter, out, moving, mixed,
-                                       resume ? d_state : nullptr, ctx->d_err, chunk, s, ctx->capture, &ctx->graph,
-                                       &ctx->graph_exec));
+                                       resume ? d_state : nullptr, ctx->d_err, chunk, tiles, s, ctx->capture,
+                                       &ctx->graph, &ctx->graph_exec));
         LW_HIP(hipEventRecord(ctx->graph_done, s));
     }
     for (int k = 0; k < KINDS; ++k)

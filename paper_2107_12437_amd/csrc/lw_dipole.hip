@@ -19,6 +19,8 @@
 // time inside the instance, so step n+1 overwrites a slot no retarded time can
 // reach any more.
 #include <math.h>
+#include <algorithm>
+#include <cmath>
 
 #include "lw_device.hpp"
 #include "lw_dipole.hpp"
@@ -1968,6 +1970,225 @@ __global__ __launch_bounds__(256, 4) void lo_wave_kernel(const DipDev *__restric
     if (err) atomicOr(d_err, err);
 }
 
+// ---------------------------------------------------------------------------
+// Many fixed targets in instances large enough to share sources: lo_wave_kernel's drives
+// with a lane per target.  That kernel is bound by its row gathers as much as by its
+// arithmetic: 64 sources' rows lie in 64 cache lines per load, and the texture unit takes
+// one line a cycle (557 line accesses against 445 VALU instructions per wave and round;
+// unit 71 % busy, VALU 61 %).  Here a workgroup stages the sample window of TILE sources,
+// every row any light time of the call can reach, in LDS by wide loads, once for up to
+// 128 targets, and the lanes gather from LDS; the source is uniform, so its constants come
+// by scalar loads, and the rows before t = 0 are staged as what they are.  A window's rows
+// are padded to an odd count: 6 dwords a row put 64 lanes' rows on 32 banks.
+// A unit is 128 targets x `chunk` sources of one instance; its waves are two target
+// halves x two source phases (64 targets or fewer: four phases) and leave one partial sum
+// per target and stage, which lo_finish_kernel adds in order and integrates.
+// 64 clusters of 2 to 975 dipoles, FP64: 130 us per step there, 91 here and 4 in
+// lo_finish_kernel (VALU-issue bound, 419 instructions per source and step; loads of the
+// window one at a time: 102).
+// ---------------------------------------------------------------------------
+constexpr int TILE_TARGETS = 128;
+
+// One source's both stage drives from its staged window (row r is step nstep - (R-1) + r).
+template <bool DIFF>
+__device__ __forceinline__ bool tile_drive(const SmallK &c, const double *win, int R, const DipLds &Si, const DipLds &Sj,
+                                           double kq, double inv_dt, int64_t nstep, double &e_half, double &e_full)
+{
+    const double X[3] = {Si.ox, Si.oy, Si.oz};
+    const PairGeo P = pair_geo(X, Si, Sj);
+    const double w = P.L * (INV_C * inv_dt);
+    const double fh = floor(0.5 - w), ff = floor(1.0 - w);
+    const int kh = (int)fh, idx = R - 1 + kh;
+    bool ok = ff < 0.0 && idx >= 0;
+    const int next = ff != fh ? 1 : 0;              // (by half a step: the same segment or the next)
+    const double *p = win + 3 * min(max(idx, 0), R - 2), *q = p + 3 * next;
+    double r0[3] = {p[0], p[1], p[2]}, r1[3] = {p[3], p[4], p[5]};
+    double s0[3] = {q[0], q[1], q[2]}, s1[3] = {q[3], q[4], q[5]};
+    if (nstep < R) {
+        // a segment that ends at t = 0 is static throughout
+        if (nstep + kh == -1) {
+            for (int k = 0; k < 3; ++k) r1[k] = r0[k];
+        }
+        if (nstep + kh + next == -1) {
+            for (int k = 0; k < 3; ++k) s1[k] = s0[k];
+        }
+    }
+    const double mu = P.sD * P.iL, muI = P.sI * P.iL;
+    const double uh = 0.5 - w - fh, uf = 1.0 - w - ff, kl = kq * (P.iL * P.iL);
+    double hp, hm, fp, fm;
+    ok = small_charge<DIFF>(c, mu, muI, w, uh, Sj.cfp, kl, P, r0, r1, hp) && ok;
+    ok = small_charge<DIFF>(c, mu, muI, w, uh, Sj.cfm, -kl, P, r0, r1, hm) && ok;
+    ok = small_charge<DIFF>(c, mu, muI, w, uf, Sj.cfp, kl, P, s0, s1, fp) && ok;
+    ok = small_charge<DIFF>(c, mu, muI, w, uf, Sj.cfm, -kl, P, s0, s1, fm) && ok;
+    e_half = hp + hm;
+    e_full = fp + fm;
+    return ok;
+}
+
+template <bool MIXED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void lo_tile_kernel(
+    const DipDev *__restrict__ dev, const TileUnit *__restrict__ units, const int64_t *__restrict__ ring_base, int n_tgt,
+    const double *__restrict__ ring, double *__restrict__ part, const int64_t *__restrict__ step_ctr, int kstep,
+    int ring_depth, double dt, int R, int tile, int chunk, int max_iter, int n_dip, const double *__restrict__ soa,
+    uint32_t *__restrict__ d_err)
+{
+    extern __shared__ double win[];                  // [tile][R][3], 8 doubles of padding
+    const TileUnit U = units[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t nstep = *step_ctr + kstep;
+    const double *rp = ring + ring_base[U.b0];
+    const Hist H{rp, U.n, ring_depth - 1, dt, 1.0 / dt};
+    const int halves = U.n - U.t0 > 64 ? 2 : 1;
+    const int phase = wave / halves, phases = 4 / halves;
+    const int i = U.t0 + (wave % halves) * 64 + lane;
+    const bool live = i < U.n;
+    const DipLds Si = soa_lds(soa, n_dip, (uint32_t)(U.i0 + (live ? i : U.t0)));
+    const SmallK c = small_k<false>();
+    uint32_t err = 0u;
+    double acc0 = 0.0, acc1 = 0.0;
+    uint64_t left = 0u;
+    int round = 0;
+    for (int s = U.s0; s < U.s1; s += tile) {
+        const int here = min(tile, U.s1 - s);
+        __syncthreads();
+        // thread t: element t % (3 * here) of every row, rows t / (3 * here) and on
+        const int cols = 3 * here, rows_at_once = 256 / cols;
+        const int col = tid % cols, src = col / 3, q = col - 3 * src;
+        if (tid < cols * rows_at_once) {
+            const double pre = q == 0 ? dev[U.i0 + s + src].d0 : 0.0;
+            double *dst = win + src * R * 3 + q;
+            // in batches, so that a batch's loads are in flight together
+            constexpr int BATCH = 8;
+            for (int r = tid / cols; r < R; r += BATCH * rows_at_once) {
+                double v[BATCH];
+#pragma unroll
+                for (int u = 0; u < BATCH; ++u) {
+                    const int64_t k = nstep - (R - 1) + min(r + u * rows_at_once, R - 1);
+                    v[u] = k < 0 ? pre : rp[((int64_t)(k & H.mask) * U.n + s) * 3 + col];
+                }
+#pragma unroll
+                for (int u = 0; u < BATCH; ++u)
+                    if (r + u * rows_at_once < R) dst[3 * (r + u * rows_at_once)] = v[u];
+            }
+        }
+        __syncthreads();
+        for (int m = phase; m < here; m += phases, ++round) {
+            const int j = s + m;
+            const DipDev &D = dev[U.i0 + j];
+            const DipLds Sj = dip_lds(D);
+            double eh, ef;
+            const bool ok = tile_drive<MIXED>(c, win + m * R * 3, R, Si, Sj, D.q * K_COUL, H.inv_dt, nstep, eh, ef);
+            if (!ok && live && j != i) left |= (uint64_t)1 << round;
+            const bool add = ok && j != i;
+            acc0 += add ? eh : 0.0;
+            acc1 += add ? ef : 0.0;
+        }
+    }
+    // the sources tile_drive does not take, by the general solvers: round r of this wave is
+    // source (r / per_tile) * tile + phase + (r % per_tile) * phases
+    const int per_tile = (tile - phase + phases - 1) / phases;
+    while (left) {
+        const int r = __ffsll((unsigned long long)left) - 1;
+        left &= left - 1u;
+        const int j = U.s0 + (r / per_tile) * tile + phase + (r % per_tile) * phases;
+        double eh, ef;
+        drive_stages_general<MIXED>(H, Si, dip_lds(dev[U.i0 + j]), j, dev[U.i0 + j].q * K_COUL, nstep, max_iter, err, eh,
+                                    ef);
+        acc0 += eh;
+        acc1 += ef;
+    }
+    // the phases' sums, in order
+    __syncthreads();
+    win[tid] = acc0;
+    win[256 + tid] = acc1;
+    __syncthreads();
+    if (phase == 0 && live) {
+        for (int k = 1; k < phases; ++k) {
+            acc0 += win[tid + 64 * halves * k];
+            acc1 += win[256 + tid + 64 * halves * k];
+        }
+        double *out = part + (int64_t)(U.s0 / chunk) * 2 * n_tgt + U.b0 + i;
+        out[0] = acc0;
+        out[n_tgt] = acc1;
+    }
+    if (err) atomicOr(d_err, err);
+}
+
+// A target's state at the step's start.
+struct TargetState {
+    double y0, y1, a0, Ec, W0, W1;
+};
+__device__ __forceinline__ TargetState target_state(const Hist &H, int gi, int i, const double *Ecur, const double *W,
+                                                    int64_t nstep)
+{
+    const double *h = H.ring + ((int64_t)(nstep & H.mask) * H.n + i) * 3;
+    return {h[0], h[1], h[2], Ecur[gi], W[2 * gi], W[2 * gi + 1]};
+}
+
+// The end of a target's step: RK4 with the drives at t_n + dt/2 and t_n + dt, the new
+// sample, the energy sums and the output row.
+__device__ __forceinline__ void finish_target(const DipDev &D, const TargetState &S, int gi, int i, const Hist &H, double *ring, double *Ecur, double *W,
+                                              int64_t nstep, int64_t n0, double Em, double Ee, double max_vel,
+                                              const RunOut &out, uint32_t &err)
+{
+    const double w2 = D.omega0 * D.omega0;
+    double dn, vn;
+    rk4_step(D.rk, S.y0, S.y1, S.Ec, Em, Ee, dn, vn);
+    const double an = D.f * Ee - D.gamma0 * vn - w2 * dn;
+    double *hn = ring + ((int64_t)((nstep + 1) & H.mask) * H.n + i) * 3;
+    hn[0] = dn;
+    hn[1] = vn;
+    hn[2] = an;
+    Ecur[gi] = Ee;
+    if (!(isfinite(dn) && isfinite(vn) && isfinite(an))) err |= ERR_NONFINITE;
+    if (max_vel > 0.0 && D.mspeed + D.vfac * fabs(vn) > max_vel) err |= ERR_VELOCITY;
+    // energy bookkeeping (Sec. 2.5), trapezoid rule over the step
+    const double wa = S.W0 + 0.5 * H.dt * (S.y1 * S.Ec + vn * Ee);
+    const double wr = S.W1 + 0.5 * H.dt * K_LARMOR * (S.a0 * S.a0 + an * an);
+    W[2 * gi] = wa;
+    W[2 * gi + 1] = wr;
+    const int64_t row = out_row(nstep + 1 - n0, out.stride);
+    if (row >= 0) put_row(out, row, gi, dn, vn, run_energy(w2, D.ehalf, dn, vn), Ee, wa, wr);
+}
+
+// 64 targets a workgroup; its four waves sum the partials of a target in four runs.
+__global__ __launch_bounds__(256) void lo_finish_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
+                                                        const int32_t *__restrict__ tgt_lo,
+                                                        const int32_t *__restrict__ tgt_n,
+                                                        const int64_t *__restrict__ ring_base, int n_tgt, double *ring,
+                                                        double *Ecur, double *W, const int64_t *__restrict__ step_ctr,
+                                                        int kstep, int ring_depth, double dt, double max_vel, int chunk,
+                                                        RunOut out, const double *__restrict__ part,
+                                                        uint32_t *__restrict__ d_err)
+{
+    __shared__ double sums[2][256];
+    const int tid = threadIdx.x, b = blockIdx.x * 64 + (tid & 63), run = tid >> 6;
+    const int bb = min(b, n_tgt - 1);
+    const int gi = tgt[bb], i0 = tgt_lo[bb], n = tgt_n[bb];
+    double Em = 0.0, Ee = 0.0;
+    const int splits = (n + chunk - 1) / chunk;
+#pragma unroll 4
+    for (int s = run; s < splits; s += 4) {
+        const double *p = part + (int64_t)s * 2 * n_tgt + bb;
+        Em += p[0];
+        Ee += p[n_tgt];
+    }
+    sums[0][tid] = Em;
+    sums[1][tid] = Ee;
+    const int64_t nstep = *step_ctr + kstep, n0 = step_ctr[1];
+    const Hist H{ring + ring_base[bb], n, ring_depth - 1, dt, 1.0 / dt};
+    const TargetState S = target_state(H, gi, gi - i0, Ecur, W, nstep);
+    __syncthreads();
+    if (run != 0 || b >= n_tgt) return;
+    for (int r = 1; r < 4; ++r) {
+        Em += sums[0][64 * r + tid];
+        Ee += sums[1][64 * r + tid];
+    }
+    uint32_t err = 0u;
+    finish_target(dev[gi], S, gi, gi - i0, H, ring + ring_base[b], Ecur, W, nstep, n0, Em, Ee, max_vel, out, err);
+    if (err) atomicOr(d_err, err);
+}
+
 __global__ void step_advance_kernel(int64_t *step_ctr, int64_t delta)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) *step_ctr += delta;
@@ -2027,6 +2248,27 @@ hipError_t launch_state_header(double *d_state, int ring, int n_dip, int64_t ste
     return hipGetLastError();
 }
 
+static size_t tile_lds_bytes(int rows, int tile)
+{
+    return std::max(sizeof(double) * (3 * (size_t)rows * tile + 8), sizeof(double) * 512);
+}
+
+// Window rows and tile for light times of up to `steps` steps, or tile = 0 where no tile of
+// at least 4 sources fits a third of a CU's LDS (light times beyond 550 steps).
+void tile_shape(double steps, int *rows, int *tile)
+{
+    *tile = 0;
+    *rows = 0;
+    if (!(steps < 1e6)) return;
+    *rows = ((int)std::ceil(steps) + 3) | 1;
+    for (int t = 16; t >= 4; t /= 2)
+        if (tile_lds_bytes(*rows, t) <= 53 * 1024) {
+            *tile = t;
+            return;
+        }
+}
+int tile_targets() { return TILE_TARGETS; }
+
 // Calls fn(std::integral_constant<bool, a>, std::integral_constant<bool, b>).
 template <typename Fn> static void with_flags(bool a, bool b, Fn &&fn)
 {
@@ -2043,8 +2285,8 @@ hipError_t launch_dipole_steps(const DipDev *d_dev, const int32_t *d_tgt, const 
                                const int64_t *d_ring_base, int n_tgt, double *d_ring, double *d_Ecur, double *d_W,
                                int64_t *d_step, int ring, int64_t steps, double dt, double max_vel, int max_iter,
                                const RunOut &out, bool moving, bool mixed, const double *d_resume, uint32_t *d_err,
-                               int graph_chunk, hipStream_t s, hipStream_t cap, hipGraph_t *graph_out,
-                               hipGraphExec_t *exec_out)
+                               int graph_chunk, const TilePlan &tiles, hipStream_t s, hipStream_t cap,
+                               hipGraph_t *graph_out, hipGraphExec_t *exec_out)
 {
     constexpr int B = 256;
     if (n_tgt <= 0) return hipSuccess;
@@ -2053,6 +2295,16 @@ hipError_t launch_dipole_steps(const DipDev *d_dev, const int32_t *d_tgt, const 
     const int wide = n_tgt <= 1024 ? 1 : 0;
     const double *soa = dip_soa(const_cast<DipDev *>(d_dev), out.n_dip);
     auto step = [&](hipStream_t q, int k, int init) {
+        if (tiles.n_units > 0 && !init) {
+            hipLaunchKernelGGL(mixed ? lo_tile_kernel<true> : lo_tile_kernel<false>, dim3((unsigned)tiles.n_units), block,
+                               tile_lds_bytes(tiles.rows, tiles.tile), q, d_dev, tiles.units, d_ring_base, n_tgt, d_ring,
+                               tiles.part, d_step, k, ring, dt, tiles.rows, tiles.tile, tiles.chunk, max_iter, out.n_dip,
+                               soa, d_err);
+            hipLaunchKernelGGL(lo_finish_kernel, dim3((unsigned)((n_tgt + 63) / 64)), block, 0, q, d_dev, d_tgt,
+                               d_tgt_lo, d_tgt_n, d_ring_base, n_tgt, d_ring, d_Ecur, d_W, d_step, k, ring, dt, max_vel,
+                               tiles.chunk, out, tiles.part, d_err);
+            return;
+        }
         if (!wide && !init && !moving) {
             const dim3 g4((unsigned)((n_tgt + 3) / 4));
             if (mixed)

@@ -95,6 +95,21 @@ hipError_t launch_state_rows(const DipDev *d_dev, const int32_t *d_off, int n_in
 // After a run: the state's header (steps taken, ring, n_dip).
 hipError_t launch_state_header(double *d_state, int ring, int n_dip, int64_t steps, bool resume, hipStream_t s);
 
+// The stepped path's split into units of targets x sources (lo_tile_kernel); n_units 0: not
+// taken.  part: max splits x 2 x n_tgt doubles.
+struct TileUnit {
+    int32_t b0, i0, n;       // the instance's first target, first dipole and size
+    int32_t t0, s0, s1;      // first target and the sources, within the instance
+};
+struct TilePlan {
+    const TileUnit *units = nullptr;
+    int n_units = 0;
+    double *part = nullptr;
+    int rows = 0, tile = 0, chunk = 0;
+};
+void tile_shape(double steps, int *rows, int *tile);
+int tile_targets();
+
 // moving: some dipole's origin moves (kernels with the moving-origin code).
 // mixed: FP32 pair fields (FP64 retarded times, state and sums).
 // Large instances: one launch per step (captured into a replayed graph when
@@ -107,8 +122,8 @@ hipError_t launch_dipole_steps(const DipDev *d_dev, const int32_t *d_tgt, const 
                                const int64_t *d_ring_base, int n_tgt, double *d_ring, double *d_Ecur, double *d_W,
                                int64_t *d_step, int ring, int64_t steps, double dt, double max_vel, int max_iter,
                                const RunOut &out, bool moving, bool mixed, const double *d_resume, uint32_t *d_err,
-                               int graph_chunk, hipStream_t s, hipStream_t cap, hipGraph_t *graph_out,
-                               hipGraphExec_t *exec_out);
+                               int graph_chunk, const TilePlan &tiles, hipStream_t s, hipStream_t cap,
+                               hipGraph_t *graph_out, hipGraphExec_t *exec_out);
 
 // Pieces of the oscillator adjoint (lw_dipole_adjoint.hip), whose sweep runs
 // over segments of steps; `ring` is the depth of the history and of its
