@@ -520,8 +520,8 @@ lw_status check_fields_args(const char *who, lw_ctx *ctx, const lw_traj *h_charg
     return LW_OK;
 }
 
-// Stages charges and times and enqueues the record preparation; returns the
-// device records.  extra_bytes of workspace follow the records (at *d_extra).
+// Enqueues the record preparation from the charges and times, as launch arguments
+// where they fit, else through the staging buffer; returns the device records.  extra_bytes of workspace follow the records (at *d_extra).
 lw_status stage_records(lw_ctx *ctx, const lw_traj *h_charges, int32_t n_charges, const double *h_times,
                         int32_t n_times, uint32_t *d_flags, int64_t n_pts, size_t extra_bytes, hipStream_t s,
                         lw::SrcRec **d_recs_out, void **d_extra)
@@ -531,17 +531,21 @@ lw_status stage_records(lw_ctx *ctx, const lw_traj *h_charges, int32_t n_charges
     const size_t rec_bytes = align_up(lw::src_rec_bytes() * (size_t)n_charges * (size_t)n_times, 256);
     lw_status st = ensure_work(ctx, ch_bytes + tm_bytes + rec_bytes + extra_bytes, s);
     if (st != LW_OK) return st;
-    st = acquire_stage(ctx, ch_bytes + tm_bytes);
-    if (st != LW_OK) return st;
-    char *stage = (char *)ctx->h_stage;
-    std::memcpy(stage, h_charges, sizeof(lw_traj) * (size_t)n_charges);
-    std::memcpy(stage + ch_bytes, h_times, sizeof(double) * (size_t)n_times);
     char *work = (char *)ctx->d_work;
-    st = upload(ctx, work, ch_bytes + tm_bytes, s);
-    if (st != LW_OK) return st;
     lw::SrcRec *d_recs = (lw::SrcRec *)(work + ch_bytes + tm_bytes);
-    LW_HIP(lw::launch_prep((const lw_traj *)work, n_charges, (const double *)(work + ch_bytes), n_times, d_recs,
-                           d_flags, n_pts, s));
+    if (lw::prep_fits_args(n_charges, n_times)) {
+        LW_HIP(lw::launch_prep_args(h_charges, n_charges, h_times, n_times, d_recs, d_flags, n_pts, s));
+    } else {
+        st = acquire_stage(ctx, ch_bytes + tm_bytes);
+        if (st != LW_OK) return st;
+        char *stage = (char *)ctx->h_stage;
+        std::memcpy(stage, h_charges, sizeof(lw_traj) * (size_t)n_charges);
+        std::memcpy(stage + ch_bytes, h_times, sizeof(double) * (size_t)n_times);
+        st = upload(ctx, work, ch_bytes + tm_bytes, s);
+        if (st != LW_OK) return st;
+        LW_HIP(lw::launch_prep((const lw_traj *)work, n_charges, (const double *)(work + ch_bytes), n_times, d_recs,
+                               d_flags, n_pts, s));
+    }
     *d_recs_out = d_recs;
     if (d_extra) *d_extra = work + ch_bytes + tm_bytes + rec_bytes;
     return LW_OK;

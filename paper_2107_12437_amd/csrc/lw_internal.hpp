@@ -44,6 +44,10 @@ struct FieldLaunch {
 // retarded-solve / Lienard-Wiechert / superposition / store kernel.
 hipError_t launch_prep(const lw_traj *d_ch, int nch, const double *d_times, int nt, SrcRec *d_recs,
                        uint32_t *d_flags, int64_t npts, hipStream_t s);
+// The same from host memory, for inputs that fit the launch's arguments.
+bool prep_fits_args(int nch, int nt);
+hipError_t launch_prep_args(const lw_traj *h_ch, int nch, const double *h_times, int nt, SrcRec *d_recs,
+                            uint32_t *d_flags, int64_t npts, hipStream_t s);
 // d_hist non-null: the counting instance (one time per lane, 256 lanes) adds each
 // pair to the iteration histogram d_hist[ITER_BINS] (see fields_kernel).
 constexpr int ITER_BINS = LW_ITER_BINS, ITER_BIN_FALLBACK = LW_ITER_BIN_FALLBACK, ITER_BIN_NOCONV = LW_ITER_BIN_NOCONV;
