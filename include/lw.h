@@ -261,8 +261,8 @@ typedef struct {
     double max_vel;      /* charge speed limit, m/s (<= 0: c/100)                            */
     int32_t ring_depth;  /* stored steps per dipole (0: automatic, power of two)             */
     int32_t stepped_min_n; /* instances of at least this many dipoles (or whose history does
-                              not fit in LDS) advance one launch per step with one workgroup
-                              per dipole; smaller ones run whole in one workgroup
+                              not fit in LDS) advance one launch per step, spread over the
+                              chip; smaller ones run whole in one workgroup
                               (0: 16; LW_STEPPED_TUNE: the fastest threshold for the run's
                               shape class, timed on trial runs of its dipoles at the first
                               call (which then synchronises the stream) and cached like the

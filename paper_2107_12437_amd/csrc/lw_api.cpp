@@ -786,7 +786,7 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
 // two.  Cached in the context (and the LW_TUNE_CACHE file); otherwise each
 // threshold that splits the instances differently is timed on trial runs of
 // the call's own dipoles, and the fastest is kept.  A trial's per-step cost is
-// the difference of a 512-step and a 256-step run, so the per-call cost of
+// the difference of a 704-step and a 448-step run, so the per-call cost of
 // staging and graph capture drops out.  Trials write two rows of moments into
 // a context buffer and no run state; tuning synchronises the stream once.
 static lw_status tune_stepped(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_dip, const int32_t *h_inst_off,
@@ -836,7 +836,7 @@ static lw_status tune_stepped(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_dip
         if (hipMalloc((void **)&ctx->d_trial, need) != hipSuccess) return fail(LW_E_NOMEM, "tuner trial buffer");
         ctx->trial_cap = need;
     }
-    // The trials run the call's own dipoles for up to 512 steps, which may latch an
+    // The trials run the call's own dipoles for up to 704 steps, which may latch an
     // error (speed limit, history) that the call itself, if shorter, never meets:
     // the error word a caller has not read yet is saved, each candidate runs on a
     // cleared word, a candidate whose trials latched anything is dropped, and the
@@ -856,7 +856,7 @@ static lw_status tune_stepped(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_dip
         if (hipMemcpy(ctx->d_err, &zero_err, sizeof(uint32_t), hipMemcpyHostToDevice) != hipSuccess)
             st = fail(LW_E_HIP, "tuner error word");
         for (int r = 0; r < 2 && st == LW_OK; ++r) {
-            const int64_t n_steps = 256 << r;
+            const int64_t n_steps = 448 + 256 * r;     // (both replay the same graph, built once each)
             o.out_stride = n_steps;
             if (hipEventRecord(ev[0], s) != hipSuccess) st = fail(LW_E_HIP, "tuner timing");
             if (st == LW_OK)
@@ -982,18 +982,25 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     }
     const size_t n_tgt = tgt.size();
 
-    // enough pairs a step to be bound by their throughput: units of targets x sources.  us per
-    // step, FP64, a wave per target -> units: 16 instances of 160 (0.41 M pairs, a chain of
-    // two launches) 27.5 -> 30.7, of 200 (0.64 M) 35.8 -> 31.4; one of 1,100 51.6 -> 40.9, of 3,000
-    // 235 -> 177; 250 of 64 52 -> 38, 2,000 of 24 (1.15 M) 88 -> 86
+    // more than 1,024 fixed targets: by the wave rounds of 64 sources a step takes.  us per
+    // step, FP64, by a workgroup per target / a wave per target / units of targets x sources:
+    //   70 instances of 16 (1,120 rounds)  10.5 / 9.0 / 14.7    20 of 96 (3,840)  17.3 / 15.0 / 19.8
+    //   120 of 48 (5,760)                  47 / 23.3 / 18.4     16 of 200 (12,800) 35 / 32 / 25.4
+    // and where few targets have many sources each
+    //   8 of 200 (6,400)  17.2 / 19.2 / 20.0    2 of 540 (9,720)  22.0 / 27.6 / 25.2
+    //   1 of 1,100 (19,800, 1.2 M pairs)  34.6 / 48 / 32.9
     lw::TilePlan tiles;
     std::vector<lw::TileUnit> units;
     size_t n_part = 0;
     if (!moving && n_tgt > 1024) {
-        double pairs = 0.0;
-        for (int32_t n : tgt_n) pairs += n;
+        double pairs = 0.0, rounds = 0.0;
+        for (int32_t n : tgt_n) {
+            pairs += n;
+            rounds += (n + 62) / 64;
+        }
+        tiles.per_wave = !(n_tgt <= 2048 && rounds >= 4500.0 && pairs < 9e5);
         lw::tile_shape(light, &tiles.rows, &tiles.tile);
-        if (tiles.tile > 0 && pairs >= 6e5) {
+        if (tiles.per_wave && tiles.tile > 0 && rounds >= 5500.0) {
             const int T = lw::tile_targets();
             auto split = [&](int chunk) {
                 units.clear();

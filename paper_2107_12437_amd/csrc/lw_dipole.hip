@@ -2305,7 +2305,7 @@ hipError_t launch_dipole_steps(const DipDev *d_dev, const int32_t *d_tgt, const 
                                tiles.chunk, out, tiles.part, d_err);
             return;
         }
-        if (!wide && !init && !moving) {
+        if (tiles.per_wave && !init) {
             const dim3 g4((unsigned)((n_tgt + 3) / 4));
             if (mixed)
                 hipLaunchKernelGGL(lo_wave_kernel<true>, g4, block, 0, q, d_dev, d_tgt, d_tgt_lo, d_tgt_n, d_ring_base,

@@ -110,6 +110,7 @@ struct TilePlan {
     int n_units = 0;
     double *part = nullptr;
     int rows = 0, tile = 0, chunk = 0;
+    bool per_wave = false;   // without units: a wave per target, not a workgroup
 };
 void tile_shape(double steps, int *rows, int *tile);
 int tile_targets();
