@@ -1721,15 +1721,15 @@ __attribute__((amdgpu_waves_per_eu(2))) void lo_group_kernel(
 // ---------------------------------------------------------------------------
 
 
-template <int BLOCK, bool MOVING, bool MIXED>
-__global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
+template <int BLOCK, bool MOVING, bool MIXED, bool WIDE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WIDE ? 2 : 3))) void lo_step_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
                                                         const int32_t *__restrict__ tgt_lo,
                                                         const int32_t *__restrict__ tgt_n,
                                                         const int64_t *__restrict__ ring_base, double *__restrict__ ring,
                                                         double *__restrict__ Ecur, double *__restrict__ W,
                                                         const int64_t *__restrict__ step_ctr, int kstep,
                                                         int ring_depth, double dt, double max_vel, int max_iter,
-                                                        int init, int wide, RunOut out,
+                                                        int init, RunOut out,
                                                         const double *__restrict__ soa, uint32_t *__restrict__ d_err)
 {
     __shared__ double red[2][BLOCK / 64];
@@ -1747,13 +1747,13 @@ __global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict
     const int nth = init ? 1 : 2;
     // Lane layout.  A launch with many targets is throughput-bound: a lane
     // takes one source for both stage times (the fewest instructions per drive).
-    // A launch with few targets (`wide`: at most one workgroup per SIMD) is a
+    // A launch with few targets (WIDE: at most one workgroup per SIMD) is a
     // latency chain, and the shortest chain that fits the block wins: in FP64
     // one charge per lane (4 drives' worth of lanes per source), else one source
     // per (stage, lane); in the mixed form one source per (stage, lane).  Sources that
     // do not fit so take both stages in a lane (900 dipoles, mixed: 38.9 us per step
     // with a lane per stage).
-    const int layout = !wide ? 0 : (!MIXED && 2 * nth * M <= BLOCK) ? 2 : (nth * M <= BLOCK) ? 1 : 0;
+    const int layout = !WIDE ? 0 : (!MIXED && 2 * nth * M <= BLOCK) ? 2 : (nth * M <= BLOCK) ? 1 : 0;
     const int units = layout == 2 ? 2 * nth * M : (layout == 1 ? nth * M : M);
     // the target's own state (only this workgroup writes it, and only at its
     // end): when the last lane has no pair work it reads the state into LDS
@@ -1770,7 +1770,10 @@ __global__ __launch_bounds__(BLOCK) void lo_step_kernel(const DipDev *__restrict
         own[4] = W[2 * gi];
         own[5] = W[2 * gi + 1];
     }
-    const SmallK c = small_k<true>();
+    // (with many targets the constants sit in scalar registers and three waves share a
+    // SIMD: 10 instances of 160 15.2 us per step, 16.8 at two waves; with few the scalar
+    // moves would lengthen the chain, 4.4 against 4.05 us at 32 dipoles)
+    const SmallK c = small_k<WIDE>();
     double acc0 = 0.0, acc1 = 0.0;                   // stage t_n + dt/2 (or t = 0), stage t_n + dt
     if (layout == 0) {
         // a lane takes one source for both stage times
@@ -2292,7 +2295,7 @@ hipError_t launch_dipole_steps(const DipDev *d_dev, const int32_t *d_tgt, const 
     if (n_tgt <= 0) return hipSuccess;
     const dim3 grid((unsigned)n_tgt), block(B);
     // at most one workgroup per SIMD (256 CUs x 4): a latency-bound launch
-    const int wide = n_tgt <= 1024 ? 1 : 0;
+    const bool wide = n_tgt <= 1024;
     const double *soa = dip_soa(const_cast<DipDev *>(d_dev), out.n_dip);
     auto step = [&](hipStream_t q, int k, int init) {
         if (tiles.n_units > 0 && !init) {
@@ -2317,9 +2320,10 @@ hipError_t launch_dipole_steps(const DipDev *d_dev, const int32_t *d_tgt, const 
             return;
         }
         with_flags(moving, mixed, [&](auto mv, auto mx) {
-            hipLaunchKernelGGL((lo_step_kernel<B, decltype(mv)::value, decltype(mx)::value>), grid, block, 0, q,
-                               d_dev, d_tgt, d_tgt_lo, d_tgt_n, d_ring_base, d_ring, d_Ecur, d_W, d_step, k, ring, dt,
-                               max_vel, max_iter, init, wide, out, soa, d_err);
+            constexpr bool MV = decltype(mv)::value, MX = decltype(mx)::value;
+            hipLaunchKernelGGL((wide ? lo_step_kernel<B, MV, MX, true> : lo_step_kernel<B, MV, MX, false>), grid, block, 0,
+                               q, d_dev, d_tgt, d_tgt_lo, d_tgt_n, d_ring_base, d_ring, d_Ecur, d_W, d_step, k, ring, dt,
+                               max_vel, max_iter, init, out, soa, d_err);
         });
     };
     hipLaunchKernelGGL(step_start_kernel, dim3(1), dim3(1), 0, s, d_step, d_resume);
