@@ -37,13 +37,13 @@ FLOP_SOLVE_FP64 = 150
 # Vector ALU peak of MI355X for FP64 and for unpacked FP32: 256 CUs x 4 SIMDs
 # x 16 lanes x 2 flops (FMA) x 2.4 GHz.
 PEAK_VALU_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
-# HBM bytes per launch of fields_kernel<float, 2> on this workload from the profiler's
+# HBM bytes per launch of fields_kernel<float, 1> (float, 2: 681.8e6) on this workload from the profiler's
 # FETCH_SIZE (x2.0) and WRITE_SIZE (x1.0) counters, calibrated on a plain 1 GiB copy
 # (profiles/fields_kernel_mixed_grid512x512x64t.md).  Valid only for the kernel
 # sources and code-generation flags they were taken on; reported as null once
 # either changes.
-TRAFFIC_BYTES = 682.1e6
-TRAFFIC_SOURCES_SHA = "a857de27d0f7cbc7"
+TRAFFIC_BYTES = 682.0e6
+TRAFFIC_SOURCES_SHA = "15fe5b40b1ef66aa"
 # Algorithmic FP64 work per charge-pair drive of the oscillator step (one source
 # charge seen by one target dipole at one stage time), counted from the method's
 # definition: the retarded time on the interpolated history (30 flops, one
