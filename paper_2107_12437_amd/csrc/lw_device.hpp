@@ -686,24 +686,29 @@ __device__ __forceinline__ void orbit_taylor(F w1b, F w2b, F b2, F T2, F K, F a,
     }
 }
 
-// (cos, sin) of theta0 - a from (c0, s0) = (cos, sin) theta0, |a| <= 0.75: Taylor
-// terms through a^11 and a^12 (truncation below 2e-17), or for the mixed path
-// (SHORT) through a^9 and a^10 (below 1.1e-9, and 1.3e-11 for |a| <= 0.5, against
-// FP32 outputs).
+// (cos, sin) of theta0 - a from (c0, s0) = (cos, sin) theta0, |a| <= 0.75.  The polynomials'
+// lowest terms are Taylor's, the others those of least maximal error over the range
+// (Remez's exchange): sin through a^13 and cos through a^12 to 4.1e-17, for the mixed
+// path (SHORT) through a^9 and a^10 to 1.5e-12, against FP32 outputs.  (Taylor's own
+// coefficients through a^11 and a^12 leave 4e-12 at 0.75 and 2e-14 at 0.5.)
 template <bool SHORT>
 __device__ __forceinline__ void rot_phase(double c0, double s0, double a, double &c, double &s)
 {
     const double a2 = a * a;
     double sa, ca;
     if constexpr (SHORT) {
-        sa = fma_k(a2, 1.0 / 362880.0, -1.0 / 5040.0);
-        ca = fma_k(a2, -1.0 / 3628800.0, 1.0 / 40320.0);
+        sa = fma_k(fma_k(fma_k(a2, 0x1.6d0107747315cp-19, -0x1.a0100f79c206ep-13), a2, 0x1.111108c357014p-7), a2,
+                   -0x1.5555554c2328fp-3);
+        ca = fma_k(fma_k(fma_k(a2, -0x1.247e88251427ap-22, 0x1.a0129e2b6279ap-16), a2, -0x1.6c16baba0e016p-10), a2,
+                   0x1.5555555129dd0p-5);
     } else {
-        sa = fma_k(a2, fma_k(a2, -1.0 / 39916800.0, 1.0 / 362880.0), -1.0 / 5040.0);
-        ca = fma_k(a2, fma_k(a2, 1.0 / 479001600.0, -1.0 / 3628800.0), 1.0 / 40320.0);
+        sa = fma_k(fma_k(a2, 0x1.5db8f28b864f3p-33, -0x1.ae5ed1ace9646p-26), a2, 0x1.71de35e02ff18p-19);
+        sa = fma_k(fma_k(fma_k(sa, a2, -0x1.a01a019c5e2e3p-13), a2, 0x1.111111110f91fp-7), a2, -0x1.5555555555548p-3);
+        ca = fma_k(fma_k(a2, 0x1.1c0e6d755a142p-29, -0x1.27e0f99997faep-22), a2, 0x1.a019fc581f90fp-16);
+        ca = fma_k(fma_k(ca, a2, -0x1.6c16c168dbc4dp-10), a2, 0x1.5555555553e74p-5);
     }
-    sa = a * fma_k(a2, fma_k(a2, fma_k(a2, sa, 1.0 / 120.0), -1.0 / 6.0), 1.0);
-    ca = fma_k(a2, fma_k(a2, fma_k(a2, fma_k(a2, ca, -1.0 / 720.0), 1.0 / 24.0), -0.5), 1.0);
+    sa = a * fma(a2, sa, 1.0);
+    ca = fma(a2, fma(a2, ca, -0.5), 1.0);
     c = c0 * ca + s0 * sa;
     s = s0 * ca - c0 * sa;
 }

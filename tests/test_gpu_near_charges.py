@@ -1,0 +1,85 @@
+"""Grid fields close to the charges, where the retarded-time problem is quasi-static, and at
+high speeds, where it is far from quadratic: points at a stated distance from a charge's
+retarded position, so that every point's light time and 1 - n.beta are known.  Against the
+extended-precision oracle, each point relative to its own field (B to the larger of |B|
+and |E| / c: B = n x E / c cancels to beta times that for slow charges), at the parity
+bounds 1e-12 (FP64) and 1e-5 (mixed) plus rounding: the coordinates and the phase carry
+errors of a few eps times the orbit's size and the phase, which the field takes up by
+at most (1 + beta / kappa) (1 + 3 beta / kappa); the mixed path's FP32 terms carry 2^-24."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2107_12437_amd import inputs as I
+from tests.helpers import gpu_ready
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_ready(), reason="needs a GPU")]
+
+EPS = 2.0 ** -53
+TOL = {"fp64": 1e-12, "mixed": 1e-5}
+PRECISIONS = pytest.mark.parametrize("precision", ["fp64", "mixed"])
+KINDS = pytest.mark.parametrize("kind", [I.CIRCULAR, I.LINEAR_OSC])
+
+
+def near_orbit(kind, beta, dist, n=203, seed=0, omega=2 * math.pi * 200e12):
+    """One charge, a time, n points `dist` amplitudes from its retarded position (not a
+    multiple of the wave), their kappa and the size of the rounding in their coordinates."""
+    g = np.random.default_rng((seed, kind, int(1e6 * beta), int(1e3 * dist)))
+    ch = I.empty_charges(1)
+    e1, e2 = I.orbit_basis(g.normal(size=3))
+    amp, phase, t = beta * I.C_LIGHT / omega, g.uniform(0, 2 * math.pi), g.uniform(-2e-14, 2e-14)
+    ch["kind"][:], ch["q"][:], ch["amp"][:], ch["omega"][:], ch["phase"][:] = kind, I.E_CHARGE, amp, omega, phase
+    ch["e1"][0], ch["e2"][0] = e1, e2
+    th = omega * (t - dist * amp / I.C_LIGHT) + phase
+    pos, vel = amp * math.cos(th) * e1, -beta * math.sin(th) * e1
+    if kind == I.CIRCULAR:
+        pos, vel = pos + amp * math.sin(th) * e2, vel + beta * math.cos(th) * e2
+    d = I.unit_sphere(g, n)
+    scale = (1.0 + 1.0 / dist) * (1.0 + abs(omega * t) + abs(th))
+    return ch, t, (pos + dist * amp * d).T.copy(), 1.0 - d @ vel, scale
+
+
+def errors(got, ref):
+    """Largest relative error of each point's Phi, A, E and B, each against its own size."""
+    e_c = np.linalg.norm(ref[4:7], axis=0) / I.C_LIGHT
+    worst = np.abs(got[0] - ref[0]) / np.abs(ref[0])
+    for rows, floor in ((slice(1, 4), np.abs(ref[0]) / I.C_LIGHT), (slice(4, 7), 0.0 * e_c), (slice(7, 10), e_c)):
+        size = np.maximum(np.linalg.norm(ref[rows], axis=0), floor)
+        worst = np.maximum(worst, np.linalg.norm(got[rows] - ref[rows], axis=0) / size)
+    return worst
+
+
+def bounds(precision, beta, kappa, scale):
+    lift = (1.0 + beta / kappa) * (1.0 + 3.0 * beta / kappa)
+    tol = TOL[precision] + 8.0 * EPS * scale * lift
+    return tol if precision == "fp64" else tol + 8.0 * 2.0 ** -24 * lift
+
+
+def gpu_fields(ch, pts, t, precision):
+    import torch
+    from paper_2107_12437_amd import lw
+    out, flags = lw.fields(ch, torch.tensor(pts, device="cuda"), np.array([t]), precision=precision, mask_radius=0.0)
+    torch.cuda.synchronize()
+    assert not flags.any()
+    return out[0].double().cpu().numpy()
+
+
+def check(case, beta, precision):
+    ch, t, pts, kappa, scale = case
+    ref = O.fields(ch, pts, [t], mask_radius=0.0, extended=True)[0][0]
+    worst, tol = errors(gpu_fields(ch, pts, t, precision), ref), bounds(precision, beta, kappa, scale)
+    assert np.isfinite(worst).all()
+    i = int((worst / tol).argmax())
+    assert worst[i] <= tol[i], (worst[i], tol[i], kappa[i])
+
+
+@KINDS
+@PRECISIONS
+@pytest.mark.parametrize("beta", [0.3, 0.6, 0.7])
+@pytest.mark.parametrize("dist", [1.5, 4.0])
+def test_phase_rotation_over_its_range(kind, precision, beta, dist):
+    """The retarded phase lies up to beta + pi / 128 from the start's, through which the
+    solve turns by polynomials."""
+    check(near_orbit(kind, beta, dist), beta, precision)
