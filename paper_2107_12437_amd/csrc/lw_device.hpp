@@ -713,47 +713,70 @@ __device__ __forceinline__ void rot_phase(double c0, double s0, double a, double
     s = s0 * ca - c0 * sa;
 }
 
-// Circular and linear orbits: the root of g (Geo).  One step of order 4 (mixed
-// path) or 5 (FULL, the FP64 path) in FP32 from a = 0, whose phase is known in
-// FP64; then one step of order 3 or 4 in FP64 from the FP64 phase there, and the
-// phase follows by a short rotation.  What remains after an FP64 step e is about
-// 0.04 |e|^3 rad (mixed) and 0.02 |e|^4 rad (FULL), measured over the families and
-// geometries of the grid workloads: accepted at |e| <= 2^-9 it is below 3e-10 rad
-// (mixed, FP32 outputs), at |e| <= 2^-12 below 7e-17 rad (FULL).  About 1 % of the
-// waves hold a lane that is not accepted or whose |a| leaves the range of the
-// phase rotation: false is returned (the caller takes the safeguarded solver).
+// One step e of order 4 towards the root of g (Geo) in FP64 from a, whose phase is turned
+// there from (c0, s0); (c, s) is that phase.  Returns whether a has settled:
+//   |g| < E g',  |g g''| / 2 <= H (g'^2 - g g'' / 2).
+// The second is Kantorovich's condition on Newton's step: met with H far below 1/4, a root
+// lies about g / g' away, of which a step of order 4 leaves H^3.  So the error is relative
+// to the root itself where g bends most: next to a slow orbit g is T^2 less the squared
+// distance, g' = 2 T, and 2 H^4 T is left.  The first bounds the step for the short rotation
+// that follows, and demands g' > 0, which the mirror root at T < 0 does not have (omega < 0
+// turns both signs).  The step's own size would prove neither: it is an absolute
+// phase, which next to a slow charge all of T is below, and it vanishes where its
+// numerator does, root or not.
+template <int KIND, bool FULL>
+__device__ __forceinline__ bool orbit_step(const SrcRec &S, const Geo &g, double c0, double s0, double a, double &c,
+                                           double &s, double &e)
+{
+    constexpr double H = FULL ? 0x1p-13 : 0x1p-12;
+    const double E = copysign(FULL ? 0x1p-12 : 0x1p-11, S.omega);
+    double t[5], num, den;
+    rot_phase<!FULL>(c0, s0, a, c, s);
+    orbit_taylor<KIND, 4, double>(g.w1b, g.w2b, KIND == K_LINEAR_OSC ? S.rt[0] : 0.0, g.T2, g.K, a, c, s, t);
+    pade_step<4, double>(t, num, den);
+    // v_rcp_f64 unrefined (relative error below 2^-26) for the mixed path
+    e = num * (FULL ? rcp_steer(den) : __builtin_amdgcn_rcp(den));
+    const double x2 = t[0] * t[2], d2 = t[1] * t[1] - x2;
+    return fabs(t[0]) < E * t[1] && fabs(x2) <= H * d2 && fabs(a) <= 0.75;
+}
+
+// Circular and linear orbits: the root of g (Geo).  One step of order 5 in FP32 from a = 0,
+// whose phase is known in FP64; then FP64 steps (orbit_step) until one settles, whose
+// phase follows by a short rotation.  1 % of the waves of the grid workloads hold a lane
+// that takes a second FP64 step; a lane that has not settled after four, or whose |a|
+// leaves the range of the phase rotation, takes the safeguarded solver (false is returned).
 //
 // VALU issue bounds the grid kernels, where an FP64 instruction costs as much as an
 // FP32 one (v_rcp_f64 four, v_rcp_f32 two).  So steps of high order, whose extra
 // terms cost two or three instructions each, replace further low-order steps,
-// each of which evaluates the phase anew (about 36): against FP32 Halley steps
-// until one was below 2^-7 and one FP64 Newton step, the 512^2 x 64 x 16 mixed grid
-// went from 1.47 to 1.22 ms per call and
-// the FP64 75^3 x 5 x 16 volume from 0.292 to 0.227 ms.
+// each of which evaluates the phase anew (about 36).  512^2 x 64 x 16 mixed grid, against
+// FP32 Halley steps until one was below 2^-7 and one FP64 Newton step: 1.47 -> 1.21 ms per
+// call, FP64 75^3 x 5 x 16 volume 0.292 -> 0.226 ms.  The first FP64 step stands before
+// the loop: as the loop's own first turn it took 1.32 ms on that grid.
 template <int KIND, bool FULL>
 __device__ __forceinline__ bool solve_orbit(const SrcRec &S, const Geo &g, Kin &k)
 {
     // phase at T0 for this observation time (FP64)
     const double c0 = S.cT * g.cw + S.sT * g.sw;
     const double s0 = S.sT * g.cw - S.cT * g.sw;
-    const double b2 = KIND == K_LINEAR_OSC ? S.rt[0] : 0.0;
-    constexpr int N32 = FULL ? 5 : 4, N64 = FULL ? 4 : 3;
     float t32[5], n32, d32;
-    orbit_taylor<KIND, N32, float>((float)g.w1b, (float)g.w2b, (float)b2, (float)g.T2, (float)g.K, 0.f, (float)c0,
-                                   (float)s0, t32);
-    pade_step<N32, float>(t32, n32, d32);
+    orbit_taylor<KIND, 5, float>((float)g.w1b, (float)g.w2b, KIND == K_LINEAR_OSC ? (float)S.rt[0] : 0.f, (float)g.T2,
+                                 (float)g.K, 0.f, (float)c0, (float)s0, t32);
+    pade_step<5, float>(t32, n32, d32);
     double a = (double)(n32 * __builtin_amdgcn_rcpf(d32));
-    double c, s, t[5], num, den;
-    rot_phase<!FULL>(c0, s0, a, c, s);
-    orbit_taylor<KIND, N64, double>(g.w1b, g.w2b, b2, g.T2, g.K, a, c, s, t);
-    pade_step<N64, double>(t, num, den);
-    // v_rcp_f64 unrefined (relative error below 2^-26) for the mixed path
-    const double e = num * (FULL ? rcp_steer(den) : __builtin_amdgcn_rcp(den));
-    if (!(fabs(a) <= 0.75) || !(fabs(e) <= (FULL ? 0x1p-12 : 0x1p-9))) return false;
+    double c, s, e;
+    int it = 1;
+    bool ok = orbit_step<KIND, FULL>(S, g, c0, s0, a, c, s, e);
+    while (!ok && it < 4) {
+        ++it;
+        a += e;
+        ok = orbit_step<KIND, FULL>(S, g, c0, s0, a, c, s, e);
+    }
+    if (!ok) return false;
     a += e;
     {
         // to fourth order (truncation e^5 / 120 below 1e-19), mixed to second (e^3 / 6
-        // below 1.3e-9)
+        // below 2e-11)
         const double e2 = e * e;
         double ce, se;
         if constexpr (FULL) {
@@ -768,7 +791,7 @@ __device__ __forceinline__ bool solve_orbit(const SrcRec &S, const Geo &g, Kin &
         s = sn;
     }
     k.flags = 0u;
-    k.iters = 2;
+    k.iters = 1 + it;
     k.tp = S.t - fma(0.5, g.T2, a) * S.Lmax;
     k.cph = c;
     k.sph = s;

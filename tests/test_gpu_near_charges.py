@@ -29,13 +29,13 @@ def near_orbit(kind, beta, dist, n=203, seed=0, omega=2 * math.pi * 200e12):
     g = np.random.default_rng((seed, kind, int(1e6 * beta), int(1e3 * dist)))
     ch = I.empty_charges(1)
     e1, e2 = I.orbit_basis(g.normal(size=3))
-    amp, phase, t = beta * I.C_LIGHT / omega, g.uniform(0, 2 * math.pi), g.uniform(-2e-14, 2e-14)
+    amp, phase, t = beta * I.C_LIGHT / abs(omega), g.uniform(0, 2 * math.pi), g.uniform(-2e-14, 2e-14)
     ch["kind"][:], ch["q"][:], ch["amp"][:], ch["omega"][:], ch["phase"][:] = kind, I.E_CHARGE, amp, omega, phase
     ch["e1"][0], ch["e2"][0] = e1, e2
     th = omega * (t - dist * amp / I.C_LIGHT) + phase
-    pos, vel = amp * math.cos(th) * e1, -beta * math.sin(th) * e1
+    pos, vel = amp * math.cos(th) * e1, -amp * omega / I.C_LIGHT * math.sin(th) * e1
     if kind == I.CIRCULAR:
-        pos, vel = pos + amp * math.sin(th) * e2, vel + beta * math.cos(th) * e2
+        pos, vel = pos + amp * math.sin(th) * e2, vel + amp * omega / I.C_LIGHT * math.cos(th) * e2
     d = I.unit_sphere(g, n)
     scale = (1.0 + 1.0 / dist) * (1.0 + abs(omega * t) + abs(th))
     return ch, t, (pos + dist * amp * d).T.copy(), 1.0 - d @ vel, scale
@@ -83,3 +83,38 @@ def test_phase_rotation_over_its_range(kind, precision, beta, dist):
     """The retarded phase lies up to beta + pi / 128 from the start's, through which the
     solve turns by polynomials."""
     check(near_orbit(kind, beta, dist), beta, precision)
+
+
+@KINDS
+@PRECISIONS
+@pytest.mark.parametrize("beta", [1e-6, 1e-3, 3e-3, 0.01, 0.03, 0.1, 0.3, 0.6, 0.9, 0.99])
+def test_near_orbits(kind, precision, beta):
+    """Next to the charge and about its orbit, where the light time is far below a radian
+    of phase for all but the fastest; either sense of rotation."""
+    for k, dist in enumerate((0.02, 0.1, 0.3, 0.5, 1.0, 2.0)):
+        check(near_orbit(kind, beta, dist, omega=(-1) ** k * 2 * math.pi * 200e12), beta, precision)
+        check(near_orbit(kind, beta, dist, omega=-(-1) ** k * 2 * math.pi * 200e12, n=70), beta, precision)
+
+
+@PRECISIONS
+@pytest.mark.parametrize("beta", [0.95, 0.99])
+def test_fast_oscillation_has_one_root(precision, beta):
+    """Where the solve's function has inflections next to no root of it: a step from there
+    can be small."""
+    for dist in (0.5, 1.0, 1.5):
+        check(near_orbit(I.LINEAR_OSC, beta, dist, n=20011), beta, precision)
+
+
+@KINDS
+@pytest.mark.parametrize("beta,dist", [(1e-3, 0.1), (0.01, 0.3), (0.03, 0.5), (0.1, 0.3)])
+def test_gradient_near_orbits(kind, beta, dist):
+    """The gradients take the same solve: against automatic differentiation in torch FP64,
+    to 1e-10 of the parameter's largest gradient (as the other families' test)."""
+    import torch
+    from tests import test_gpu_adjoint_families as F
+    ch, t, pts, _, _ = near_orbit(kind, beta, dist, n=81)
+    cot = F.cotangent(1, pts.shape[1], ("E",))
+    from paper_2107_12437_amd import lw
+    got = lw.fields_vjp(ch, torch.tensor(pts, device="cuda"), np.array([t]), torch.tensor(cot, device="cuda"),
+                        outputs=("E",), mask_radius=0.0).cpu().numpy()
+    F.assert_close(got, F.reference(ch, pts, [t], torch.tensor(cot), ("E",), "total"), 1e-10)
