@@ -829,9 +829,12 @@ __device__ __forceinline__ bool solve_orbit(const SrcRec &S, const Geo &g, Kin &
 // from its position at t, X = w1 - L, in units of D0:
 //   f(u) = u (2 + u) - m (2 X + m) - K0h,  m = (a / 2c)(1 + u)(2t - tau),
 // K0h = (perp^2 + X^2 - D0^2) / D0^2: a polynomial in u whose root is the retarded
-// time's.  One step of order 5 in FP32 from u = 0, then in FP64 steps of order 3
-// (mixed) or 5 (FULL) until one is below 2^-9 or 2^-11, after which about |d|^3 and
-// |d|^5 remain: one such step on 99 % of the pairs of the grid workloads.  Returns
+// time's.  One step of order 5 in FP32 from u = 0, then in FP64 steps of order N = 3
+// (mixed) or 5 (FULL) from where the last one led until that point has settled,
+//   |f| < E f',  |f f''| / 2 <= H (f'^2 - f f'' / 2),
+// as for the orbits (orbit_step): about a root of the physical sign only, of which the
+// step leaves H^(N - 1).  (Behind a charge beyond 0.6 c f has inflections next to no root,
+// where a step is small all the same.)  One such step on 99 % of the pairs of the grid workloads.  Returns
 // false (the caller takes the safeguarded solver) when they do not settle.
 template <int N, typename F>
 __device__ __forceinline__ void accel_taylor(F Xh, F K0h, F gh, F t, F tau0, F u, F f[5])
@@ -877,9 +880,9 @@ __device__ __forceinline__ bool solve_accel_poly(const SrcRec &S, const Geo &g, 
             double f[5], num, den;
             accel_taylor<N64, double>(Xh, K0h, gh, t, tau0, u, f);
             pade_step<N64, double>(f, num, den);
-            const double d = num * (FULL ? rcp_steer(den) : __builtin_amdgcn_rcp(den));
-            u += d;
-            ok = fabs(d) <= (FULL ? 0x1p-11 : 0x1p-9);
+            u += num * (FULL ? rcp_steer(den) : __builtin_amdgcn_rcp(den));
+            const double x2 = f[0] * f[2], d2 = f[1] * f[1] - x2;
+            ok = fabs(f[0]) < (FULL ? 0x1p-11 : 0x1p-9) * f[1] && fabs(x2) <= (FULL ? 0x1p-11 : 0x1p-12) * d2;
         } while (!ok && it < 8);
         const double tau = fma(tau0, u, tau0);
         tp = t - tau;

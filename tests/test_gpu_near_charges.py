@@ -118,3 +118,25 @@ def test_gradient_near_orbits(kind, beta, dist):
     got = lw.fields_vjp(ch, torch.tensor(pts, device="cuda"), np.array([t]), torch.tensor(cot, device="cuda"),
                         outputs=("E",), mask_radius=0.0).cpu().numpy()
     F.assert_close(got, F.reference(ch, pts, [t], torch.tensor(cot), ("E",), "total"), 1e-10)
+
+
+def near_acceleration(speed, share, n, t=1e-15, seed=0):
+    """One charge accelerated from rest to `speed` c at time t, n points on its light sphere
+    of emission time `share` t; as near_orbit."""
+    g = np.random.default_rng((seed, int(1e6 * speed), int(1e6 * share)))
+    ch = I.empty_charges(1)
+    e1 = I.unit_sphere(g, 1)[0]
+    acc, tp = speed * I.C_LIGHT / t, share * t
+    ch["kind"][:], ch["q"][:], ch["accel"][:], ch["e1"][0] = I.ACCEL, I.E_CHARGE, acc, e1
+    d = I.unit_sphere(g, n)
+    pts = (0.5 * acc * tp * tp * e1 + I.C_LIGHT * (t - tp) * d).T.copy()
+    return ch, t, pts, 1.0 - share * speed * (d @ e1), 1.0 + 1.0 / (1.0 - share)
+
+
+@PRECISIONS
+@pytest.mark.parametrize("speed", [1e-3, 0.3, 0.6, 0.8, 0.9, 0.99])
+def test_near_an_accelerated_charge(precision, speed):
+    """From points that see it just started to points within 0.001 c t of it: behind a fast
+    one the solve's polynomial has other roots and inflections."""
+    for share in (0.02, 0.3, 0.4, 0.5, 0.6, 0.7, 0.8, 0.9, 0.95, 0.99, 0.999):
+        check(near_acceleration(speed, share, n=20011), speed * share, precision)
