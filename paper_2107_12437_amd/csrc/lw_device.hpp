@@ -642,24 +642,19 @@ __device__ __forceinline__ void solve_uniform(const SrcRec &S, const double x[3]
 template <int N, typename F>
 __device__ __forceinline__ void pade_step(const F c[5], F &num, F &den)
 {
-    static_assert(N >= 3 && N <= 5, "");
+    static_assert(N == 4 || N == 5, "");
     const F x2 = c[0] * c[2];
     const F d2 = c[1] * c[1] - x2;
-    if constexpr (N == 3) {
-        num = -c[0] * c[1];
-        den = d2;
+    const F f2 = c[0] * c[0];
+    const F x3 = f2 * c[3];
+    const F d3 = c[1] * (d2 - x2) + x3;
+    if constexpr (N == 4) {
+        num = -c[0] * d2;
+        den = d3;
     } else {
-        const F f2 = c[0] * c[0];
-        const F x3 = f2 * c[3];
-        const F d3 = c[1] * (d2 - x2) + x3;
-        if constexpr (N == 4) {
-            num = -c[0] * d2;
-            den = d3;
-        } else {
-            const F x4 = f2 * c[0] * c[4];
-            num = -c[0] * d3;
-            den = c[1] * (d3 + x3) - x2 * d2 - x4;
-        }
+        const F x4 = f2 * c[0] * c[4];
+        num = -c[0] * d3;
+        den = c[1] * (d3 + x3) - x2 * d2 - x4;
     }
 }
 
@@ -673,7 +668,7 @@ __device__ __forceinline__ void orbit_taylor(F w1b, F w2b, F b2, F T2, F K, F a,
         g[0] = a * (T2 + a) + (P - K);
         g[1] = (F)2 * a + (T2 - Q);
         g[2] = (F)-0.5 * P + (F)1;
-        if constexpr (N >= 4) g[3] = Q * (F)(1.0 / 6.0);
+        g[3] = Q * (F)(1.0 / 6.0);
         if constexpr (N >= 5) g[4] = P * (F)(1.0 / 24.0);
     } else {
         const F bc = b2 * c, bs = b2 * s, y = w1b - bc;            // y - bc = -dG / d cos theta
@@ -681,7 +676,7 @@ __device__ __forceinline__ void orbit_taylor(F w1b, F w2b, F b2, F T2, F K, F a,
         g[0] = a * (T2 + a) + (c * y - K);
         g[1] = (F)2 * a + (s * (y - bc) + T2);
         g[2] = (F)-0.5 * cy + (F)1;
-        if constexpr (N >= 4) g[3] = s * ((F)7 * bc - y) * (F)(1.0 / 6.0);
+        g[3] = s * ((F)7 * bc - y) * (F)(1.0 / 6.0);
         if constexpr (N >= 5) g[4] = (cy - (F)6 * (bc * c - bs * s)) * (F)(1.0 / 24.0);
     }
 }
@@ -829,14 +824,15 @@ __device__ __forceinline__ bool solve_orbit(const SrcRec &S, const Geo &g, Kin &
 // from its position at t, X = w1 - L, in units of D0:
 //   f(u) = u (2 + u) - m (2 X + m) - K0h,  m = (a / 2c)(1 + u)(2t - tau),
 // K0h = (perp^2 + X^2 - D0^2) / D0^2: a polynomial in u whose root is the retarded
-// time's.  One step of order 5 in FP32 from u = 0, then in FP64 steps of order N = 3
+// time's.  One step of order 5 in FP32 from u = 0, then in FP64 steps of order N = 4
 // (mixed) or 5 (FULL) from where the last one led until that point has settled,
 //   |f| < E f',  |f f''| / 2 <= H (f'^2 - f f'' / 2),
 // as for the orbits (orbit_step): about a root of the physical sign only, of which the
-// step leaves H^(N - 1).  (Behind a charge beyond 0.6 c f has inflections next to no root,
-// where a step is small all the same.)  One such step on 99 % of the pairs of the grid workloads.  Returns
-// false (the caller takes the safeguarded solver) when they do not settle.
-template <int N, typename F>
+// step leaves H^(N - 1), 2^-36 or 2^-44, of a distance below H.  (Behind a charge beyond
+// 0.6 c f has inflections next to no root, where a step is small all the same.)  One
+// such step on 99 % of the pairs of the grid workloads.  Returns false (the caller takes
+// the safeguarded solver) when they do not settle.
+template <typename F>
 __device__ __forceinline__ void accel_taylor(F Xh, F K0h, F gh, F t, F tau0, F u, F f[5])
 {
     const F tau = tau0 * u + tau0;
@@ -846,8 +842,8 @@ __device__ __forceinline__ void accel_taylor(F Xh, F K0h, F gh, F t, F tau0, F u
     f[0] = u * ((F)2 + u) - (m * (Xh + xm) + K0h);
     f[1] = (F)-2 * mp * xm + ((F)2 + (F)2 * u);
     f[2] = (F)1 - (mpp * xm + mp * mp);
-    if constexpr (N >= 4) f[3] = -mp * mpp;
-    if constexpr (N >= 5) f[4] = (F)-0.25 * mpp * mpp;
+    f[3] = -mp * mpp;
+    f[4] = (F)-0.25 * mpp * mpp;
 }
 
 template <bool FULL>
@@ -856,7 +852,6 @@ __device__ __forceinline__ bool solve_accel_poly(const SrcRec &S, const Geo &g, 
     const double t = S.t, acc = S.accel, L = S.Lmax;
     const double W2 = fma(g.w1, g.w1, g.w2);
     const double ct = C_LIGHT * t;
-    constexpr int N64 = FULL ? 5 : 3;
     k.flags = 0u;
     k.cph = 1.0;
     k.sph = 0.0;
@@ -870,7 +865,7 @@ __device__ __forceinline__ bool solve_accel_poly(const SrcRec &S, const Geo &g, 
         const double iD0 = rcp_steer(D0), tau0 = D0 * INV_C;
         const double Xh = X * iD0, K0h = fma(-D0, D0, Dn2) * (iD0 * iD0), gh = acc * (0.5 * INV_C);
         float f32[5], n32, d32;
-        accel_taylor<5, float>((float)Xh, (float)K0h, (float)gh, (float)t, (float)tau0, 0.f, f32);
+        accel_taylor<float>((float)Xh, (float)K0h, (float)gh, (float)t, (float)tau0, 0.f, f32);
         pade_step<5, float>(f32, n32, d32);
         double u = (double)(n32 * __builtin_amdgcn_rcpf(d32));
         ok = false;
@@ -878,11 +873,11 @@ __device__ __forceinline__ bool solve_accel_poly(const SrcRec &S, const Geo &g, 
         do {
             ++it;
             double f[5], num, den;
-            accel_taylor<N64, double>(Xh, K0h, gh, t, tau0, u, f);
-            pade_step<N64, double>(f, num, den);
-            u += num * (FULL ? rcp_steer(den) : __builtin_amdgcn_rcp(den));
+            accel_taylor<double>(Xh, K0h, gh, t, tau0, u, f);
+            pade_step<FULL ? 5 : 4, double>(f, num, den);
+            u += num * rcp_steer(den);
             const double x2 = f[0] * f[2], d2 = f[1] * f[1] - x2;
-            ok = fabs(f[0]) < (FULL ? 0x1p-11 : 0x1p-9) * f[1] && fabs(x2) <= (FULL ? 0x1p-11 : 0x1p-12) * d2;
+            ok = fabs(f[0]) < 0x1p-11 * f[1] && fabs(x2) <= (FULL ? 0x1p-11 : 0x1p-12) * d2;
         } while (!ok && it < 8);
         const double tau = fma(tau0, u, tau0);
         tp = t - tau;
