@@ -610,18 +610,12 @@ __device__ __forceinline__ void solve_uniform(const SrcRec &S, const double x[3]
     const double ww = wt[0] * wt[0] + wt[1] * wt[1] + wt[2] * wt[2];
     const double den = S.amp;
     const double disc = wv * wv + den * ww;
-    double sq, isq, tau;
-    if (FULL) {
-        sq = sqrt(disc);
-        // the two algebraically equal forms, chosen to avoid cancellation
-        tau = (wv >= 0.0) ? (wv + sq) / den : ww / (sq - wv);
-    } else {
-        root_rsqrt<false>(fmax(disc, 1e-300), sq, isq);
-        // at |v| <= 0.999 c (the same for every lane) the first form alone loses at most
-        // a factor 2 / (1 - |beta|) < 2000 of the root's 2^-40, far below FP32
-        if (den >= 2e-3 * C_LIGHT * C_LIGHT) tau = (wv + sq) * S.omega;
-        else tau = (wv >= 0.0) ? (wv + sq) * S.omega : ww * rcp_steer(sq - wv);
-    }
+    double sq, isq;
+    if (FULL) sq = sqrt(disc);
+    else root_rsqrt<false>(fmax(disc, 1e-300), sq, isq);
+    // the two algebraically equal forms, chosen to avoid cancellation
+    const double tau = FULL ? ((wv >= 0.0) ? (wv + sq) / den : ww / (sq - wv))
+                            : ((wv >= 0.0) ? (wv + sq) * S.omega : ww * rcp_steer(sq - wv));
     k.tp = S.t - tau;
     k.cph = 1.0;
     k.sph = 0.0;
