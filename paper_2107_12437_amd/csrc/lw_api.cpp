@@ -209,13 +209,13 @@ lw_status check_traj(const lw_traj &T, int idx, double t_max)
     return LW_OK;
 }
 
-// Shape class of a grid-field call: precision, field kind, charges, times and
-// the point count rounded up to a power of two.
 // Shape class of a grid call: precision, field kind, charge and time counts, the
 // point count rounded up to a power of two, the set of trajectory families present
-// (bit k for kind k: each family's solver has its own cost and register needs) and
-// the output rows when not all four groups.
-std::string field_key(const lw_opts &o, const lw_traj *ch, int nch, int nt, int64_t npts)
+// (bit k for kind k: each family's solver has its own cost and register needs), the
+// output rows when not all four groups, and whether the call takes fields_kernel (g): its
+// neighbours in the class that go by (point, time) lanes take no shape, so what is noted
+// for them says nothing of it.
+std::string field_key(const lw_opts &o, const lw_traj *ch, int nch, int nt, int64_t npts, bool by_lane)
 {
     int64_t p2 = 1;
     while (p2 < npts) p2 <<= 1;
@@ -225,7 +225,7 @@ std::string field_key(const lw_opts &o, const lw_traj *ch, int nch, int nt, int6
     const int om = lw::output_mask(o.outputs);
     return "fields p" + std::to_string(o.precision) + " k" + std::to_string(o.field_kind) + " c" + std::to_string(nch) +
            " t" + std::to_string(nt) + " n" + std::to_string(p2) + " f" + std::to_string(fam) +
-           (om == 15 ? "" : " o" + std::to_string(om));
+           (om == 15 ? "" : " o" + std::to_string(om)) + (by_lane ? "" : " g");
 }
 
 void load_tune_file(lw_ctx *ctx)
@@ -576,11 +576,12 @@ lw_status lw_fields(lw_ctx *ctx, const lw_traj *h_charges, int32_t n_charges, co
         return LW_OK;
     }
     lw::FieldLaunch L = ctx->field_launch;
-    const std::string key = field_key(*opts, h_charges, n_charges, n_times, n_pts);
+    const bool by_lane = lw::fields_by_lane(n_pts, n_times, n_charges);
+    const std::string key = field_key(*opts, h_charges, n_charges, n_times, n_pts, by_lane);
     auto it = ctx->tuned.find(key);
     if (it != ctx->tuned.end()) {
         L = it->second;
-    } else if (ctx->autotune && lw::fields_by_lane(n_pts, n_times, n_charges)) {
+    } else if (ctx->autotune && by_lane) {
         // a size that takes its own launch whatever the shape: nothing to time
         ctx->tuned[key] = L;
         save_tune_entry(ctx, key, L);
