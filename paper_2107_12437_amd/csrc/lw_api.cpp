@@ -788,7 +788,9 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
 // threshold that splits the instances differently is timed on trial runs of
 // the call's own dipoles, and the fastest is kept.  A trial's per-step cost is
 // the difference of a 704-step and a 448-step run, so the per-call cost of
-// staging and graph capture drops out.  Trials write two rows of moments into
+// staging and graph capture drops out; an untimed run goes before them, since the first
+// of a process loads its kernels (174 ms for a stepped one, which made the difference
+// negative and the threshold the fastest).  Trials write two rows of moments into
 // a context buffer and no run state; tuning synchronises the stream once.
 static lw_status tune_stepped(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_dip, const int32_t *h_inst_off,
                               int32_t n_inst, double dt, const lw_run_opts *opts, int ring, hipStream_t s, int *out)
@@ -856,15 +858,15 @@ static lw_status tune_stepped(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_dip
         float ms[2] = {0.f, 0.f};
         if (hipMemcpy(ctx->d_err, &zero_err, sizeof(uint32_t), hipMemcpyHostToDevice) != hipSuccess)
             st = fail(LW_E_HIP, "tuner error word");
-        for (int r = 0; r < 2 && st == LW_OK; ++r) {
-            const int64_t n_steps = 448 + 256 * r;     // (both replay the same graph, built once each)
+        for (int r = -1; r < 2 && st == LW_OK; ++r) {
+            const int64_t n_steps = r < 1 ? 448 : 704;     // (all replay the same graph, built once each)
             o.out_stride = n_steps;
             if (hipEventRecord(ev[0], s) != hipSuccess) st = fail(LW_E_HIP, "tuner timing");
             if (st == LW_OK)
                 st = dipole_run_impl(ctx, h_dip, n_dip, h_inst_off, n_inst, dt, n_steps, &o, ctx->d_trial, nullptr,
                                      nullptr, nullptr, nullptr, nullptr, nullptr, 0, false, (void *)s);
             if (st == LW_OK && (hipEventRecord(ev[1], s) != hipSuccess || hipEventSynchronize(ev[1]) != hipSuccess ||
-                                hipEventElapsedTime(&ms[r], ev[0], ev[1]) != hipSuccess))
+                                hipEventElapsedTime(&ms[std::max(r, 0)], ev[0], ev[1]) != hipSuccess))
                 st = fail(LW_E_HIP, "tuner timing");
         }
         if (st != LW_OK) break;

@@ -1,6 +1,10 @@
-"""Shape classes of the launch-shape tuner next to the sizes that take a launch of their own:
-a grid call whose lanes are (point, time) pairs has no shape to tune and must not settle
-that of a larger call in the same class (point counts rounded up to a power of two)."""
+"""What the tuners note.  A grid call whose lanes are (point, time) pairs has no launch shape
+to tune and must not settle that of a larger call in the same class (point counts rounded
+up to a power of two); the oscillator runs' threshold is the one that runs fastest."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -36,3 +40,26 @@ def test_a_call_without_a_shape_leaves_its_class_open(tmp_path, monkeypatch, sma
         assert len(lines()) == before + 1
     finally:
         ctx.close()
+
+
+
+COLD = """
+import math, sys
+import numpy as np
+from paper_2107_12437_amd import inputs as I, lw
+parts = [I.cluster_dipoles(I.rng_for(90 + k), 12, 40e-9, 10e-9, 2 * math.pi * 200e12, 0.01, True) for k in range(8)]
+lw.dipole_run(I.concat_dipoles(parts), (12 * np.arange(9)).astype(np.int32), 1 / 200e12 / 200, 50,
+              stepped_min_n="tune", precision=sys.argv[1])
+"""
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_run_tuner_in_a_new_process(tmp_path, precision):
+    """A process's first trial loads its kernels, which must not count: instances of 12 run
+    three times faster per step whole in a workgroup than by launches."""
+    f = tmp_path / "tune.txt"
+    env = dict(os.environ, LW_TUNE_CACHE=str(f), PYTHONPATH=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    env.pop("LW_AUTOTUNE", None)
+    subprocess.run([sys.executable, "-c", COLD, precision], env=env, check=True, timeout=100)
+    lines = [ln for ln in f.read_text().splitlines() if ln.startswith("dipoles")]
+    assert len(lines) == 1 and int(lines[0].split("|")[1]) > 12, lines
