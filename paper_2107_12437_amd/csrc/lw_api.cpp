@@ -782,6 +782,23 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
                                  double *d_moment, double *d_dot, double *d_energy, double *d_drive, double *d_wabs,
                                  double *d_wrad, double *d_state, int64_t n_state, bool resume, void *stream);
 
+// Kind of kernel that holds an instance of n dipoles whole (lw::dipole_kind_max_n; the last
+// kind takes any size and all moving origins), and whether its history fits there.  The
+// kernels with a lane per pair take all of a CU's 160 KB of LDS (96 instances of 5 to 12
+// dipoles with 256 samples, 76 KB for 12: 5.2 us per step by launches, 1.6 there); the
+// general one, slower per step, keeps two workgroups per CU.
+static int dipole_kind(int n, bool moving)
+{
+    int k = 0;
+    while (k < lw_ctx::DIPOLE_KINDS - 1 && (moving || n > lw::dipole_kind_max_n(k))) ++k;
+    return k;
+}
+static bool holds_history(int n, int ring, bool moving)
+{
+    const bool general = dipole_kind(n, moving) == lw_ctx::DIPOLE_KINDS - 1;
+    return lw::ring_lds_bytes(n, ring) <= (general ? 64 * 1024 : 160 * 1024 - 512);
+}
+
 // Stepped-path threshold (stepped_min_n) for a run's shape class: precision,
 // moving origins, dt policy, history depth and the instance sizes by power of
 // two.  Cached in the context (and the LW_TUNE_CACHE file); otherwise each
@@ -807,7 +824,8 @@ static lw_status tune_stepped(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_dip
         ++sizes[b];
         max_n = std::max(max_n, n);
     }
-    std::string key = "dipoles p" + std::to_string(opts->precision) + " m" + std::to_string(moving ? 1 : 0) + " d" +
+    // ("k2": thresholds timed on other kernels, as in files of earlier versions, do not count)
+    std::string key = "dipoles p" + std::to_string(opts->precision) + " k2 m" + std::to_string(moving ? 1 : 0) + " d" +
                       std::to_string(opts->dt_policy) + " r" + std::to_string(ring) + " n";
     for (const auto &kv : sizes) key += " " + std::to_string(1 << kv.first) + ":" + std::to_string(kv.second);
     auto it = ctx->tuned_dip.find(key);
@@ -825,7 +843,7 @@ static lw_status tune_stepped(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_dip
         int stepped = 0;
         for (int k = 0; k < n_inst; ++k) {
             const int n = h_inst_off[k + 1] - h_inst_off[k];
-            if (n > 0 && (n >= T || lw::ring_lds_bytes(n, ring) > 64 * 1024)) ++stepped;
+            if (n > 0 && (n >= T || !holds_history(n, ring, moving))) ++stepped;
         }
         if (stepped != last_split) cand.push_back(T);
         last_split = stepped;
@@ -915,10 +933,7 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     hipStream_t s = (hipStream_t)stream;
 
     // small instances whose ring fits in LDS run whole in one workgroup each; the others
-    // advance one launch per step.  The kernels with a lane per pair take all of a CU's
-    // 160 KB (96 instances of 5 to 12 dipoles with 256 samples, 76 KB for 12: 5.2 us per step by
-    // launches, 1.6 here); the general one, slower per step, keeps two workgroups per CU
-    auto lds_limit = [](int kind) { return kind < lw_ctx::DIPOLE_KINDS - 1 ? 160 * 1024 - 512 : 64 * 1024; };
+    // advance one launch per step
     int stepped_min = opts->stepped_min_n == 0 ? 16 : (opts->stepped_min_n < 0 ? (1 << 30) : opts->stepped_min_n);
     if (opts->stepped_min_n == LW_STEPPED_TUNE) {
         const lw_status tst = tune_stepped(ctx, h_dip, n_dip, h_inst_off, n_inst, dt, opts, ring, s, &stepped_min);
@@ -930,7 +945,6 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     // wave, the next two a workgroup with a lane per pair, the rest (and all moving ones) the general
     // kernel.  Each kind is one launch, so that no instance takes another's slower kernel
     struct Kind {
-        int max_n = 0;                   // largest instance this kind takes
         std::vector<int32_t> list;
         int lo = 1 << 30, hi = 0;        // smallest and largest present
         hipStream_t on = nullptr;
@@ -938,7 +952,6 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     };
     constexpr int KINDS = lw_ctx::DIPOLE_KINDS;
     Kind kinds[KINDS];
-    for (int k = 0; k < KINDS; ++k) kinds[k].max_n = k == KINDS - 1 ? 1 << 30 : moving ? 0 : lw::dipole_kind_max_n(k);
     std::vector<int32_t> tgt, tgt_lo, tgt_n;
     std::vector<int64_t> tgt_base;
     size_t n_listed = 0;
@@ -946,10 +959,8 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     for (int k = 0; k < n_inst; ++k) {
         const int a0 = h_inst_off[k], n = h_inst_off[k + 1] - a0;
         if (n == 0) continue;
-        int q = 0;
-        while (n > kinds[q].max_n) ++q;
-        if (n < stepped_min && lw::ring_lds_bytes(n, ring) <= lds_limit(q)) {
-            Kind &K = kinds[q];
+        if (n < stepped_min && holds_history(n, ring, moving)) {
+            Kind &K = kinds[dipole_kind(n, moving)];
             K.list.push_back(k);
             K.lo = std::min(K.lo, n);
             K.hi = std::max(K.hi, n);

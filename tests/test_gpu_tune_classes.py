@@ -63,3 +63,24 @@ def test_run_tuner_in_a_new_process(tmp_path, precision):
     subprocess.run([sys.executable, "-c", COLD, precision], env=env, check=True, timeout=100)
     lines = [ln for ln in f.read_text().splitlines() if ln.startswith("dipoles")]
     assert len(lines) == 1 and int(lines[0].split("|")[1]) > 12, lines
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_run_tuner_knows_which_histories_fit(tmp_path, monkeypatch, precision):
+    """12 dipoles with 256 samples (76 KB) run whole in one workgroup, three times faster per
+    step than by launches: the threshold must leave them there."""
+    import math
+
+    from paper_2107_12437_amd import lw
+    f = tmp_path / "tune.txt"
+    monkeypatch.setenv("LW_TUNE_CACHE", str(f))
+    parts = [I.cluster_dipoles(I.rng_for(90 + k), 12, 40e-9, 10e-9, 2 * math.pi * 200e12, 0.01, True) for k in range(8)]
+    off = (12 * np.arange(9)).astype(np.int32)
+    ctx = lw.Context(0)
+    try:
+        lw.dipole_run(I.concat_dipoles(parts), off, 1 / 200e12 / 200, 50, ring_depth=256, stepped_min_n="tune",
+                      precision=precision, ctx=ctx)
+        lines = [ln for ln in f.read_text().splitlines() if ln.startswith("dipoles")]
+        assert len(lines) == 1 and int(lines[0].split("|")[1]) > 12, lines
+    finally:
+        ctx.close()
