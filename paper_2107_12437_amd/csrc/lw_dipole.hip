@@ -466,7 +466,10 @@ __device__ __forceinline__ bool small_source(const SmallK &c, const Hist &H, con
     return op && om;
 }
 
-// The same for one charge (kq with its sign).
+// The same for one charge (kq with its sign).  (The kernels for moving origins
+// take the general solvers throughout: the series' registers cost them a wave
+// per SIMD, 2,048 moving instances of 12 in FP64 47.3 us per step with them, 39.8
+// without.)
 __device__ __forceinline__ bool small_one(const SmallK &c, const Hist &H, const PairGeo &P, int j, double d0, double cf, double kq,
                                           int64_t nstep, double theta, double &e, uint32_t &err)
 {
@@ -485,8 +488,10 @@ __device__ __forceinline__ double pair_drive(const SmallK &c, const Hist &H, con
     if (MOVING) origin_at(Si, base * H.dt, X);
     if (!MOVING || Sj.mw == 0.0) {
         const PairGeo P = pair_geo(X, Si, Sj);
-        double e;
-        if (small_one(c, H, P, j, Sj.d0, cf, kq, nstep, theta, e, err)) return e;
+        if constexpr (!MOVING) {
+            double e;
+            if (small_one(c, H, P, j, Sj.d0, cf, kq, nstep, theta, e, err)) return e;
+        }
         return fixed_drive(H, P, j, Sj.d0, cf, kq, nstep, base, max_iter, err);
     }
     if constexpr (MOVING) {
@@ -624,8 +629,10 @@ __device__ __forceinline__ double dipole_drive_mixed(const SmallK &c, const Hist
             return e + charge_field(Si, R, v, a, -kq);
         }
     }
-    double e;
-    if (small_source<true>(c, H, pair_geo(X, Si, Sj), j, Sj.d0, Sj.cfp, Sj.cfm, kq, nstep, theta, e, err)) return e;
+    if constexpr (!MOVING) {
+        double e;
+        if (small_source<true>(c, H, pair_geo(X, Si, Sj), j, Sj.d0, Sj.cfp, Sj.cfm, kq, nstep, theta, e, err)) return e;
+    }
     const MixedGeo G = mixed_geo(X, Si, Sj);
     Seg g;
     g.k = seg_none<int64_t>();
@@ -657,8 +664,10 @@ __device__ __forceinline__ double dipole_drive_fp64(const SmallK &c, const Hist 
         }
     }
     const PairGeo P = pair_geo(X, Si, Sj);
-    double e;
-    if (small_source<false>(c, H, P, j, Sj.d0, Sj.cfp, Sj.cfm, kq, nstep, theta, e, err)) return e;
+    if constexpr (!MOVING) {
+        double e;
+        if (small_source<false>(c, H, P, j, Sj.d0, Sj.cfp, Sj.cfm, kq, nstep, theta, e, err)) return e;
+    }
     Seg g;
     g.k = seg_none<int64_t>();
     double hp[3], hm[3];
@@ -1722,7 +1731,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void lo_group_kernel(
 
 
 template <int BLOCK, bool MOVING, bool MIXED, bool WIDE>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WIDE ? 2 : 3))) void lo_step_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WIDE && !MOVING ? 2 : 3))) void lo_step_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
                                                         const int32_t *__restrict__ tgt_lo,
                                                         const int32_t *__restrict__ tgt_n,
                                                         const int64_t *__restrict__ ring_base, double *__restrict__ ring,
