@@ -1004,6 +1004,7 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
     //   8 of 200 (6,400)  17.2 / 19.2 / 20.0    2 of 540 (9,720)  22.0 / 27.6 / 25.2
     //   1 of 1,100 (19,800, 1.2 M pairs)  34.6 / 48 / 32.9
     lw::TilePlan tiles;
+    if (n_tgt > 0) tiles.max_n = tgt_n[0];
     std::vector<lw::TileUnit> units;
     size_t n_part = 0;
     if (!moving && n_tgt > 1024) {

@@ -1730,8 +1730,12 @@ __attribute__((amdgpu_waves_per_eu(2))) void lo_group_kernel(
 // ---------------------------------------------------------------------------
 
 
-template <int BLOCK, bool MOVING, bool MIXED, bool WIDE>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WIDE && !MOVING ? 2 : 3))) void lo_step_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
+// Register budgets of the launches by targets: FEW targets (at most two workgroups per CU), SOME
+// (up to four) with at most 128 other dipoles each or, SOME_LARGE, with more, and MANY.
+enum StepPlan { MANY, FEW, SOME, SOME_LARGE };
+
+template <int BLOCK, bool MOVING, bool MIXED, int PLAN>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(PLAN == FEW && !MOVING ? 2 : 3))) void lo_step_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
                                                         const int32_t *__restrict__ tgt_lo,
                                                         const int32_t *__restrict__ tgt_n,
                                                         const int64_t *__restrict__ ring_base, double *__restrict__ ring,
@@ -1756,13 +1760,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WIDE && !
     const int nth = init ? 1 : 2;
     // Lane layout.  A launch with many targets is throughput-bound: a lane
     // takes one source for both stage times (the fewest instructions per drive).
-    // A launch with few targets (WIDE: at most one workgroup per SIMD) is a
+    // A launch with few targets (all plans but MANY: at most one workgroup per SIMD) is a
     // latency chain, and the shortest chain that fits the block wins: in FP64
     // one charge per lane (4 drives' worth of lanes per source), else one source
     // per (stage, lane); in the mixed form one source per (stage, lane).  Sources that
     // do not fit so take both stages in a lane (900 dipoles, mixed: 38.9 us per step
     // with a lane per stage).
-    const int layout = !WIDE ? 0 : (!MIXED && 2 * nth * M <= BLOCK) ? 2 : (nth * M <= BLOCK) ? 1 : 0;
+    const int layout = PLAN == MANY ? 0 : (!MIXED && 2 * nth * M <= BLOCK) ? 2 : (nth * M <= BLOCK) ? 1 : 0;
     const int units = layout == 2 ? 2 * nth * M : (layout == 1 ? nth * M : M);
     // the target's own state (only this workgroup writes it, and only at its
     // end): when the last lane has no pair work it reads the state into LDS
@@ -1780,12 +1784,19 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WIDE && !
         own[5] = W[2 * gi + 1];
     }
     // (with many targets the constants sit in scalar registers and three waves share a
-    // SIMD: 10 instances of 160 15.2 us per step, 16.8 at two waves; with few the scalar
-    // moves would lengthen the chain, 4.4 against 4.05 us at 32 dipoles)
-    const SmallK c = small_k<WIDE>();
+    // SIMD: 10 instances of 160 14.9 us per step, 16.8 at two waves; with few the scalar
+    // moves would lengthen the chain, 4.4 against 4.05 us at 32 dipoles.  Two waves hold two
+    // workgroups per CU, so that from 513 targets on some would wait for a second turn: 40
+    // instances of 16 5.9 us per step at two waves, 4.5 at three, 4 of 200 12.0 and 10.4)
+    const SmallK c = small_k<PLAN == FEW || PLAN == SOME>();
     double acc0 = 0.0, acc1 = 0.0;                   // stage t_n + dt/2 (or t = 0), stage t_n + dt
     if (layout == 0) {
-        // a lane takes one source for both stage times
+        // a lane takes one source for both stage times.  A launch of few targets lasts as long
+        // as its slowest workgroup, and at each step some workgroup has a source that
+        // drive_stages does not take.  So such a source goes on in place, on the values it has (3
+        // instances of 200 9.1 us per step, 9.5 in a pass of its own), and where a lane has one
+        // source and a CU at most two workgroups, all take the general solvers at once (1 of 200
+        // 6.1 us per step, 6.9 with drive_stages first; 1 of 300, two rounds, 9.6 and 8.3)
         if (MOVING || init) {
             for (int jj = tid; jj < M; jj += BLOCK) {
                 const int j = jj < i ? jj : jj + 1;
@@ -1794,9 +1805,20 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WIDE && !
                 acc0 += source_drive<MOVING, MIXED>(c, H, Si, Sj, j, qj, nstep, init ? 0.0 : 0.5, max_iter, err);
                 if (!init) acc1 += source_drive<MOVING, MIXED>(c, H, Si, Sj, j, qj, nstep, 1.0, max_iter, err);
             }
-        } else {
+        } else if constexpr (PLAN == FEW || PLAN == SOME_LARGE) {
+            for (int jj = tid; jj < M; jj += BLOCK) {
+                const int j = jj < i ? jj : jj + 1;
+                const DipLds Sj = soa_lds(soa, out.n_dip, (uint32_t)(i0 + j));
+                const double kq = soa_get(soa, out.n_dip, SF_Q, (uint32_t)(i0 + j)) * K_COUL;
+                double eh, ef;
+                if ((PLAN == FEW && M <= BLOCK) || !drive_stages<MIXED>(c, H, Si, Sj, j, kq, nstep, err, eh, ef))
+                    drive_stages_general<MIXED>(H, Si, Sj, j, kq, nstep, max_iter, err, eh, ef);
+                acc0 += eh;
+                acc1 += ef;
+            }
+        } else if constexpr (PLAN == MANY) {
             target_stages<BLOCK, MIXED>(c, H, Si, soa, out.n_dip, i0, i, M, tid, nstep, max_iter, err, acc0, acc1);
-        }
+        }                                            // (SOME's targets all have layout 1 or 2)
     } else if (layout == 2) {
         // FP64, few targets: a lane per (stage, source, charge)
         for (int m = tid; m < 2 * nth * M; m += BLOCK) {
@@ -2304,7 +2326,7 @@ hipError_t launch_dipole_steps(const DipDev *d_dev, const int32_t *d_tgt, const 
     if (n_tgt <= 0) return hipSuccess;
     const dim3 grid((unsigned)n_tgt), block(B);
     // at most one workgroup per SIMD (256 CUs x 4): a latency-bound launch
-    const bool wide = n_tgt <= 1024;
+    const StepPlan plan = n_tgt > 1024 ? MANY : n_tgt <= 512 ? FEW : 2 * (tiles.max_n - 1) <= B ? SOME : SOME_LARGE;
     const double *soa = dip_soa(const_cast<DipDev *>(d_dev), out.n_dip);
     auto step = [&](hipStream_t q, int k, int init) {
         if (tiles.n_units > 0 && !init) {
@@ -2330,9 +2352,13 @@ hipError_t launch_dipole_steps(const DipDev *d_dev, const int32_t *d_tgt, const 
         }
         with_flags(moving, mixed, [&](auto mv, auto mx) {
             constexpr bool MV = decltype(mv)::value, MX = decltype(mx)::value;
-            hipLaunchKernelGGL((wide ? lo_step_kernel<B, MV, MX, true> : lo_step_kernel<B, MV, MX, false>), grid, block, 0,
-                               q, d_dev, d_tgt, d_tgt_lo, d_tgt_n, d_ring_base, d_ring, d_Ecur, d_W, d_step, k, ring, dt,
-                               max_vel, max_iter, init, out, soa, d_err);
+            // (the kernels for moving origins have one budget)
+            auto kernel = plan == MANY                 ? lo_step_kernel<B, MV, MX, MANY>
+                          : plan == FEW || MV          ? lo_step_kernel<B, MV, MX, FEW>
+                          : plan == SOME               ? lo_step_kernel<B, MV, MX, MV ? FEW : SOME>
+                                                       : lo_step_kernel<B, MV, MX, MV ? FEW : SOME_LARGE>;
+            hipLaunchKernelGGL(kernel, grid, block, 0, q, d_dev, d_tgt, d_tgt_lo, d_tgt_n, d_ring_base, d_ring, d_Ecur,
+                               d_W, d_step, k, ring, dt, max_vel, max_iter, init, out, soa, d_err);
         });
     };
     hipLaunchKernelGGL(step_start_kernel, dim3(1), dim3(1), 0, s, d_step, d_resume);

@@ -111,6 +111,7 @@ struct TilePlan {
     double *part = nullptr;
     int rows = 0, tile = 0, chunk = 0;
     bool per_wave = false;   // without units: a wave per target, not a workgroup
+    int max_n = 0;           // largest instance
 };
 void tile_shape(double steps, int *rows, int *tile);
 int tile_targets();

@@ -1,0 +1,45 @@
+"""The launch-per-step kernels by their numbers of targets and sources (few targets, some with
+few or many sources each, many) against the FP64 oracle, across the edges of the choice."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2107_12437_amd import inputs as I
+from tests.helpers import gpu_ready
+from tests.test_gpu_dipole import TOL_MIXED_STATE, assert_state_close
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not gpu_ready(), reason="needs a GPU")]
+
+DT = 1 / 200e12 / 200
+
+
+def batch(n, count):
+    """`count` instances of n, of which the first and the last differ from the rest."""
+    half = 9e-9 * n ** (1 / 3)                 # light times of up to about 5 n^(1/3) / 2 steps
+    parts = [I.cluster_dipoles(I.rng_for(60 + k), n, half, 10e-9, 2 * math.pi * 200e12, 0.01, True) for k in range(3)]
+    pick = [0] + [1] * (count - 2) + [2] if count > 1 else [0]
+    return I.concat_dipoles([parts[k] for k in pick]), (n * np.arange(count + 1)).astype(np.int32), parts
+
+
+# targets: up to 512, 513 to 1,024 with up to 128 other dipoles each or more, over 1,024 with a
+# wave or (4,500 rounds of 64 sources, up to 2,048 targets) a workgroup each
+@pytest.mark.parametrize("n,count", [(16, 32), (16, 33), (129, 4), (130, 4), (130, 3), (257, 1), (258, 1), (258, 2),
+                                     (16, 64), (16, 65), (200, 8)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_targets_and_sources_about_the_plans_edges(precision, n, count):
+    """The first and the last instance as the oracle has them alone (instances do not act on
+    each other), at the run tests' tolerances."""
+    from paper_2107_12437_amd import lw
+    dip, off, parts = batch(n, count)
+    steps = 60 if n == 16 else 24 if n <= 130 else 12
+    r = lw.dipole_run(dip, off, DT, steps, out_stride=4, precision=precision, stepped_min_n=2)
+    for part, lo in ((parts[0], 0), (parts[2], (count - 1) * n))[:count]:
+        got = {k: v.cpu().numpy()[:, lo:lo + n] for k, v in r.items()}
+        w = {"dipoles": part, "inst_off": [0, n]}
+        ref = O.dipole_run(part, [0, n], DT, steps, out_stride=4)
+        if precision == "fp64":
+            assert_state_close(got, ref, w, what=f"{count} x {n}")
+        else:
+            assert_state_close(got, ref, w, keys=("d", "d_dot", "energy"), tol=TOL_MIXED_STATE, what=f"{count} x {n}")
