@@ -1109,7 +1109,9 @@ __global__ __launch_bounds__(64) void lo_small_kernel(const DipDev *__restrict__
     if (tid == 0) s_err = 0u;
     __syncthreads();
 
-    const SmallK sk = small_k<true>();
+    // (mixed: in scalar registers, 241 VGPRs; with them in VGPRs it takes 268 and a SIMD holds one
+    // wave: 2,048 pairs 1.37 us per step, 0.83 so)
+    const SmallK sk = small_k<!MIXED>();
     Hist H{ringp, n, ring - 1, dt, 1.0 / dt};
     uint32_t err = 0u;
     int64_t n0 = 0;
