@@ -2444,7 +2444,16 @@ hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, co
                                                         (int)shmem);
     };
     hipError_t e = hipSuccess;
-    if (ring_lds && !moving && min_n > SMALL_MAX_N && max_n <= GROUP_MAX_N) {
+    // Where instances of 10 and more (FP64: up to 13), or of 5 alone, are many, the SIMDs are full
+    // whichever kernel holds them, and the general one issues less for them.  us per step, FP64
+    // (mixed), by lo_group_kernel / lo_instances_kernel: 12 dipoles x 1,024 5.7 / 6.2 (5.6 / 5.6),
+    // x 2,048 11.4 / 10.5 (11.1 / 9.6), x 8,192 45 / 39 (44 / 36); 15 x 4,096 22.7 / 25.2 (23.9 /
+    // 19.1); 5 x 2,048 2.5 / 2.7 (2.6 / 2.0), x 4,096 4.9 / 4.7 (5.0 / 3.6); 6 x 8,192 9.2 / 10.8
+    // (9.7 / 9.6).  (Its histories are at most 64 KB.)
+    const bool crowded = shmem <= 64 * 1024 &&
+                         ((max_n > GROUP8_MAX_N && max_n <= (mixed ? GROUP_MAX_N : 13) && n_list >= 1536) ||
+                          (max_n == SMALL_MAX_N + 1 && n_list >= 3072));
+    if (ring_lds && !moving && min_n > SMALL_MAX_N && max_n <= GROUP_MAX_N && !crowded) {
         const dim3 block((unsigned)group_threads(max_n));
         with_flags(mixed, group_lg(max_n) == 3, [&](auto mx, auto eight) {
             auto kernel = lo_group_kernel<decltype(mx)::value, decltype(eight)::value ? 3 : 4>;

@@ -1,5 +1,6 @@
-"""The launch-per-step kernels by their numbers of targets and sources (few targets, some with
-few or many sources each, many) against the FP64 oracle, across the edges of the choice."""
+"""The kernels of oscillator runs by their numbers of targets, sources and instances, against
+the FP64 oracle across the edges of each choice: launches per step (few targets, some
+with few or many sources each, many) and instances held whole (few or many)."""
 import math
 
 import numpy as np
@@ -39,6 +40,24 @@ def test_targets_and_sources_about_the_plans_edges(precision, n, count):
         got = {k: v.cpu().numpy()[:, lo:lo + n] for k, v in r.items()}
         w = {"dipoles": part, "inst_off": [0, n]}
         ref = O.dipole_run(part, [0, n], DT, steps, out_stride=4)
+        if precision == "fp64":
+            assert_state_close(got, ref, w, what=f"{count} x {n}")
+        else:
+            assert_state_close(got, ref, w, keys=("d", "d_dot", "energy"), tol=TOL_MIXED_STATE, what=f"{count} x {n}")
+
+
+@pytest.mark.parametrize("n,count", [(5, 3071), (5, 3072), (10, 1535), (10, 1536), (16, 1536)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_many_instances_held_whole(precision, n, count):
+    """The kernel with a lane per pair, and the general one where instances are many."""
+    from paper_2107_12437_amd import lw
+    dip, off, parts = batch(n, count)
+    steps = 100
+    r = lw.dipole_run(dip, off, DT, steps, out_stride=20, precision=precision, stepped_min_n=-1)
+    for part, lo in ((parts[0], 0), (parts[2], (count - 1) * n)):
+        got = {k: v.cpu().numpy()[:, lo:lo + n] for k, v in r.items()}
+        w = {"dipoles": part, "inst_off": [0, n]}
+        ref = O.dipole_run(part, [0, n], DT, steps, out_stride=20)
         if precision == "fp64":
             assert_state_close(got, ref, w, what=f"{count} x {n}")
         else:
