@@ -998,11 +998,12 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
 
     // more than 1,024 fixed targets: by the wave rounds of 64 sources a step takes.  us per
     // step, FP64, by a workgroup per target / a wave per target / units of targets x sources:
-    //   70 instances of 16 (1,120 rounds)  10.5 / 9.0 / 14.7    20 of 96 (3,840)  17.3 / 15.0 / 19.8
-    //   120 of 48 (5,760)                  47 / 23.3 / 18.4     16 of 200 (12,800) 35 / 32 / 25.4
+    //   70 instances of 16 (1,120 rounds)  8.3 / 6.0 / 9.5     20 of 96 (3,840)  15.3 / 11.0 / 17.5
+    //   300 of 16 (4,800)  24.8 / 10.7 / 12.2                  120 of 48 (5,760) 35.6 / 17.0 / 14.9
+    //   16 of 200 (12,800) 26.5 / 23.9 / 23.7
     // and where few targets have many sources each
-    //   8 of 200 (6,400)  17.2 / 19.2 / 20.0    2 of 540 (9,720)  22.0 / 27.6 / 25.2
-    //   1 of 1,100 (19,800, 1.2 M pairs)  34.6 / 48 / 32.9
+    //   8 of 200 (6,400)  15.3 / 15.9 / 18.7    2 of 540 (9,720)  20.5 / 24.9 / 24.1
+    //   1 of 1,100 (19,800, 1.2 M pairs)  33.4 / 45.7 / 32.3
     lw::TilePlan tiles;
     if (n_tgt > 0) tiles.max_n = tgt_n[0];
     std::vector<lw::TileUnit> units;

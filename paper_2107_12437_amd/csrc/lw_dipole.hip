@@ -1946,12 +1946,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(PLAN == F
 // a wave's start (its target's constants, three dependent loads) and end (the
 // target's state, the lane sums, the step) are a chain of several microseconds, which
 // one wave per target pays once for its ceil((n - 1) / 64) rounds, where a workgroup per
-// target paid it in four waves for a quarter of the rounds each.  64 clusters of
-// 12,530 dipoles, per step: 147 us, 156 with a workgroup per
-// target (both on drive_stages; 170 before it).  What bounds it now is half VALU issue
-// (81 us) and half the row gathers (six loads of 64 lines per round).
+// target pays it in four waves for a quarter of the rounds each: 300 instances of 16, FP64,
+// per step 10.5 us, 24.8 by workgroups.  Three waves per SIMD: four leave 128 VGPRs, 26
+// short (11.3 us, and 20 instances of 96 12.7 for 11.0).  Large instances are bound by their
+// row gathers as much as by VALU issue (lo_tile_kernel).
 template <bool MIXED>
-__global__ __launch_bounds__(256, 4) void lo_wave_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
+__global__ __launch_bounds__(256, 3) void lo_wave_kernel(const DipDev *__restrict__ dev, const int32_t *__restrict__ tgt,
                                                          const int32_t *__restrict__ tgt_lo,
                                                          const int32_t *__restrict__ tgt_n,
                                                          const int64_t *__restrict__ ring_base, int n_tgt,
