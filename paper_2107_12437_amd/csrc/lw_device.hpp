@@ -428,8 +428,10 @@ __device__ __forceinline__ void geo_safe(const SrcRec &S, const double x[3], Geo
         g.w3 = w3;
         const double rho = sqrt_rough(w1 * w1 + w2 * w2);
         // the distance to the orbit lies between these, so c tau does too
-        // (widened by 1e-6 to cover the rough square roots)
-        g.lo = sqrt_rough(w3 * w3 + (rho - A) * (rho - A)) * (INV_C * (1.0 - 1e-6));
+        // (widened by 1e-6 to cover the rough square roots; next to the orbit rho's
+        // error is of the size of rho, not of rho - A)
+        const double gap = fmax(fabs(rho - A) - 1e-6 * rho, 0.0);
+        g.lo = sqrt_rough(w3 * w3 + gap * gap) * (INV_C * (1.0 - 1e-6));
         g.hi = sqrt_rough(w3 * w3 + (rho + A) * (rho + A)) * (INV_C * (1.0 + 1e-6));
         g.tau0 = fmin(fmax(sqrt_rough(w1 * w1 + w2 * w2 + w3 * w3 + A * A) * INV_C, g.lo), g.hi);
     } else {

@@ -105,6 +105,15 @@ def test_fast_oscillation_has_one_root(precision, beta):
         check(near_orbit(I.LINEAR_OSC, beta, dist, n=20011), beta, precision)
 
 
+@PRECISIONS
+@pytest.mark.parametrize("beta,dist", [(2e-4, 0.02), (0.82, 0.02), (0.93, 0.011), (0.99, 0.023)])
+def test_bracket_next_to_an_orbit(precision, beta, dist):
+    """Points whose solve ends in the safeguarded solver, seen across the motion (kappa = 1),
+    where the orbit's nearest point is the charge itself: the bracket's end lies at the root
+    but for its own rounding."""
+    check(near_orbit(I.CIRCULAR, beta, dist, n=20011), beta, precision)
+
+
 @KINDS
 @pytest.mark.parametrize("beta,dist", [(1e-3, 0.1), (0.01, 0.3), (0.03, 0.5), (0.1, 0.3)])
 def test_gradient_near_orbits(kind, beta, dist):
