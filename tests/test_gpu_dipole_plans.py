@@ -62,3 +62,39 @@ def test_many_instances_held_whole(precision, n, count):
             assert_state_close(got, ref, w, what=f"{count} x {n}")
         else:
             assert_state_close(got, ref, w, keys=("d", "d_dot", "energy"), tol=TOL_MIXED_STATE, what=f"{count} x {n}")
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_segment_edges_in_the_general_kernel(precision):
+    """The series drives' segment edges and range limits (test_gpu_dipole_series) in instances
+    too large for the kernels with a lane per pair: a pair and 16 far dipoles each."""
+    from tests import test_gpu_dipole_series as S
+    seps = [S.CDT * m * (1 + e) for m in (0.5, 1.0, 2.0, 7.0) for e in (-4e-5, 0.0, 3e-5)]
+    w = S.pairs(seps, [1e-13, 1e-12, 4e-12, 4e-11], 100)
+    g = np.random.default_rng(3)
+    parts = []
+    for k in range(0, len(seps), 2):
+        far = I.cluster_dipoles(g, 16, 60e-9, 12e-9, 2 * math.pi * 200e12, 0.01, True)
+        far["origin"][:, 1] += 300e-9
+        parts += [{q: np.asarray(v)[2 * k:2 * k + 2] for q, v in w["dipoles"].items()}, far]
+    w = dict(w, dipoles=I.concat_dipoles(parts), inst_off=np.arange(0, 18 * (len(parts) // 2) + 1, 18, dtype=np.int32))
+    got = S.gpu_run(w, "extrapolate", precision=precision, stepped_min_n=-1)
+    ref = S.oracle_run(w, "extrapolate")
+    if precision == "fp64":
+        assert_state_close(got, ref, w)
+    else:
+        assert_state_close(got, ref, w, keys=("d", "d_dot", "energy"), tol=TOL_MIXED_STATE)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("moment", [1e-12, 4e-11])
+def test_tiles_of_four_sources(precision, moment):
+    """Light times of 300 steps leave room for four sources' windows; the larger moment puts
+    sources of every round outside the series' range."""
+    from tests import test_gpu_dipole_tile as T
+    w = T.batch(T.SIZES, 30, moment, 720e-9)
+    got = T.gpu_run(w, "strict", precision=precision)
+    for k in (0, 4, 6, 9, 10):
+        a, b = w["inst_off"][k], w["inst_off"][k + 1]
+        alone = T.gpu_run(T.part(w, k), "strict", precision=precision)
+        T.check({q: v[:, a:b] for q, v in got.items()}, alone, T.part(w, k), precision, f"{T.SIZES[k]} dipoles")
