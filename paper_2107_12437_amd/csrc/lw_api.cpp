@@ -1143,9 +1143,9 @@ static lw_status dipole_run_impl(lw_ctx *ctx, const lw_dipole *h_dip, int32_t n_
             LW_HIP(hipStreamWaitEvent(side, ctx->join_a, 0));
             K.on = side;
         }
-        LW_HIP(lw::launch_dipole_instances(d_dev, d_off, d_kind, (int)K.list.size(), K.lo, K.hi, true, nullptr, nullptr,
-                                           ring, steps, dt, max_vel, max_iter, out, moving, mixed, d_state, resume,
-                                           ctx->d_err, K.on));
+        LW_HIP(lw::launch_dipole_instances(d_dev, d_off, d_kind, (int)K.list.size(), K.lo, K.hi, ring, steps,
+                                           dt, max_vel, max_iter, out, moving, mixed, d_state, resume, ctx->d_err,
+                                           K.on));
         d_kind += K.list.size();
     }
     if (n_tgt > 0) {

@@ -265,18 +265,6 @@ __device__ __forceinline__ double halley_step(double tau, double D, double dD, d
     }
     return tn;
 }
-__device__ __forceinline__ double halley_step(double tau, double D, double dD, double ddD, Bracket &b)
-{
-    bool free_step;
-    return halley_step(tau, D, dD, ddD, b, free_step);
-}
-
-// Plain Newton update (same safeguards), for sources whose D'' is not tracked.
-__device__ __forceinline__ double newton_step(double tau, double D, double dD, Bracket &b)
-{
-    return halley_step(tau, D, dD, 0.0, b);
-}
-
 
 // Converged when the last step is below tol_rel (relative), or when both
 // bracket ends have been evaluated and lie within 4 tol_rel of each other

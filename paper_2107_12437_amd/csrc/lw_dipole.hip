@@ -896,14 +896,13 @@ __device__ void drive_all(const SmallK &c, const Hist &H, const DipLds *S, const
     }
 }
 
-template <int BLOCK, bool RING_LDS, bool MOVING, bool MIXED>
+template <int BLOCK, bool MOVING, bool MIXED>
 __global__ __launch_bounds__(BLOCK) void lo_instances_kernel(const DipDev *__restrict__ dev,
                                                              const int32_t *__restrict__ off,
                                                              const int32_t *__restrict__ inst_list, int ring,
                                                              int64_t steps, double dt,
                                                              double max_vel, int max_iter,
-                                                             double *__restrict__ ring_global,
-                                                             const int64_t *__restrict__ ring_off, RunOut out,
+                                                             RunOut out,
                                                              double *__restrict__ state, int resume,
                                                              uint32_t *__restrict__ d_err)
 {
@@ -923,8 +922,7 @@ __global__ __launch_bounds__(BLOCK) void lo_instances_kernel(const DipDev *__res
     double *Wab = Enew + 2 * n;
     double *Wra = Wab + n;
     double *Kc = Wra + n;                       // [6][n]
-    double *ring_lds = Kc + 6 * n;
-    double *ringp = RING_LDS ? ring_lds : ring_global + ring_off[blockIdx.x];
+    double *ringp = Kc + 6 * n;
     __shared__ uint32_t s_err;
 
     for (int j = tid; j < n; j += BLOCK) {
@@ -2405,23 +2403,15 @@ int ring_lds_bytes(int n, int ring)
 }
 
 template <int BLOCK>
-static hipError_t launch_lo(bool ring_lds, bool moving, bool mixed, dim3 grid, size_t shmem, hipStream_t s,
-                            const DipDev *d_dev, const int32_t *d_off, const int32_t *d_list, int ring, int64_t steps,
-                            double dt, double max_vel, int max_iter, double *d_ring_global,
-                            const int64_t *d_ring_off, const RunOut &out, double *d_state, bool resume,
+static hipError_t launch_lo(bool moving, bool mixed, dim3 grid, size_t shmem, hipStream_t s, const DipDev *d_dev,
+                            const int32_t *d_off, const int32_t *d_list, int ring, int64_t steps, double dt,
+                            double max_vel, int max_iter, const RunOut &out, double *d_state, bool resume,
                             uint32_t *d_err)
 {
-    const int rs = resume ? 1 : 0;
     with_flags(moving, mixed, [&](auto mv, auto mx) {
-        constexpr bool MV = decltype(mv)::value, MX = decltype(mx)::value;
-        if (ring_lds)
-            hipLaunchKernelGGL((lo_instances_kernel<BLOCK, true, MV, MX>), grid, dim3(BLOCK), shmem, s, d_dev, d_off,
-                               d_list, ring, steps, dt, max_vel, max_iter, d_ring_global, d_ring_off, out, d_state,
-                               rs, d_err);
-        else
-            hipLaunchKernelGGL((lo_instances_kernel<BLOCK, false, MV, MX>), grid, dim3(BLOCK), shmem, s, d_dev,
-                               d_off, d_list, ring, steps, dt, max_vel, max_iter, d_ring_global, d_ring_off, out,
-                               d_state, rs, d_err);
+        hipLaunchKernelGGL((lo_instances_kernel<BLOCK, decltype(mv)::value, decltype(mx)::value>), grid, dim3(BLOCK),
+                           shmem, s, d_dev, d_off, d_list, ring, steps, dt, max_vel, max_iter, out, d_state,
+                           resume ? 1 : 0, d_err);
     });
     return hipGetLastError();
 }
@@ -2429,13 +2419,12 @@ static hipError_t launch_lo(bool ring_lds, bool moving, bool mixed, dim3 grid, s
 int dipole_kind_max_n(int kind) { return kind == 0 ? SMALL_MAX_N : kind == 1 ? GROUP8_MAX_N : GROUP_MAX_N; }
 
 hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, const int32_t *d_list, int n_list,
-                                   int min_n, int max_n, bool ring_lds, const int64_t *d_ring_off, double *d_ring_global,
-                                   int ring, int64_t steps, double dt, double max_vel, int max_iter,
+                                   int min_n, int max_n, int ring, int64_t steps, double dt, double max_vel, int max_iter,
                                    const RunOut &out, bool moving, bool mixed, double *d_state, bool resume,
                                    uint32_t *d_err, hipStream_t s)
 {
     if (n_list <= 0) return hipSuccess;
-    const size_t shmem = (size_t)ring_lds_bytes(max_n, ring_lds ? ring : 0);
+    const size_t shmem = (size_t)ring_lds_bytes(max_n, ring);
     const dim3 grid((unsigned)n_list);
     // more than the default 64 KB of dynamic LDS is asked for per kernel
     auto roomy = [&](auto kernel) {
@@ -2453,7 +2442,7 @@ hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, co
     const bool crowded = shmem <= 64 * 1024 &&
                          ((max_n > GROUP8_MAX_N && max_n <= (mixed ? GROUP_MAX_N : 13) && n_list >= 1536) ||
                           (max_n == SMALL_MAX_N + 1 && n_list >= 3072));
-    if (ring_lds && !moving && min_n > SMALL_MAX_N && max_n <= GROUP_MAX_N && !crowded) {
+    if (!moving && min_n > SMALL_MAX_N && max_n <= GROUP_MAX_N && !crowded) {
         const dim3 block((unsigned)group_threads(max_n));
         with_flags(mixed, group_lg(max_n) == 3, [&](auto mx, auto eight) {
             auto kernel = lo_group_kernel<decltype(mx)::value, decltype(eight)::value ? 3 : 4>;
@@ -2463,7 +2452,7 @@ hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, co
         });
         return e != hipSuccess ? e : hipGetLastError();
     }
-    if (ring_lds && !moving && max_n <= SMALL_MAX_N) {
+    if (!moving && max_n <= SMALL_MAX_N) {
         auto kernel = mixed ? lo_small_kernel<true> : lo_small_kernel<false>;
         if ((e = roomy(kernel)) != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, grid, dim3(64), shmem, s, d_dev, d_off, d_list, ring, steps, dt, max_vel, max_iter,
@@ -2471,10 +2460,10 @@ hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, co
         return hipGetLastError();
     }
     if (max_n <= 8)
-        return launch_lo<64>(ring_lds, moving, mixed, grid, shmem, s, d_dev, d_off, d_list, ring, steps, dt, max_vel,
-                             max_iter, d_ring_global, d_ring_off, out, d_state, resume, d_err);
-    return launch_lo<256>(ring_lds, moving, mixed, grid, shmem, s, d_dev, d_off, d_list, ring, steps, dt, max_vel,
-                          max_iter, d_ring_global, d_ring_off, out, d_state, resume, d_err);
+        return launch_lo<64>(moving, mixed, grid, shmem, s, d_dev, d_off, d_list, ring, steps, dt, max_vel, max_iter,
+                             out, d_state, resume, d_err);
+    return launch_lo<256>(moving, mixed, grid, shmem, s, d_dev, d_off, d_list, ring, steps, dt, max_vel, max_iter, out,
+                          d_state, resume, d_err);
 }
 
 }  // namespace lw

@@ -77,19 +77,17 @@ struct DipDev;     // device-side oscillator constants
 size_t dip_dev_bytes(int n);   // the DipDev array and its structure-of-arrays copy
 int ring_lds_bytes(int n, int ring);
 hipError_t launch_dipole_prep(const lw_dipole *d_in, int n, double dt, DipDev *d_dev, hipStream_t s);
-// Largest instance (fixed origins, ring in LDS) of the one-wave kernel (kind 0) and of the
+// Largest instance (fixed origins) of the one-wave kernel (kind 0) and of the
 // one-workgroup kernel with a lane per pair, 8 (kind 1) and 16 (kind 2) lanes a target; a
 // list takes the first kind that holds all its sizes, the general kernel beyond the last.
 int dipole_kind_max_n(int kind);
 // One launch of the per-instance persistent kernel over the instances listed in
-// d_list[0..n_list); max_n is the largest of them and min_n the
-// smallest.  With ring_lds the history
-// ring lives in LDS, otherwise at d_ring_global + d_ring_off[block].
+// d_list[0..n_list); max_n is the largest of them and min_n the smallest.  The history
+// ring lives in LDS.
 // d_state (nullable): the run state, read at the start when resume is set and
 // written at the end.
 hipError_t launch_dipole_instances(const DipDev *d_dev, const int32_t *d_off, const int32_t *d_list, int n_list,
-                                   int min_n, int max_n, bool ring_lds, const int64_t *d_ring_off, double *d_ring_global,
-                                   int ring, int64_t steps, double dt, double max_vel, int max_iter,
+                                   int min_n, int max_n, int ring, int64_t steps, double dt, double max_vel, int max_iter,
                                    const RunOut &out, bool moving, bool mixed, double *d_state, bool resume,
                                    uint32_t *d_err, hipStream_t s);
 // A resumed run: checks the state's header against (ring, n_dip) and writes
