@@ -729,9 +729,10 @@ __device__ __forceinline__ bool orbit_step(const SrcRec &S, const Geo &g, double
 // FP32 one (v_rcp_f64 four, v_rcp_f32 two).  So steps of high order, whose extra
 // terms cost two or three instructions each, replace further low-order steps,
 // each of which evaluates the phase anew (about 36).  512^2 x 64 x 16 mixed grid, against
-// FP32 Halley steps until one was below 2^-7 and one FP64 Newton step: 1.47 -> 1.21 ms per
-// call, FP64 75^3 x 5 x 16 volume 0.292 -> 0.226 ms.  The first FP64 step stands before
-// the loop: as the loop's own first turn it took 1.32 ms on that grid.
+// FP32 Halley steps until one was below 2^-7 and one FP64 Newton step: 1.47 -> 1.24 to
+// 1.32 ms per call by its mix of charges, FP64 75^3 x 5 x 16 volume 0.292 -> 0.226 ms.  The
+// first FP64 step stands before the loop: as the loop's own first turn 1.32 ms on that
+// grid, 1.29 so.
 template <int KIND, bool FULL>
 __device__ __forceinline__ bool solve_orbit(const SrcRec &S, const Geo &g, Kin &k)
 {
@@ -923,7 +924,7 @@ __device__ __forceinline__ void retarded_fallback(const SrcRec &S, const Geo &g,
 // Retarded kinematics of a source S of family KIND (its record for the
 // observation time) seen from point x, with g = geo_prepare_k<KIND>(record of any
 // time of this source, x).  FULL: to FP64 rounding; otherwise for FP32 fields
-// (phases good to about 1e-9).  Only the fallback can fail to converge: its flags
+// (phases good to about 2e-11).  Only the fallback can fail to converge: its flags
 // are added to `flags` there, off the usual path.
 template <bool FULL, int KIND>
 __device__ __forceinline__ void retarded_kind(const SrcRec &S, const Geo &g, const double x[3], int max_iter,

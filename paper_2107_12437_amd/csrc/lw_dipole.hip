@@ -1389,7 +1389,8 @@ __global__ __launch_bounds__(64) void lo_small_kernel(const DipDev *__restrict__
 // here: 8 dipoles 4.0 -> 0.94 (3.9 -> 0.99), 12 dipoles 3.4 -> 1.51 (3.7 -> 1.48); 2,048
 // instances of 7 5.1 -> 3.1 (5.9 -> 3.0), 1,024 of 12 6.2 -> 6.0 (8.8 -> 5.8).  The series'
 // constants sit in scalar registers and waves_per_eu(2) caps the rest at 256 VGPRs: above
-// that a SIMD holds one wave (4.0 us for the 2,048 instances).
+// that a SIMD holds one wave (4.0 us for the 2,048 instances).  The mixed form is 12 short
+// of that and spills 48 bytes a lane, which its times above include.
 // ---------------------------------------------------------------------------
 constexpr int GROUP8_MAX_N = 9, GROUP_MAX_N = 16;
 constexpr int DPP_MIRROR16 = 0x140;
