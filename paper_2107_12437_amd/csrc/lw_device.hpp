@@ -99,8 +99,8 @@ __device__ __forceinline__ double fma_k(double a, double b, double k)
     return r;
 }
 
-// sin and cos of a small angle |x| <= 0.75 from their Taylor series (terms
-// through x^17 and x^16; the truncation error is below 1e-18).
+// sin and cos of a small angle from their Taylor series (terms through x^17 and x^16;
+// the truncation error is below 1e-18 for |x| <= 0.75 and 9e-16 for |x| <= 1.1).
 __device__ __forceinline__ void sincos_small(double x, double &s, double &c)
 {
     const double x2 = x * x;
@@ -702,28 +702,38 @@ __device__ __forceinline__ void rot_phase(double c0, double s0, double a, double
 // that follows, and demands g' > 0, which the mirror root at T < 0 does not have (omega < 0
 // turns both signs).  The step's own size would prove neither: it is an absolute
 // phase, which next to a slow charge all of T is below, and it vanishes where its
-// numerator does, root or not.
-template <int KIND, bool FULL>
+// numerator does, root or not.  WIDE (the further steps): |a| up to 1.1, which holds every
+// root (|a| <= beta + pi / 128), by longer series; otherwise up to 0.75.
+template <int KIND, bool FULL, bool WIDE>
 __device__ __forceinline__ bool orbit_step(const SrcRec &S, const Geo &g, double c0, double s0, double a, double &c,
                                            double &s, double &e)
 {
     constexpr double H = FULL ? 0x1p-13 : 0x1p-12;
     const double E = copysign(FULL ? 0x1p-12 : 0x1p-11, S.omega);
     double t[5], num, den;
-    rot_phase<!FULL>(c0, s0, a, c, s);
+    if constexpr (WIDE) {
+        double sa, ca;
+        sincos_small(a, sa, ca);
+        c = c0 * ca + s0 * sa;
+        s = s0 * ca - c0 * sa;
+    } else {
+        rot_phase<!FULL>(c0, s0, a, c, s);
+    }
     orbit_taylor<KIND, 4, double>(g.w1b, g.w2b, KIND == K_LINEAR_OSC ? S.rt[0] : 0.0, g.T2, g.K, a, c, s, t);
     pade_step<4, double>(t, num, den);
     // v_rcp_f64 unrefined (relative error below 2^-26) for the mixed path
     e = num * (FULL ? rcp_steer(den) : __builtin_amdgcn_rcp(den));
     const double x2 = t[0] * t[2], d2 = t[1] * t[1] - x2;
-    return fabs(t[0]) < E * t[1] && fabs(x2) <= H * d2 && fabs(a) <= 0.75;
+    return fabs(t[0]) < E * t[1] && fabs(x2) <= H * d2 && fabs(a) <= (WIDE ? 1.1 : 0.75);
 }
 
 // Circular and linear orbits: the root of g (Geo).  One step of order 5 in FP32 from a = 0,
 // whose phase is known in FP64; then FP64 steps (orbit_step) until one settles, whose
 // phase follows by a short rotation.  1 % of the waves of the grid workloads hold a lane
-// that takes a second FP64 step; a lane that has not settled after four, or whose |a|
-// leaves the range of the phase rotation, takes the safeguarded solver (false is returned).
+// that takes a second FP64 step, most waves beyond 0.7 c, where |a| leaves the first step's
+// range; one that has not settled after four takes the safeguarded solver (false is
+// returned).  512^2 x 16 x 16 orbits at 0.9 c, mixed, 0.37 ms, 0.72 with those lanes left to
+// the safeguarded solver.
 //
 // VALU issue bounds the grid kernels, where an FP64 instruction costs as much as an
 // FP32 one (v_rcp_f64 four, v_rcp_f32 two).  So steps of high order, whose extra
@@ -746,11 +756,11 @@ __device__ __forceinline__ bool solve_orbit(const SrcRec &S, const Geo &g, Kin &
     double a = (double)(n32 * __builtin_amdgcn_rcpf(d32));
     double c, s, e;
     int it = 1;
-    bool ok = orbit_step<KIND, FULL>(S, g, c0, s0, a, c, s, e);
+    bool ok = orbit_step<KIND, FULL, false>(S, g, c0, s0, a, c, s, e);
     while (!ok && it < 4) {
         ++it;
         a += e;
-        ok = orbit_step<KIND, FULL>(S, g, c0, s0, a, c, s, e);
+        ok = orbit_step<KIND, FULL, true>(S, g, c0, s0, a, c, s, e);
     }
     if (!ok) return false;
     a += e;

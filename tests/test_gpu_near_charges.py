@@ -77,7 +77,7 @@ def check(case, beta, precision):
 
 @KINDS
 @PRECISIONS
-@pytest.mark.parametrize("beta", [0.3, 0.6, 0.7])
+@pytest.mark.parametrize("beta", [0.3, 0.6, 0.7, 0.9, 0.98])
 @pytest.mark.parametrize("dist", [1.5, 4.0])
 def test_phase_rotation_over_its_range(kind, precision, beta, dist):
     """The retarded phase lies up to beta + pi / 128 from the start's, through which the
