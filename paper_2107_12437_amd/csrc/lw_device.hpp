@@ -626,19 +626,24 @@ __device__ __forceinline__ void solve_uniform(const SrcRec &S, const double x[3]
 template <int N, typename F>
 __device__ __forceinline__ void pade_step(const F c[5], F &num, F &den)
 {
-    static_assert(N == 4 || N == 5, "");
+    static_assert(N >= 3 && N <= 5, "");
     const F x2 = c[0] * c[2];
     const F d2 = c[1] * c[1] - x2;
-    const F f2 = c[0] * c[0];
-    const F x3 = f2 * c[3];
-    const F d3 = c[1] * (d2 - x2) + x3;
-    if constexpr (N == 4) {
-        num = -c[0] * d2;
-        den = d3;
+    if constexpr (N == 3) {
+        num = -c[0] * c[1];
+        den = d2;
     } else {
-        const F x4 = f2 * c[0] * c[4];
-        num = -c[0] * d3;
-        den = c[1] * (d3 + x3) - x2 * d2 - x4;
+        const F f2 = c[0] * c[0];
+        const F x3 = f2 * c[3];
+        const F d3 = c[1] * (d2 - x2) + x3;
+        if constexpr (N == 4) {
+            num = -c[0] * d2;
+            den = d3;
+        } else {
+            const F x4 = f2 * c[0] * c[4];
+            num = -c[0] * d3;
+            den = c[1] * (d3 + x3) - x2 * d2 - x4;
+        }
     }
 }
 
@@ -652,7 +657,7 @@ __device__ __forceinline__ void orbit_taylor(F w1b, F w2b, F b2, F T2, F K, F a,
         g[0] = a * (T2 + a) + (P - K);
         g[1] = (F)2 * a + (T2 - Q);
         g[2] = (F)-0.5 * P + (F)1;
-        g[3] = Q * (F)(1.0 / 6.0);
+        if constexpr (N >= 4) g[3] = Q * (F)(1.0 / 6.0);
         if constexpr (N >= 5) g[4] = P * (F)(1.0 / 24.0);
     } else {
         const F bc = b2 * c, bs = b2 * s, y = w1b - bc;            // y - bc = -dG / d cos theta
@@ -660,7 +665,7 @@ __device__ __forceinline__ void orbit_taylor(F w1b, F w2b, F b2, F T2, F K, F a,
         g[0] = a * (T2 + a) + (c * y - K);
         g[1] = (F)2 * a + (s * (y - bc) + T2);
         g[2] = (F)-0.5 * cy + (F)1;
-        g[3] = s * ((F)7 * bc - y) * (F)(1.0 / 6.0);
+        if constexpr (N >= 4) g[3] = s * ((F)7 * bc - y) * (F)(1.0 / 6.0);
         if constexpr (N >= 5) g[4] = (cy - (F)6 * (bc * c - bs * s)) * (F)(1.0 / 24.0);
     }
 }
@@ -692,24 +697,28 @@ __device__ __forceinline__ void rot_phase(double c0, double s0, double a, double
     s = s0 * ca - c0 * sa;
 }
 
-// One step e of order 4 towards the root of g (Geo) in FP64 from a, whose phase is turned
-// there from (c0, s0); (c, s) is that phase.  Returns whether a has settled:
+// One step e of order N = 3 (mixed path) or 4 (FULL) towards the root of g (Geo) in FP64
+// from a, whose phase is turned there from (c0, s0); (c, s) is that phase.  Returns whether
+// a has settled:
 //   |g| < E g',  |g g''| / 2 <= H (g'^2 - g g'' / 2).
 // The second is Kantorovich's condition on Newton's step: met with H far below 1/4, a root
-// lies about g / g' away, of which a step of order 4 leaves H^3.  So the error is relative
-// to the root itself where g bends most: next to a slow orbit g is T^2 less the squared
-// distance, g' = 2 T, and 2 H^4 T is left.  The first bounds the step for the short rotation
-// that follows, and demands g' > 0, which the mirror root at T < 0 does not have (omega < 0
-// turns both signs).  The step's own size would prove neither: it is an absolute
-// phase, which next to a slow charge all of T is below, and it vanishes where its
-// numerator does, root or not.  WIDE (the further steps): |a| up to 1.1, which holds every
-// root (|a| <= beta + pi / 128), by longer series; otherwise up to 0.75.
+// lies about g / g' away, of which a step of order N leaves H^(N - 1).  So the error is
+// relative to the root itself where g bends most: next to a slow orbit g is T^2 less the
+// squared distance, g' = 2 T, and 2 H^N T is left, 4e-12 T or 4e-16 T.  The first bounds the
+// step for the short rotation that follows, and demands g' > 0, which the mirror root at
+// T < 0 does not have (omega < 0 turns both signs).  The step's own size would prove
+// neither: it is an absolute phase, which next to a slow charge all of T is below, and it
+// vanishes where its numerator does, root or not.  WIDE (the further steps): |a| up to 1.1, by
+// longer series, which holds the roots of all but points close to the fastest orbits (|a|
+// is at most beta away from the orbit, sqrt 2 beta on it, and pi / 128 for the grid);
+// otherwise up to 0.75.
 template <int KIND, bool FULL, bool WIDE>
 __device__ __forceinline__ bool orbit_step(const SrcRec &S, const Geo &g, double c0, double s0, double a, double &c,
                                            double &s, double &e)
 {
-    constexpr double H = FULL ? 0x1p-13 : 0x1p-12;
-    const double E = copysign(FULL ? 0x1p-12 : 0x1p-11, S.omega);
+    constexpr int N = FULL ? 4 : 3;
+    constexpr double H = 0x1p-13;
+    const double E = copysign(0x1p-12, S.omega);
     double t[5], num, den;
     if constexpr (WIDE) {
         double sa, ca;
@@ -719,8 +728,8 @@ __device__ __forceinline__ bool orbit_step(const SrcRec &S, const Geo &g, double
     } else {
         rot_phase<!FULL>(c0, s0, a, c, s);
     }
-    orbit_taylor<KIND, 4, double>(g.w1b, g.w2b, KIND == K_LINEAR_OSC ? S.rt[0] : 0.0, g.T2, g.K, a, c, s, t);
-    pade_step<4, double>(t, num, den);
+    orbit_taylor<KIND, N, double>(g.w1b, g.w2b, KIND == K_LINEAR_OSC ? S.rt[0] : 0.0, g.T2, g.K, a, c, s, t);
+    pade_step<N, double>(t, num, den);
     // v_rcp_f64 unrefined (relative error below 2^-26) for the mixed path
     e = num * (FULL ? rcp_steer(den) : __builtin_amdgcn_rcp(den));
     const double x2 = t[0] * t[2], d2 = t[1] * t[1] - x2;
@@ -766,7 +775,7 @@ __device__ __forceinline__ bool solve_orbit(const SrcRec &S, const Geo &g, Kin &
     a += e;
     {
         // to fourth order (truncation e^5 / 120 below 1e-19), mixed to second (e^3 / 6
-        // below 2e-11)
+        // below 3e-12)
         const double e2 = e * e;
         double ce, se;
         if constexpr (FULL) {
@@ -934,7 +943,7 @@ __device__ __forceinline__ void retarded_fallback(const SrcRec &S, const Geo &g,
 // Retarded kinematics of a source S of family KIND (its record for the
 // observation time) seen from point x, with g = geo_prepare_k<KIND>(record of any
 // time of this source, x).  FULL: to FP64 rounding; otherwise for FP32 fields
-// (phases good to about 2e-11).  Only the fallback can fail to converge: its flags
+// (phases good to about 5e-12).  Only the fallback can fail to converge: its flags
 // are added to `flags` there, off the usual path.
 template <bool FULL, int KIND>
 __device__ __forceinline__ void retarded_kind(const SrcRec &S, const Geo &g, const double x[3], int max_iter,
