@@ -748,10 +748,10 @@ __device__ __forceinline__ bool orbit_step(const SrcRec &S, const Geo &g, double
 // FP32 one (v_rcp_f64 four, v_rcp_f32 two).  So steps of high order, whose extra
 // terms cost two or three instructions each, replace further low-order steps,
 // each of which evaluates the phase anew (about 36).  512^2 x 64 x 16 mixed grid, against
-// FP32 Halley steps until one was below 2^-7 and one FP64 Newton step: 1.47 -> 1.24 to
-// 1.32 ms per call by its mix of charges, FP64 75^3 x 5 x 16 volume 0.292 -> 0.226 ms.  The
+// FP32 Halley steps until one was below 2^-7 and one FP64 Newton step: 1.47 -> 1.22 to
+// 1.26 ms per call by its mix of charges, FP64 75^3 x 5 x 16 volume 0.292 -> 0.226 ms.  The
 // first FP64 step stands before the loop: as the loop's own first turn 1.32 ms on that
-// grid, 1.29 so.
+// grid, 1.29 so (both with steps of order 4).
 template <int KIND, bool FULL>
 __device__ __forceinline__ bool solve_orbit(const SrcRec &S, const Geo &g, Kin &k)
 {
